@@ -60,7 +60,8 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 // persistent-plan shape: trajectories per workgroup, threads, trajectories
 // per lane in the step loop, column indices staged in LDS
 struct TileCfg {
-  int T, threads, vec, csr, dreg, ipt, sb;  // sb: one iterate buffer (steps gather into registers first)
+  int T, threads, vec, csr, dreg, ipt;
+  int sb;  // 1: one iterate buffer (steps gather into registers first), TILE_ELL: sliced adjacency
 };
 
 struct Resources {
@@ -291,7 +292,7 @@ int64_t max_graph_rows(const mqo_graph *g) {
 struct Layout {
   size_t X, Xt, V, Z, Zb, NB, PRIO, F, value, best, acc, act, voff, rpat, bestb, dmax, err, reset, tzs, tnb, tprio,
       tfl, tvm, tls, gorder, lsval, pX, pXt, pV, colact, fixedc, steps, pz[2], pv[2], ph[2], chash, ptaken, psrc,
-      pbase, solz, solv, choice, total;
+      pbase, solz, solv, choice, eord, estart, eblock, total;
 };
 
 // K: pool slots per graph (0 = no pool); the pool buffers come last, so the
@@ -350,6 +351,11 @@ Layout make_layout(const mqo_graph *g, int32_t B, int32_t K = 0) {
   L.solz = take(K ? n : 0);  // the pool modes' best set (I_sol / S_sol) and its value
   L.solv = take(K ? G * 8 : 0);
   L.choice = take(K ? G * 4 : 0);
+  // persistent plan: the sliced adjacency (shapes that any tile can have)
+  const bool ell = max_graph_rows(g) <= 8192 && !g->weight;
+  L.eord = take(ell ? n * 2 : 0);
+  L.estart = take(ell ? ell_start_bytes(n, G) : 0);
+  L.eblock = take(ell ? ell_block_bytes(n, g->nnz_total, G) : 0);
   L.total = o;
   return L;
 }
@@ -1242,9 +1248,9 @@ int64_t nnz_max_of(const Solve &S) {
 }
 
 bool tile_feasible(const Solve &S, const TileCfg &c) {
-  return tile_shape_ok(S.n_max, c.T, c.threads, c.vec, c.csr != 0, c.dreg, c.ipt, c.sb != 0) &&
-         (int64_t)tile_lds_bytes(S.n_max, c.T, nnz_max_of(S), c.csr != 0, c.dreg > 0, c.sb != 0) <=
-             tile_lds_budget();
+  return tile_shape_ok(S.n_max, c.T, c.threads, c.vec, c.csr != 0, c.dreg, c.ipt, c.sb) &&
+         !(c.sb == TILE_ELL && S.g->weight) &&
+         (int64_t)tile_lds_bytes(S.n_max, c.T, nnz_max_of(S), c.csr != 0, c.dreg > 0, c.sb) <= tile_lds_budget();
 }
 
 // any shape at all fits (plan selection)
@@ -1327,6 +1333,9 @@ TileArgs tile_args(Solve &S, const TileCfg &c, const float *x0) {
   a.check_every = S.p->check_every;
   a.restart_every = S.p->restart_every;
   a.steps_done = at<int64_t>(S.ws, S.L.steps);
+  a.ell_ord = at<uint16_t>(S.ws, S.L.eord);
+  a.ell_starts = at<int32_t>(S.ws, S.L.estart);
+  a.ell_blocks = at<uint4>(S.ws, S.L.eblock);
   return a;
 }
 
@@ -1368,6 +1377,12 @@ std::vector<TileCfg> tile_candidates(const Solve &S) {
             if (tile_feasible(S, c)) out.push_back(c);
           }
         }
+      // sliced adjacency: all T columns of a row in one lane; offered where no
+      // step-loop shape is asked for
+      if (!S.p->tile_vec && !S.p->tile_csr && !S.p->tile_reg && !S.p->tile_sb && T <= 4) {
+        const TileCfg c{T, th, T, 0, 0, 0, TILE_ELL};
+        if (tile_feasible(S, c)) out.push_back(c);
+      }
     }
   }
   return out;
@@ -1414,6 +1429,7 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       a.steps = tsteps;
       a.ls = 0;
       float ms = 0.f;
+      if (c.sb == TILE_ELL && launch_ell_build(a, S.s) != hipSuccess) continue;
       if (launch_tile_round(mc, w, a, c.threads, S.s) != hipSuccess) continue;  // warm-up
       HIP_TRY(hipEventRecord(e0, S.s));
       for (int rep = 0; rep < 2; ++rep) (void)launch_tile_round(mc, w, a, c.threads, S.s);
@@ -1456,6 +1472,10 @@ int solve_tile(Solve &S, int32_t *rounds_done, TileCfg *used) {
   launch_fill_i32(at<int32_t>(S.ws, S.L.err), 1, 0, S.s);
   TileArgs a = tile_args(S, cfg, x0);
   const bool mc = S.maxcut, w = S.g->weight != nullptr;
+  if (cfg.sb == TILE_ELL) {
+    const hipError_t e = launch_ell_build(a, S.s);
+    if (e != hipSuccess) return fail(MQO_ERR_HIP, "sliced adjacency: %s", hipGetErrorString(e));
+  }
   const int nwg = S.G * a.tiles;
   std::vector<int32_t> lsi;
   int32_t r = 0;
@@ -1914,7 +1934,7 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
   r->tile_vec_used = used.vec;
   r->tile_csr_lds_used = used.csr;
   r->tile_reg_degree_used = used.dreg;
-  r->tile_single_buffer_used = used.sb;
+  r->tile_single_buffer_used = used.sb == 1;
   r->ls_iterations = S.ls_iters;
   r->step_kernel_ms = S.timed_ms();
   r->step_kernel_launches = (int64_t)S.timed.size();

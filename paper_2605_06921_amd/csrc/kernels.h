@@ -148,7 +148,7 @@ struct TileArgs {
   int32_t csr_lds;  // stage the graph's columns in LDS (16-bit local ids)
   int32_t dreg;     // > 0: neighbour offsets held in registers, padded to dreg
   int32_t ipt;      // lane items per thread in the register-adjacency path
-  int32_t sb;       // 1: one iterate buffer, steps gather into registers first
+  int32_t sb;       // 1: one iterate buffer, steps gather into registers first; TILE_ELL: sliced adjacency
   int32_t steps, r0, r1, reset_mode, ls;
   int32_t check_every;  // > 0: early-exit test after every check_every steps of a round
   int32_t restart_every;  // > 0: round r with r % restart_every == 0 starts from x0 (a fresh start)
@@ -174,10 +174,19 @@ struct TileArgs {
   int32_t *ls_iters;  // [workgroups]
   int64_t *steps_done;  // [G*B] PGA steps executed, accumulated
   int32_t *err;
+  // sliced adjacency (TILE_ELL; written by launch_ell_build for this T):
+  // rows by descending degree [n_total], slice starts, blocks of 64 x 8 entries
+  uint16_t *ell_ord;
+  int32_t *ell_starts;
+  uint4 *ell_blocks;
 };
 
-bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, bool sb);
-size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, bool sb);
+constexpr int TILE_ELL = 2;  // TileArgs::sb of the sliced step loop
+bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, int sb);
+size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb);
+size_t ell_start_bytes(int64_t n_total, int64_t G);
+size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G);
+hipError_t launch_ell_build(const TileArgs &a, hipStream_t s);
 hipError_t launch_tile_round(bool maxcut, bool weighted, const TileArgs &a, int threads, hipStream_t s);
 // Prop. 4.1 toy: mode 0 = single-coordinate global reset, 1 = full restarts
 // (attempts = restarts); n <= 64; x_out [trials][n] or nullptr (mode 0).

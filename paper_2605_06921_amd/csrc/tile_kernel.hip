@@ -16,6 +16,11 @@
 // that twice the trajectories fit in LDS -- wider rows of the tile, whose
 // random gathers then meet fewer LDS bank conflicts.
 //
+// Few trajectories per graph (T = VEC columns, one lane per row): the general
+// loop then reads every lane's column ids from a row of its own, one cache
+// line per lane.  The sliced form (ELL) keeps the adjacency of 64 rows of
+// nearly equal degree interleaved instead: see k_ell_build.
+//
 // Arithmetic per element is identical to the grid kernels (same operation
 // order), so every plan gives bit-identical trajectories.
 #include <type_traits>
@@ -107,7 +112,125 @@ __host__ __device__ inline size_t tile_state_offset(int64_t n_max, int T, int64_
   return (b + 15) & ~(size_t)15;
 }
 
-template <bool MAXCUT, bool WEIGHTED, int VEC, bool CSR_LDS, int DREG, int IPT, bool SB>
+// ---------------------------------------------------------------------------
+// Sliced adjacency (unweighted graphs of at most ELL_MAX_ROWS rows).  The rows
+// of a graph are sorted by descending degree (ord) and cut into slices of 64;
+// slice s is as wide as its longest row, rounded up to 8 entries, and holds,
+// for each block of 8 entries, the 64 lanes' 8 entries side by side: one
+// 16-byte load per lane and 1 KB per wavefront, fully coalesced.  An entry is
+// the neighbour's byte offset in an iterate tile of T columns (4 T x local
+// row, 16 bits), in ascending CSR order; the padding is the tile's zero row,
+// and adding zeros at the end of a sum leaves every result bit-identical.
+// The sort keeps the padding below 64 x the largest degree plus 8 per row.
+//
+// What bounds it: the random 4 T-byte LDS gathers (bank conflicts; a random
+// 4- or 8-byte read of 64 lanes measured 7.5 clocks, a conflict-free one 2.8).
+// Measured, one trajectory per workgroup, 64 of them: n = 1000, degree 100,
+// 5.7 us per step (the general loop 14.5), the whole 91-round solve 264.9 ->
+// 112.3 ms; n = 3000, degree 100, 61 rounds with early exit, 247.9 (streaming
+// plan, every round as long as its slowest trajectory) -> 61.9 ms; n = 100,
+// degree 10, 1000 steps 860 -> 666 us.  The autotuner times it beside the
+// other shapes for T <= 4 (a lane owns whole rows; wider tiles share a row
+// between lanes, whose column loads then fall together anyway).
+//
+// Places in the workspace, without tables: graph g's slice starts are at
+// ell_slice_base (one per slice and the end), its blocks of 64 x 8 entries
+// at ell_block_base, both rounded so that neighbouring graphs never overlap.
+// ---------------------------------------------------------------------------
+constexpr int ELL_MAX_ROWS = 8192;
+
+__host__ __device__ inline int64_t ell_slice_base(int64_t lo, int64_t g) { return (lo >> 6) + 2 * g; }
+__host__ __device__ inline int64_t ell_block_base(int64_t lo, int64_t e0, int64_t g) {
+  return (e0 >> 9) + (lo >> 3) + (lo >> 6) + 6 * g;
+}
+size_t ell_start_bytes(int64_t n_total, int64_t G) { return (size_t)ell_slice_base(n_total, G) * sizeof(int32_t); }
+size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G) {
+  return (size_t)ell_block_base(n_total, nnz_total, G) * 1024;
+}
+
+// one workgroup per graph; off_shift = log2(4 T), zrow: the tile's zero row
+__global__ __launch_bounds__(1024) void k_ell_build(const int32_t *__restrict__ row_ptr,
+                                                    const int32_t *__restrict__ col_idx,
+                                                    const int64_t *__restrict__ vtx_off, int32_t off_shift,
+                                                    int32_t zrow, uint16_t *__restrict__ ord,
+                                                    int32_t *__restrict__ starts, uint16_t *__restrict__ blocks) {
+  __shared__ uint32_t bins[ELL_MAX_ROWS];  // rows per degree (a degree is below the row count), then places
+  __shared__ uint16_t so[ELL_MAX_ROWS];    // the order
+  __shared__ int32_t sst[ELL_MAX_ROWS / 64 + 1];
+  __shared__ uint32_t part[1024];
+  const int32_t g = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
+  const int64_t lo = vtx_off[g];
+  const int32_t n = (int32_t)(vtx_off[g + 1] - lo);
+  const int32_t *rp = row_ptr + lo;
+  const int32_t e0 = rp[0];
+  for (int32_t d = tid; d < ELL_MAX_ROWS; d += nthr) bins[d] = 0u;
+  __syncthreads();
+  // bin 0 holds the largest possible degree, n - 1
+  for (int32_t v = tid; v < n; v += nthr) atomicAdd(&bins[n - 1 - (rp[v + 1] - rp[v])], 1u);
+  __syncthreads();
+  constexpr int PER = ELL_MAX_ROWS / 1024;
+  uint32_t own = 0;
+  for (int i = 0; i < PER; ++i) own += bins[tid * PER + i];
+  part[tid] = own;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    const uint32_t t = tid >= off ? part[tid - off] : 0u;
+    __syncthreads();
+    part[tid] += t;
+    __syncthreads();
+  }
+  uint32_t run = part[tid] - own;
+  for (int i = 0; i < PER; ++i) {
+    const uint32_t h = bins[tid * PER + i];
+    bins[tid * PER + i] = run;
+    run += h;
+  }
+  __syncthreads();
+  for (int32_t v = tid; v < n; v += nthr) so[atomicAdd(&bins[n - 1 - (rp[v + 1] - rp[v])], 1u)] = (uint16_t)v;
+  __syncthreads();
+  for (int32_t i = tid; i < n; i += nthr) ord[lo + i] = so[i];
+  const int32_t ns = (n + 63) >> 6;
+  int32_t *st = starts + ell_slice_base(lo, g);
+  if (tid == 0) {
+    int32_t b = 0;
+    for (int32_t s = 0; s < ns; ++s) {
+      sst[s] = b;
+      const int32_t v = so[s * 64];  // the slice's longest row
+      b += (rp[v + 1] - rp[v] + 7) >> 3;
+    }
+    sst[ns] = b;
+  }
+  __syncthreads();
+  for (int32_t s = tid; s <= ns; s += nthr) st[s] = sst[s];
+  uint16_t *bl = blocks + ell_block_base(lo, e0, g) * 512;
+  const int32_t lane = tid & 63;
+  const uint32_t pad = (uint32_t)zrow << off_shift;
+  for (int32_t s = tid >> 6; s < ns; s += nthr >> 6) {
+    const int32_t i = s * 64 + lane;
+    const int32_t v = i < n ? so[i] : -1;
+    const int32_t beg = v >= 0 ? rp[v] : 0, deg = v >= 0 ? rp[v + 1] - beg : 0;
+    for (int32_t b = sst[s]; b < sst[s + 1]; ++b) {
+      uint32_t q[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int32_t j = (b - sst[s]) * 8 + k;
+        q[k] = j < deg ? (uint32_t)(col_idx[beg + j] - (int32_t)lo) << off_shift : pad;
+      }
+      reinterpret_cast<uint4 *>(bl)[(int64_t)b * 64 + lane] =
+          make_uint4(q[0] | q[1] << 16, q[2] | q[3] << 16, q[4] | q[5] << 16, q[6] | q[7] << 16);
+    }
+  }
+}
+
+hipError_t launch_ell_build(const TileArgs &a, hipStream_t s) {
+  int off_shift = 2 + a.log2T;
+  const int32_t zrow = a.n_max > 256 ? a.n_max : 256;
+  hipLaunchKernelGGL(k_ell_build, dim3((unsigned)a.G), dim3(1024), 0, s, a.row_ptr, a.col_idx, a.vtx_off, off_shift,
+                     zrow, a.ell_ord, a.ell_starts, reinterpret_cast<uint16_t *>(a.ell_blocks));
+  return hipGetLastError();
+}
+
+template <bool MAXCUT, bool WEIGHTED, int VEC, bool CSR_LDS, int DREG, int IPT, bool SB, bool ELL>
 // Four register rows per lane need more than the 128 VGPRs a 1024-thread
 // workgroup leaves, so that variant is built for at most 512 threads.
 __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a) {
@@ -162,12 +285,14 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   const int64_t sbase = (int64_t)wid * a.n_max * T;
   const int64_t nTmax = (int64_t)a.n_max * T;
   char *sl = reinterpret_cast<char *>(smem) + tile_state_offset(a.n_max, T, a.nnz_max, CSR_LDS, SB, ROWORD);
-  constexpr bool SLDS = DREG > 0;
-  int8_t *zs = SLDS ? reinterpret_cast<int8_t *>(sl + 8 * nTmax) : a.zs + sbase;
+  // (the sliced form keeps its momentum there too, after the flags' words)
+  constexpr bool SLDS = DREG > 0 || ELL;
+  constexpr int SZ = ELL ? 12 : 8;  // 4-byte words first: priorities, counts, (ELL) momentum
+  int8_t *zs = SLDS ? reinterpret_cast<int8_t *>(sl + SZ * nTmax) : a.zs + sbase;
   int32_t *nb = SLDS ? reinterpret_cast<int32_t *>(sl + 4 * nTmax) : a.nb + sbase;
   uint32_t *prio = SLDS ? reinterpret_cast<uint32_t *>(sl) : a.prio + sbase;  // also the reset keys
-  int8_t *fl = SLDS ? reinterpret_cast<int8_t *>(sl + 9 * nTmax) : a.fl + sbase;
-  float *vm = a.vm + sbase;
+  int8_t *fl = SLDS ? reinterpret_cast<int8_t *>(sl + (SZ + 1) * nTmax) : a.fl + sbase;
+  float *vm = ELL ? reinterpret_cast<float *>(sl + 8 * nTmax) : a.vm + sbase;
   const int32_t *ci = a.col_idx;
   const int32_t *wt = a.weight;
 
@@ -213,7 +338,10 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   }
   __syncthreads();
 
-  if constexpr (ROWORD) {
+  if constexpr (ELL) {
+    for (int32_t i = tid; i < n; i += nthr) rord[i] = a.ell_ord[lo + i];
+    __syncthreads();
+  } else if constexpr (ROWORD) {
     // rows by descending degree: a counting sort over 256 bins of the
     // degree shifted right until the largest fits (ties in any order: a
     // row's arithmetic does not depend on the lane that runs it); the tile
@@ -333,6 +461,31 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
           if (j >= end) break;
         }
       }
+    }
+  };
+
+  // ELL: slice s of the sliced adjacency, walked by one wavefront: one row
+  // per lane (its VEC = T columns), visit(xu) for each neighbour in
+  // ascending CSR order.  The next block of 8 entries is loaded while the
+  // current one's gathers run.
+  const int32_t ell_n = ELL ? (n + 63) >> 6 : 0;
+  const int32_t *ell_st = ELL ? a.ell_starts + ell_slice_base(lo, g) : nullptr;
+  const uint4 *ell_bl = ELL ? a.ell_blocks + ell_block_base(lo, e0, g) * 64 + (tid & 63) : nullptr;
+  auto slice_gather = [&](const float *src, int32_t s, auto &&visit) {
+    const int32_t b0 = __builtin_amdgcn_readfirstlane(ell_st[s]), b1 = __builtin_amdgcn_readfirstlane(ell_st[s + 1]);
+    if (b0 == b1) return;
+    const uint32_t ab = lds_byte_addr(src);
+    uint4 q = ell_bl[(int64_t)b0 * 64];
+    for (int32_t b = b0; b < b1; ++b) {
+      const uint4 nq = ell_bl[(int64_t)(b + 1 < b1 ? b + 1 : b) * 64];
+      const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
+      float xu[8][VEC];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        lds_load_addr<VEC>(ab + (kk & 1 ? qw[kk >> 1] >> 16 : qw[kk >> 1] & 0xffffu), xu[kk]);
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) visit(xu[kk]);
+      q = nq;
     }
   };
 
@@ -503,7 +656,43 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
           }
         }
       }
-      if constexpr (DREG == 0) {
+      if constexpr (ELL) {
+        for (int32_t st = done; st < done + len; ++st) {
+          const float *src = (st & 1) ? xb : xa;
+          float *dst = (st & 1) ? xa : xb;
+          for (int32_t sl = wave; sl < ell_n; sl += nwaves) {
+            const int32_t i = sl * 64 + (tid & 63);
+            float acc[VEC];
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) acc[c] = 0.0f;
+            slice_gather(src, sl, [&](const float (&xu)[VEC]) {
+#pragma unroll
+              for (int c = 0; c < VEC; ++c) acc[c] = acc[c] + xu[c];
+            });
+            if (i < n) {
+              const int32_t L0 = (int32_t)rord[i] << lt;
+              float x[VEC];
+              lds_load<VEC>(src + L0, x);
+#pragma unroll
+              for (int c = 0; c < VEC; ++c) {
+                const bool act = !chk || s_act[c];
+                const float gr = grad_from_sum<MAXCUT>(acc[c], a.param);
+                float d = gr;
+                if (momentum) {
+                  const float t = a.mu * vm[L0 + c];
+                  d = t + gr;
+                  if (act) vm[L0 + c] = d;
+                }
+                const float sv = a.alpha * d;
+                const float y = x[c] + sv;
+                if (act) x[c] = clip_box<MAXCUT>(y);  // else copied through
+              }
+              lds_store<VEC>(dst + L0, x);
+            }
+          }
+          __syncthreads();
+        }
+      } else if constexpr (DREG == 0) {
         // CHK (compile-time): stopped columns are copied through
         // the new iterate of lane item I (VEC trajectories of one row) from src
         auto item_step = [&](auto chk_tag, const float *src, int32_t I, float (&x)[VEC]) {
@@ -596,7 +785,29 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
             return z ? sum != 0 : sum == 0;  // checker of Eq. (8), gamma > 1
           }
         };
-        if constexpr (DREG == 0) {
+        if constexpr (ELL) {
+          for (int32_t sl = wave; sl < ell_n; sl += nwaves) {
+            const int32_t i = sl * 64 + (tid & 63);
+            int32_t cnt[VEC];
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) cnt[c] = 0;
+            // a MaxCut padding entry rounds to -1: taken off again by the row's degree
+            slice_gather(xc, sl, [&](const float (&xu)[VEC]) {
+#pragma unroll
+              for (int c = 0; c < VEC; ++c) cnt[c] += round_x<MAXCUT>(xu[c]);
+            });
+            if (i < n) {
+              const int32_t v = rord[i];
+              const int32_t pad =
+                  MAXCUT ? (ell_st[sl + 1] - ell_st[sl]) * 8 - (rps[v + 1] - rps[v]) : 0;
+              float x[VEC];
+              lds_load<VEC>(xc + (v << lt), x);
+#pragma unroll
+              for (int c = 0; c < VEC; ++c)
+                if (c < cols && s_act[c] && moves(round_x<MAXCUT>(x[c]), cnt[c] + pad)) s_viol[c] = 1;
+            }
+          }
+        } else if constexpr (DREG == 0) {
           // per lane item, the neighbours rounded as read from the tile in
           // LDS (the gather loop of the steps)
           for (int32_t I = tid; I < nT / VEC; I += nthr) {
@@ -650,7 +861,30 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
     const float *xf = (done & 1) ? xb : xa;
 
     // ------------------------------------------- rounding and neighbour counts
-    if constexpr (DREG == 0) {
+    if constexpr (ELL) {
+      for (int32_t sl = wave; sl < ell_n; sl += nwaves) {
+        const int32_t i = sl * 64 + (tid & 63);
+        int32_t cnt[VEC];
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) cnt[c] = 0;
+        slice_gather(xf, sl, [&](const float (&xu)[VEC]) {
+#pragma unroll
+          for (int c = 0; c < VEC; ++c) cnt[c] += round_x<MAXCUT>(xu[c]);
+        });
+        if (i < n) {
+          const int32_t v = rord[i];
+          const int32_t pad = MAXCUT ? (ell_st[sl + 1] - ell_st[sl]) * 8 - (rps[v + 1] - rps[v]) : 0;
+          float x[VEC];
+          lds_load<VEC>(xf + (v << lt), x);
+#pragma unroll
+          for (int c = 0; c < VEC; ++c) {
+            zs[(v << lt) + c] = (int8_t)round_x<MAXCUT>(x[c]);
+            nb[(v << lt) + c] = cnt[c] + pad;
+          }
+        }
+      }
+      __syncthreads();
+    } else if constexpr (DREG == 0) {
       // one pass over the lane items: the item's own entries rounded, its
       // neighbour counts taken from the rounded neighbours read straight
       // from the iterate tile in LDS (rounding a neighbour's entry again
@@ -872,11 +1106,14 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   if (tid < cols) a.steps_done[traj0 + tid] += s_cnt[tid];
 }
 
-bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, bool sb) {
+bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, int sb) {
   if (!(T >= 1 && T <= TILE_MAX_T && (T & (T - 1)) == 0 && (threads == 256 || threads == 512 || threads == 1024) &&
         n_max >= 1 && n_max * T < (1LL << 30) && (vec == 1 || vec == 2 || vec == 4) && vec <= T &&
         (!csr_lds || n_max <= 65536) && (dreg > 0 || n_max <= 65536)))  // uint16 local ids / row order
     return false;
+  // sliced adjacency: one lane per row, entries of 16 bits
+  if (sb == TILE_ELL)
+    return dreg == 0 && !csr_lds && vec == T && n_max <= ELL_MAX_ROWS && ((n_max > 256 ? n_max : 256) * 4 * T) < 65536;
   // single buffer: every lane item of a step held in registers at once
   if (sb) return dreg == 0 && n_max * T <= (int64_t)SB_ITEMS * vec * threads;
   if (dreg == 0) return true;
@@ -890,17 +1127,19 @@ bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int
          n_max * T <= (int64_t)ipt * threads;
 }
 
-size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, bool sb) {
-  size_t b = tile_state_offset(n_max, T, nnz_max, csr_lds, sb, !state_lds);
-  // prio, nb (4 bytes), z, flag (1 byte) per (row, trajectory)
-  if (state_lds) b += (size_t)n_max * T * 10;
+size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb) {
+  const bool ell = sb == TILE_ELL;
+  size_t b = tile_state_offset(n_max, T, nnz_max, csr_lds, sb == 1, !state_lds);
+  // prio, nb (4 bytes), z, flag (1 byte) per (row, trajectory); with the
+  // sliced adjacency the momentum (4 bytes) too
+  if (state_lds || ell) b += (size_t)n_max * T * (ell ? 14 : 10);
   return (b + 15) & ~(size_t)15;
 }
 
-template <bool MC, bool W, int VEC, bool CL, int DREG, int IPT, bool SB = false>
+template <bool MC, bool W, int VEC, bool CL, int DREG, int IPT, bool SB = false, bool ELL = false>
 static hipError_t tile_launch_t(const TileArgs &a, int threads, hipStream_t s) {
-  const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, SB);
-  auto kern = k_tile_round<MC, W, VEC, CL, DREG, IPT, SB>;
+  const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, ELL ? TILE_ELL : SB ? 1 : 0);
+  auto kern = k_tile_round<MC, W, VEC, CL, DREG, IPT, SB, ELL>;
   // the dynamic-LDS limit only ever grows; raise it when a launch needs more
   // (per device; callers hold the library's host lock)
   static int limit_set[64] = {0};
@@ -934,6 +1173,15 @@ static hipError_t tile_launch_mw(const TileArgs &a, int threads, hipStream_t s) 
       default: return tile_launch_reg<MC, 16>(a, threads, s);
     }
   }
+  if constexpr (!W) {
+    if (a.sb == TILE_ELL) {
+      switch (a.vec) {
+        case 4: return tile_launch_t<MC, W, 4, false, 0, 1, false, true>(a, threads, s);
+        case 2: return tile_launch_t<MC, W, 2, false, 0, 1, false, true>(a, threads, s);
+        default: return tile_launch_t<MC, W, 1, false, 0, 1, false, true>(a, threads, s);
+      }
+    }
+  }
   if (a.sb) {
     if (a.csr_lds) {
       switch (a.vec) {
@@ -963,9 +1211,9 @@ static hipError_t tile_launch_mw(const TileArgs &a, int threads, hipStream_t s) 
 }
 
 hipError_t launch_tile_round(bool maxcut, bool weighted, const TileArgs &a, int threads, hipStream_t s) {
-  if (!tile_shape_ok(a.n_max, a.T, threads, a.vec, a.csr_lds != 0, a.dreg, a.ipt, a.sb != 0))
+  if (!tile_shape_ok(a.n_max, a.T, threads, a.vec, a.csr_lds != 0, a.dreg, a.ipt, a.sb))
     return hipErrorInvalidValue;
-  if (weighted && a.dreg > 0) return hipErrorInvalidValue;
+  if (weighted && (a.dreg > 0 || a.sb == TILE_ELL)) return hipErrorInvalidValue;
   if (maxcut) return weighted ? tile_launch_mw<true, true>(a, threads, s) : tile_launch_mw<true, false>(a, threads, s);
   return tile_launch_mw<false, false>(a, threads, s);
 }
