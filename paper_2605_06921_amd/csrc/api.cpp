@@ -354,7 +354,7 @@ Layout make_layout(const mqo_graph *g, int32_t B, int32_t K = 0) {
   // persistent plan: the sliced adjacency (shapes that any tile can have)
   const bool ell = max_graph_rows(g) <= 8192 && !g->weight;
   L.eord = take(ell ? n * 2 : 0);
-  L.estart = take(ell ? ell_start_bytes(n, G) : 0);
+  L.estart = take(ell ? ell_slice_bytes(n, G) : 0);
   L.eblock = take(ell ? ell_block_bytes(n, g->nnz_total, G) : 0);
   L.total = o;
   return L;
@@ -1334,7 +1334,7 @@ TileArgs tile_args(Solve &S, const TileCfg &c, const float *x0) {
   a.restart_every = S.p->restart_every;
   a.steps_done = at<int64_t>(S.ws, S.L.steps);
   a.ell_ord = at<uint16_t>(S.ws, S.L.eord);
-  a.ell_starts = at<int32_t>(S.ws, S.L.estart);
+  a.ell_slices = at<int2>(S.ws, S.L.estart);
   a.ell_blocks = at<uint4>(S.ws, S.L.eblock);
   return a;
 }

@@ -175,16 +175,17 @@ struct TileArgs {
   int64_t *steps_done;  // [G*B] PGA steps executed, accumulated
   int32_t *err;
   // sliced adjacency (TILE_ELL; written by launch_ell_build for this T):
-  // rows by descending degree [n_total], slice starts, blocks of 64 x 8 entries
+  // rows by descending degree [n_total], per slice its first block and block
+  // count, blocks of 64 x 8 entries
   uint16_t *ell_ord;
-  int32_t *ell_starts;
+  int2 *ell_slices;
   uint4 *ell_blocks;
 };
 
 constexpr int TILE_ELL = 2;  // TileArgs::sb of the sliced step loop
 bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, int sb);
 size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb);
-size_t ell_start_bytes(int64_t n_total, int64_t G);
+size_t ell_slice_bytes(int64_t n_total, int64_t G);
 size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G);
 hipError_t launch_ell_build(const TileArgs &a, hipStream_t s);
 hipError_t launch_tile_round(bool maxcut, bool weighted, const TileArgs &a, int threads, hipStream_t s);

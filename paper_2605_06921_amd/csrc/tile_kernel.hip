@@ -95,74 +95,96 @@ __device__ __forceinline__ void lds_store(float *p, const float (&o)[VEC]) {
 // row order) the rows by descending degree as uint16, (CSR_LDS) the local
 // column ids, (register shapes) the discrete state.  Byte offsets of the
 // row order, the column ids and the state:
-__host__ __device__ inline size_t tile_rord_offset(int64_t n_max, int T, bool single_buf) {
-  const int64_t rowsX = (n_max > 256 ? n_max : 256) + 1;
+// Rows of an iterate buffer: the graph's (at least 256, the reset histogram),
+// then the zero rows: one, or for the sliced adjacency one per LDS bank from
+// a multiple of 32 on.
+constexpr int ELL_ZROWS = 32;
+__host__ __device__ inline int64_t tile_zero_row(int64_t n_max, bool ell) {
+  const int64_t m = n_max > 256 ? n_max : 256;
+  return ell ? (m + ELL_ZROWS - 1) & ~(int64_t)(ELL_ZROWS - 1) : m;
+}
+__host__ __device__ inline int64_t tile_rows(int64_t n_max, bool ell) {
+  return tile_zero_row(n_max, ell) + (ell ? ELL_ZROWS : 1);
+}
+__host__ __device__ inline size_t tile_rord_offset(int64_t n_max, int T, bool single_buf, bool ell) {
+  const int64_t rowsX = tile_rows(n_max, ell);
   const size_t b =
       (size_t)((single_buf ? 1 : 2) * rowsX) * T * sizeof(float) + (size_t)(n_max + 1) * sizeof(int32_t);
   return (b + 15) & ~(size_t)15;
 }
-__host__ __device__ inline size_t tile_cls_offset(int64_t n_max, int T, bool single_buf, bool row_order) {
-  const size_t b = tile_rord_offset(n_max, T, single_buf) + (row_order ? (size_t)(n_max + 1) * sizeof(uint16_t) : 0);
+__host__ __device__ inline size_t tile_cls_offset(int64_t n_max, int T, bool single_buf, bool row_order,
+                                                  bool ell) {
+  const size_t b = tile_rord_offset(n_max, T, single_buf, ell) + (row_order ? (size_t)(n_max + 1) * sizeof(uint16_t) : 0);
   return (b + 15) & ~(size_t)15;
 }
 __host__ __device__ inline size_t tile_state_offset(int64_t n_max, int T, int64_t nnz_max, bool csr_lds,
-                                                    bool single_buf, bool row_order) {
-  size_t b = tile_cls_offset(n_max, T, single_buf, row_order);
+                                                    bool single_buf, bool row_order, bool ell) {
+  size_t b = tile_cls_offset(n_max, T, single_buf, row_order, ell);
   if (csr_lds) b += (size_t)(nnz_max + 8) * sizeof(uint16_t);
   return (b + 15) & ~(size_t)15;
 }
 
 // ---------------------------------------------------------------------------
 // Sliced adjacency (unweighted graphs of at most ELL_MAX_ROWS rows).  The rows
-// of a graph are sorted by descending degree (ord) and cut into slices of 64;
-// slice s is as wide as its longest row, rounded up to 8 entries, and holds,
-// for each block of 8 entries, the 64 lanes' 8 entries side by side: one
-// 16-byte load per lane and 1 KB per wavefront, fully coalesced.  An entry is
-// the neighbour's byte offset in an iterate tile of T columns (4 T x local
-// row, 16 bits), in ascending CSR order; the padding is the tile's zero row,
-// and adding zeros at the end of a sum leaves every result bit-identical.
-// The sort keeps the padding below 64 x the largest degree plus 8 per row.
+// of a graph are sorted by descending degree (ord) and cut into slices of 64.
+// A slice is a list of issue slots, 64 entries each, one per lane; eight slots
+// form a block in which the 64 lanes' 8 entries lie side by side: one 16-byte
+// load per lane and 1 KB per wavefront, fully coalesced.  An entry is a byte
+// offset in an iterate tile of T columns (4 T x local row, 16 bits): the
+// lane's next neighbour in ascending CSR order, or a row of zeros; adding a
+// zero anywhere in a sum leaves every result bit-identical (a sum starts at
+// +0 and never becomes -0).
 //
-// What bounds it: the random 4 T-byte LDS gathers (bank conflicts; a random
-// 4- or 8-byte read of 64 lanes measured 7.5 clocks, a conflict-free one 2.8).
+// What bounds the step is the LDS: a 4- or 8-byte read runs as two passes of
+// 32 lanes over 32 banks (of 4 or 8 bytes), each as long as the rows that
+// meet on its fullest bank: 7.5 clocks for random rows, 2.8 conflict-free,
+// 4.4 with at most two on a bank (measured).  So for T <= 2 a slot takes at
+// most two different rows per bank and pass; the lanes with the fewest
+// entries left wait with a zero row of a bank that is free (about 1.08 times
+// the slots, 5 clocks per slot instead of 7.2).  A 16-byte read (T = 4) runs
+// as four passes of 16 lanes and is left as it comes.
+//
 // Measured, one trajectory per workgroup, 64 of them: n = 1000, degree 100,
-// 5.7 us per step (the general loop 14.5), the whole 91-round solve 264.9 ->
-// 112.3 ms; n = 3000, degree 100, 61 rounds with early exit, 247.9 (streaming
-// plan, every round as long as its slowest trajectory) -> 61.9 ms; n = 100,
-// degree 10, 1000 steps 860 -> 666 us.  The autotuner times it beside the
-// other shapes for T <= 4 (a lane owns whole rows; wider tiles share a row
-// between lanes, whose column loads then fall together anyway).
+// 4.46 us per step (5.7 without the slots' rule, the general loop 14.5); with
+// the entries of a wavefront's only slice kept in registers the whole
+// 91-round solve went from 264.9 to 90.3 ms (112.3 as they come, 93.5 with
+// the rule and the entries read again in every step); n = 3000, degree 100,
+// 61 rounds with early exit, 247.9 (streaming plan) -> 47.5 ms (61.9 without
+// the rule); n = 100, degree 10, 1000 steps 860 -> 593 us (711 with the
+// entries read in every step).  The autotuner times it beside the other
+// shapes for T <= 4 (a lane owns whole rows; wider tiles share a row between
+// lanes, whose column loads then fall together anyway).
 //
-// Places in the workspace, without tables: graph g's slice starts are at
-// ell_slice_base (one per slice and the end), its blocks of 64 x 8 entries
-// at ell_block_base, both rounded so that neighbouring graphs never overlap.
+// Places in the workspace, without tables: graph g's slices (first block and
+// block count) are at ell_slice_base, its blocks at ell_block_base, both
+// rounded so that neighbouring graphs never overlap.  A slice as wide as w
+// may take ell_slots(w) slots, and the widths of a sorted graph add up to at
+// most its degrees / 64 plus its largest; one whose rows meet on few banks
+// and would take more is stored as it comes, w slots.
 // ---------------------------------------------------------------------------
 constexpr int ELL_MAX_ROWS = 8192;
 
+__host__ __device__ inline int32_t ell_slots(int32_t w) { return (w + w / 4 + 8 + 7) & ~7; }  // <= 1.25 w + 15
 __host__ __device__ inline int64_t ell_slice_base(int64_t lo, int64_t g) { return (lo >> 6) + 2 * g; }
 __host__ __device__ inline int64_t ell_block_base(int64_t lo, int64_t e0, int64_t g) {
-  return (e0 >> 9) + (lo >> 3) + (lo >> 6) + 6 * g;
+  return (e0 >> 8) + (lo >> 2) + (lo >> 5) + 8 * g;
 }
-size_t ell_start_bytes(int64_t n_total, int64_t G) { return (size_t)ell_slice_base(n_total, G) * sizeof(int32_t); }
+size_t ell_slice_bytes(int64_t n_total, int64_t G) { return (size_t)ell_slice_base(n_total, G) * sizeof(int2); }
 size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G) {
   return (size_t)ell_block_base(n_total, nnz_total, G) * 1024;
 }
 
-// one workgroup per graph; off_shift = log2(4 T), zrow: the tile's zero row
-__global__ __launch_bounds__(1024) void k_ell_build(const int32_t *__restrict__ row_ptr,
-                                                    const int32_t *__restrict__ col_idx,
-                                                    const int64_t *__restrict__ vtx_off, int32_t off_shift,
-                                                    int32_t zrow, uint16_t *__restrict__ ord,
-                                                    int32_t *__restrict__ starts, uint16_t *__restrict__ blocks) {
+// the row order and the slices' first blocks; one workgroup per graph
+__global__ __launch_bounds__(1024) void k_ell_order(const int32_t *__restrict__ row_ptr,
+                                                    const int64_t *__restrict__ vtx_off, uint16_t *__restrict__ ord,
+                                                    int2 *__restrict__ slices) {
   __shared__ uint32_t bins[ELL_MAX_ROWS];  // rows per degree (a degree is below the row count), then places
   __shared__ uint16_t so[ELL_MAX_ROWS];    // the order
-  __shared__ int32_t sst[ELL_MAX_ROWS / 64 + 1];
   __shared__ uint32_t part[1024];
   const int32_t g = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const int64_t lo = vtx_off[g];
   const int32_t n = (int32_t)(vtx_off[g + 1] - lo);
   const int32_t *rp = row_ptr + lo;
-  const int32_t e0 = rp[0];
   for (int32_t d = tid; d < ELL_MAX_ROWS; d += nthr) bins[d] = 0u;
   __syncthreads();
   // bin 0 holds the largest possible degree, n - 1
@@ -189,44 +211,103 @@ __global__ __launch_bounds__(1024) void k_ell_build(const int32_t *__restrict__ 
   for (int32_t v = tid; v < n; v += nthr) so[atomicAdd(&bins[n - 1 - (rp[v + 1] - rp[v])], 1u)] = (uint16_t)v;
   __syncthreads();
   for (int32_t i = tid; i < n; i += nthr) ord[lo + i] = so[i];
-  const int32_t ns = (n + 63) >> 6;
-  int32_t *st = starts + ell_slice_base(lo, g);
   if (tid == 0) {
+    int2 *st = slices + ell_slice_base(lo, g);
     int32_t b = 0;
-    for (int32_t s = 0; s < ns; ++s) {
-      sst[s] = b;
+    for (int32_t s = 0; s * 64 < n; ++s) {
       const int32_t v = so[s * 64];  // the slice's longest row
-      b += (rp[v + 1] - rp[v] + 7) >> 3;
-    }
-    sst[ns] = b;
-  }
-  __syncthreads();
-  for (int32_t s = tid; s <= ns; s += nthr) st[s] = sst[s];
-  uint16_t *bl = blocks + ell_block_base(lo, e0, g) * 512;
-  const int32_t lane = tid & 63;
-  const uint32_t pad = (uint32_t)zrow << off_shift;
-  for (int32_t s = tid >> 6; s < ns; s += nthr >> 6) {
-    const int32_t i = s * 64 + lane;
-    const int32_t v = i < n ? so[i] : -1;
-    const int32_t beg = v >= 0 ? rp[v] : 0, deg = v >= 0 ? rp[v + 1] - beg : 0;
-    for (int32_t b = sst[s]; b < sst[s + 1]; ++b) {
-      uint32_t q[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int32_t j = (b - sst[s]) * 8 + k;
-        q[k] = j < deg ? (uint32_t)(col_idx[beg + j] - (int32_t)lo) << off_shift : pad;
-      }
-      reinterpret_cast<uint4 *>(bl)[(int64_t)b * 64 + lane] =
-          make_uint4(q[0] | q[1] << 16, q[2] | q[3] << 16, q[4] | q[5] << 16, q[6] | q[7] << 16);
+      st[s] = make_int2(b, 0);
+      b += ell_slots(rp[v + 1] - rp[v]) >> 3;
     }
   }
 }
 
+// the slots of a slice; one wavefront per (graph, slice)
+__global__ __launch_bounds__(256) void k_ell_slots(const int32_t *__restrict__ row_ptr,
+                                                   const int32_t *__restrict__ col_idx,
+                                                   const int64_t *__restrict__ vtx_off, int32_t log2T, int32_t zrow,
+                                                   const uint16_t *__restrict__ ord, int2 *__restrict__ slices,
+                                                   uint4 *__restrict__ blocks) {
+  // per wavefront, pass (32 lanes) and bank: the keys of the first and second row taken
+  __shared__ uint32_t s_first[4][64], s_second[4][64];
+  const int32_t g = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t lo = vtx_off[g];
+  const int32_t n = (int32_t)(vtx_off[g + 1] - lo);
+  const int32_t s = blockIdx.y * 4 + wave;
+  if (s * 64 >= n) return;  // the whole wavefront
+  const int32_t *rp = row_ptr + lo;
+  int2 *sl = slices + ell_slice_base(lo, g) + s;
+  const int32_t b0 = sl->x;
+  uint4 *bl = blocks + (ell_block_base(lo, rp[0], g) + b0) * 64 + lane;
+  const int32_t i = s * 64 + lane;
+  const int32_t v = i < n ? ord[lo + i] : -1;
+  const int32_t beg = v >= 0 ? rp[v] : 0, deg = v >= 0 ? rp[v + 1] - beg : 0;
+  const int32_t w = __builtin_amdgcn_readfirstlane(deg);  // lane 0 holds the longest row
+  const int32_t cap = ell_slots(w);
+  const int32_t sh = 2 + log2T;
+  auto column = [&](int32_t j) { return col_idx[beg + j] - (int32_t)lo; };
+  volatile uint32_t *first = s_first[wave], *second = s_second[wave];
+  bool fits = log2T <= 1;
+  int32_t slots = 0;
+  if (fits) {
+    int32_t p = 0;
+    int32_t u = p < deg ? column(p) : 0;
+    while (__ballot(p < deg)) {
+      if (slots == cap) {
+        fits = false;
+        break;
+      }
+      uint32_t q[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const bool act = p < deg;
+        const int32_t bank = (lane & 32) | (u & 31);
+        const uint32_t key = ((uint32_t)(deg - p) << 6) | (uint32_t)(63 - lane);  // most left first
+        first[lane] = 0u;
+        second[lane] = 0u;
+        __builtin_amdgcn_wave_barrier();
+        if (act) atomicMax(&s_first[wave][bank], key);
+        __builtin_amdgcn_wave_barrier();
+        bool win = act && first[bank] == key;
+        if (act && !win) atomicMax(&s_second[wave][bank], key);
+        __builtin_amdgcn_wave_barrier();
+        win = win || (act && second[bank] == key);
+        // a bank of this pass that no row, else at most one row, is read from
+        const uint32_t none = (uint32_t)(__ballot(first[lane] == 0u) >> (lane & 32));
+        const uint32_t one = (uint32_t)(__ballot(second[lane] == 0u) >> (lane & 32));
+        const int32_t z = none ? __builtin_ctz(none) : one ? __builtin_ctz(one) : lane & 31;
+        q[k] = (uint32_t)(win ? u : zrow + z) << sh;
+        if (win) {
+          ++p;
+          u = p < deg ? column(p) : 0;
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+      bl[(int64_t)(slots >> 3) * 64] =
+          make_uint4(q[0] | q[1] << 16, q[2] | q[3] << 16, q[4] | q[5] << 16, q[6] | q[7] << 16);
+      slots += 8;
+    }
+  }
+  if (!fits) {
+    for (slots = 0; slots < w; slots += 8) {
+      uint32_t q[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        q[k] = (uint32_t)(slots + k < deg ? column(slots + k) : zrow + (lane & 31)) << sh;
+      bl[(int64_t)(slots >> 3) * 64] =
+          make_uint4(q[0] | q[1] << 16, q[2] | q[3] << 16, q[4] | q[5] << 16, q[6] | q[7] << 16);
+    }
+  }
+  if (lane == 0) sl->y = slots >> 3;
+}
+
 hipError_t launch_ell_build(const TileArgs &a, hipStream_t s) {
-  int off_shift = 2 + a.log2T;
-  const int32_t zrow = a.n_max > 256 ? a.n_max : 256;
-  hipLaunchKernelGGL(k_ell_build, dim3((unsigned)a.G), dim3(1024), 0, s, a.row_ptr, a.col_idx, a.vtx_off, off_shift,
-                     zrow, a.ell_ord, a.ell_starts, reinterpret_cast<uint16_t *>(a.ell_blocks));
+  const int32_t zrow = (int32_t)tile_zero_row(a.n_max, true);
+  hipLaunchKernelGGL(k_ell_order, dim3((unsigned)a.G), dim3(1024), 0, s, a.row_ptr, a.vtx_off, a.ell_ord,
+                     a.ell_slices);
+  const unsigned gy = (unsigned)((a.n_max + 255) / 256);
+  hipLaunchKernelGGL(k_ell_slots, dim3((unsigned)a.G, gy), dim3(256), 0, s, a.row_ptr, a.col_idx, a.vtx_off, a.log2T,
+                     zrow, a.ell_ord, a.ell_slices, a.ell_blocks);
   return hipGetLastError();
 }
 
@@ -267,24 +348,24 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   // both iterate buffers have rowsX rows; the last row stays 0 (padding
   // target of the register adjacency), rows 0..255 of xa also hold the reset
   // histogram
-  const int32_t rowsX = max(a.n_max, 256) + 1;
-  const int32_t zrow = rowsX - 1;
+  const int32_t rowsX = (int32_t)tile_rows(a.n_max, ELL);
+  const int32_t zrow = (int32_t)tile_zero_row(a.n_max, ELL);
   float *xa = smem;                                                     // [rowsX][T]
   float *xb = SB ? smem : smem + (size_t)rowsX * T;                     // [rowsX][T] (SB: the same buffer)
   int32_t *rps = reinterpret_cast<int32_t *>(xb + (size_t)rowsX * T);  // [n_max+1] row_ptr of the graph
   // [n_max + 1] rows by descending degree (the general step loop's lane
   // items walk rows in this order)
   constexpr bool ROWORD = DREG == 0;
-  uint16_t *rord = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + tile_rord_offset(a.n_max, T, SB));
+  uint16_t *rord = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + tile_rord_offset(a.n_max, T, SB, ELL));
   // [nnz_max + 8] local columns (CSR_LDS), 16-byte aligned for 8-wide reads
   uint16_t *cls =
-      reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + tile_cls_offset(a.n_max, T, SB, ROWORD));
+      reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(smem) + tile_cls_offset(a.n_max, T, SB, ROWORD, ELL));
   // discrete state per (row, trajectory): in LDS after the CSR for the
   // register-adjacency shapes (small tiles), else in the workgroup's region
   // of the global scratch (L2-resident)
   const int64_t sbase = (int64_t)wid * a.n_max * T;
   const int64_t nTmax = (int64_t)a.n_max * T;
-  char *sl = reinterpret_cast<char *>(smem) + tile_state_offset(a.n_max, T, a.nnz_max, CSR_LDS, SB, ROWORD);
+  char *sl = reinterpret_cast<char *>(smem) + tile_state_offset(a.n_max, T, a.nnz_max, CSR_LDS, SB, ROWORD, ELL);
   // (the sliced form keeps its momentum there too, after the flags' words)
   constexpr bool SLDS = DREG > 0 || ELL;
   constexpr int SZ = ELL ? 12 : 8;  // 4-byte words first: priorities, counts, (ELL) momentum
@@ -308,7 +389,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   const int32_t k = (int32_t)floor(a.rho * (double)n);
   const int32_t ls_cap = 4 * (n + nnz_g) + 64;
   int32_t ls_total = 0;
-  for (int32_t c = tid; c < T; c += nthr) {
+  for (int32_t c = tid; c < (rowsX - zrow) * T; c += nthr) {
     xa[zrow * T + c] = 0.0f;
     xb[zrow * T + c] = 0.0f;
   }
@@ -465,28 +546,39 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   };
 
   // ELL: slice s of the sliced adjacency, walked by one wavefront: one row
-  // per lane (its VEC = T columns), visit(xu) for each neighbour in
-  // ascending CSR order.  The next block of 8 entries is loaded while the
-  // current one's gathers run.
+  // per lane (its VEC = T columns), visit(xu) for each entry: the neighbours
+  // in ascending CSR order with zeros between.  Two blocks of 8 entries are
+  // on the way while the current one's gathers run.
   const int32_t ell_n = ELL ? (n + 63) >> 6 : 0;
-  const int32_t *ell_st = ELL ? a.ell_starts + ell_slice_base(lo, g) : nullptr;
+  __shared__ int2 ell_sl[ELL ? ELL_MAX_ROWS / 64 : 1];
+  if constexpr (ELL) {
+    for (int32_t i = tid; i < ell_n; i += nthr) ell_sl[i] = a.ell_slices[ell_slice_base(lo, g) + i];
+    __syncthreads();
+  }
   const uint4 *ell_bl = ELL ? a.ell_blocks + ell_block_base(lo, e0, g) * 64 + (tid & 63) : nullptr;
-  auto slice_gather = [&](const float *src, int32_t s, auto &&visit) {
-    const int32_t b0 = __builtin_amdgcn_readfirstlane(ell_st[s]), b1 = __builtin_amdgcn_readfirstlane(ell_st[s + 1]);
-    if (b0 == b1) return;
-    const uint32_t ab = lds_byte_addr(src);
-    uint4 q = ell_bl[(int64_t)b0 * 64];
-    for (int32_t b = b0; b < b1; ++b) {
-      const uint4 nq = ell_bl[(int64_t)(b + 1 < b1 ? b + 1 : b) * 64];
-      const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
-      float xu[8][VEC];
+  auto block_gather = [&](uint32_t ab, const uint4 &q, auto &&visit) {
+    const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
+    float xu[8][VEC];
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk)
-        lds_load_addr<VEC>(ab + (kk & 1 ? qw[kk >> 1] >> 16 : qw[kk >> 1] & 0xffffu), xu[kk]);
+    for (int kk = 0; kk < 8; ++kk)
+      lds_load_addr<VEC>(ab + (kk & 1 ? qw[kk >> 1] >> 16 : qw[kk >> 1] & 0xffffu), xu[kk]);
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) visit(xu[kk]);
-      q = nq;
+    for (int kk = 0; kk < 8; ++kk) visit(xu[kk]);
+  };
+  // blocks b .. nb - 1 of a slice at bl
+  auto blocks_gather = [&](uint32_t ab, const uint4 *bl, int32_t b, int32_t nb, auto &&visit) {
+    if (b >= nb) return;
+    uint4 q = bl[b * 64], q1 = bl[(b + 1 < nb ? b + 1 : b) * 64];
+    for (; b < nb; ++b) {
+      const uint4 q2 = bl[(b + 2 < nb ? b + 2 : nb - 1) * 64];
+      block_gather(ab, q, visit);
+      q = q1;
+      q1 = q2;
     }
+  };
+  auto slice_gather = [&](const float *src, int32_t s, auto &&visit) {
+    blocks_gather(lds_byte_addr(src), ell_bl + (int64_t)__builtin_amdgcn_readfirstlane(ell_sl[s].x) * 64, 0,
+                  __builtin_amdgcn_readfirstlane(ell_sl[s].y), visit);
   };
 
   for (int32_t r = a.r0; r < a.r1; ++r) {
@@ -603,6 +695,21 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
       s_viol[tid] = 0;
     }
     __syncthreads();
+    // ELL, one slice per wavefront: the first ELL_REG blocks of its entries and
+    // its row (-1: none) are held in registers for the round's steps
+    constexpr int ELL_REG = !ELL ? 1 : VEC == 4 ? 7 : VEC == 2 ? 12 : 14;
+    uint4 ell_q[ELL_REG];
+    int32_t ell_nb = 0, ell_v = -1;
+    const uint4 *ell_blw = nullptr;
+    if constexpr (ELL) {
+      if (ell_n <= nwaves && wave < ell_n) {
+        ell_nb = __builtin_amdgcn_readfirstlane(ell_sl[wave].y);
+        ell_blw = ell_bl + (int64_t)__builtin_amdgcn_readfirstlane(ell_sl[wave].x) * 64;
+        if (tid < n) ell_v = rord[tid];
+#pragma unroll
+        for (int b = 0; b < ELL_REG; ++b) ell_q[b] = b < ell_nb ? ell_blw[b * 64] : make_uint4(0, 0, 0, 0);
+      }
+    }
     int32_t done = 0;
     while (done < a.steps) {
       const int32_t len = chk ? min(a.check_every, a.steps - done) : a.steps - done;
@@ -657,40 +764,75 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
         }
       }
       if constexpr (ELL) {
-        for (int32_t st = done; st < done + len; ++st) {
-          const float *src = (st & 1) ? xb : xa;
-          float *dst = (st & 1) ? xa : xb;
-          for (int32_t sl = wave; sl < ell_n; sl += nwaves) {
-            const int32_t i = sl * 64 + (tid & 63);
-            float acc[VEC];
+        // the step of the row at LDS element L0 with neighbour sums acc
+        auto row_step = [&](const float (&acc)[VEC], int32_t L0, float (&x)[VEC]) {
 #pragma unroll
-            for (int c = 0; c < VEC; ++c) acc[c] = 0.0f;
-            slice_gather(src, sl, [&](const float (&xu)[VEC]) {
-#pragma unroll
-              for (int c = 0; c < VEC; ++c) acc[c] = acc[c] + xu[c];
-            });
-            if (i < n) {
-              const int32_t L0 = (int32_t)rord[i] << lt;
-              float x[VEC];
-              lds_load<VEC>(src + L0, x);
-#pragma unroll
-              for (int c = 0; c < VEC; ++c) {
-                const bool act = !chk || s_act[c];
-                const float gr = grad_from_sum<MAXCUT>(acc[c], a.param);
-                float d = gr;
-                if (momentum) {
-                  const float t = a.mu * vm[L0 + c];
-                  d = t + gr;
-                  if (act) vm[L0 + c] = d;
-                }
-                const float sv = a.alpha * d;
-                const float y = x[c] + sv;
-                if (act) x[c] = clip_box<MAXCUT>(y);  // else copied through
-              }
-              lds_store<VEC>(dst + L0, x);
+          for (int c = 0; c < VEC; ++c) {
+            const bool act = !chk || s_act[c];
+            const float gr = grad_from_sum<MAXCUT>(acc[c], a.param);
+            float d = gr;
+            if (momentum) {
+              const float t = a.mu * vm[L0 + c];
+              d = t + gr;
+              if (act) vm[L0 + c] = d;
             }
+            const float sv = a.alpha * d;
+            const float y = x[c] + sv;
+            if (act) x[c] = clip_box<MAXCUT>(y);  // else copied through
           }
-          __syncthreads();
+        };
+        if (ell_n <= nwaves) {
+          // one slice per wavefront: its entries stay in registers
+          const bool have = ell_v >= 0;
+          const int32_t L0 = have ? ell_v << lt : 0;
+          float x[VEC];
+          lds_load<VEC>(((done & 1) ? xb : xa) + L0, x);
+          for (int32_t st = done; st < done + len; ++st) {
+            const float *src = (st & 1) ? xb : xa;
+            float *dst = (st & 1) ? xa : xb;
+            if (wave < ell_n) {
+              const uint32_t ab = lds_byte_addr(src);
+              float acc[VEC];
+#pragma unroll
+              for (int c = 0; c < VEC; ++c) acc[c] = 0.0f;
+              auto add = [&](const float (&xu)[VEC]) {
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) acc[c] = acc[c] + xu[c];
+              };
+#pragma unroll
+              for (int b = 0; b < ELL_REG; ++b)
+                if (b < ell_nb) block_gather(ab, ell_q[b], add);
+              blocks_gather(ab, ell_blw, ELL_REG, ell_nb, add);
+              if (have) {
+                row_step(acc, L0, x);
+                lds_store<VEC>(dst + L0, x);
+              }
+            }
+            __syncthreads();
+          }
+        } else {
+          for (int32_t st = done; st < done + len; ++st) {
+            const float *src = (st & 1) ? xb : xa;
+            float *dst = (st & 1) ? xa : xb;
+            for (int32_t sl = wave; sl < ell_n; sl += nwaves) {
+              const int32_t i = sl * 64 + (tid & 63);
+              float acc[VEC];
+#pragma unroll
+              for (int c = 0; c < VEC; ++c) acc[c] = 0.0f;
+              slice_gather(src, sl, [&](const float (&xu)[VEC]) {
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) acc[c] = acc[c] + xu[c];
+              });
+              if (i < n) {
+                const int32_t L0 = (int32_t)rord[i] << lt;
+                float x[VEC];
+                lds_load<VEC>(src + L0, x);
+                row_step(acc, L0, x);
+                lds_store<VEC>(dst + L0, x);
+              }
+            }
+            __syncthreads();
+          }
         }
       } else if constexpr (DREG == 0) {
         // CHK (compile-time): stopped columns are copied through
@@ -798,8 +940,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
             });
             if (i < n) {
               const int32_t v = rord[i];
-              const int32_t pad =
-                  MAXCUT ? (ell_st[sl + 1] - ell_st[sl]) * 8 - (rps[v + 1] - rps[v]) : 0;
+              const int32_t pad = MAXCUT ? ell_sl[sl].y * 8 - (rps[v + 1] - rps[v]) : 0;
               float x[VEC];
               lds_load<VEC>(xc + (v << lt), x);
 #pragma unroll
@@ -873,7 +1014,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
         });
         if (i < n) {
           const int32_t v = rord[i];
-          const int32_t pad = MAXCUT ? (ell_st[sl + 1] - ell_st[sl]) * 8 - (rps[v + 1] - rps[v]) : 0;
+          const int32_t pad = MAXCUT ? ell_sl[sl].y * 8 - (rps[v + 1] - rps[v]) : 0;
           float x[VEC];
           lds_load<VEC>(xf + (v << lt), x);
 #pragma unroll
@@ -1113,7 +1254,7 @@ bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int
     return false;
   // sliced adjacency: one lane per row, entries of 16 bits
   if (sb == TILE_ELL)
-    return dreg == 0 && !csr_lds && vec == T && n_max <= ELL_MAX_ROWS && ((n_max > 256 ? n_max : 256) * 4 * T) < 65536;
+    return dreg == 0 && !csr_lds && vec == T && n_max <= ELL_MAX_ROWS && tile_rows(n_max, true) * 4 * T <= 65536;
   // single buffer: every lane item of a step held in registers at once
   if (sb) return dreg == 0 && n_max * T <= (int64_t)SB_ITEMS * vec * threads;
   if (dreg == 0) return true;
@@ -1129,7 +1270,7 @@ bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int
 
 size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb) {
   const bool ell = sb == TILE_ELL;
-  size_t b = tile_state_offset(n_max, T, nnz_max, csr_lds, sb == 1, !state_lds);
+  size_t b = tile_state_offset(n_max, T, nnz_max, csr_lds, sb == 1, !state_lds, ell);
   // prio, nb (4 bytes), z, flag (1 byte) per (row, trajectory); with the
   // sliced adjacency the momentum (4 bytes) too
   if (state_lds || ell) b += (size_t)n_max * T * (ell ? 14 : 10);
