@@ -556,14 +556,18 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
     __syncthreads();
   }
   const uint4 *ell_bl = ELL ? a.ell_blocks + ell_block_base(lo, e0, g) * 64 + (tid & 63) : nullptr;
-  auto block_gather = [&](uint32_t ab, const uint4 &q, auto &&visit) {
-    const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
-    float xu[8][VEC];
+  auto blocks_at_once = [&](auto count, uint32_t ab, const uint4 *q, auto &&visit) {
+    constexpr int N = decltype(count)::value;
+    float xu[8 * N][VEC];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      lds_load_addr<VEC>(ab + (kk & 1 ? qw[kk >> 1] >> 16 : qw[kk >> 1] & 0xffffu), xu[kk]);
+    for (int t = 0; t < N; ++t) {
+      const uint32_t qw[4] = {q[t].x, q[t].y, q[t].z, q[t].w};
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) visit(xu[kk]);
+      for (int kk = 0; kk < 8; ++kk)
+        lds_load_addr<VEC>(ab + (kk & 1 ? qw[kk >> 1] >> 16 : qw[kk >> 1] & 0xffffu), xu[8 * t + kk]);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 8 * N; ++kk) visit(xu[kk]);
   };
   // blocks b .. nb - 1 of a slice at bl
   auto blocks_gather = [&](uint32_t ab, const uint4 *bl, int32_t b, int32_t nb, auto &&visit) {
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
     uint4 q = bl[b * 64], q1 = bl[(b + 1 < nb ? b + 1 : b) * 64];
     for (; b < nb; ++b) {
       const uint4 q2 = bl[(b + 2 < nb ? b + 2 : nb - 1) * 64];
-      block_gather(ab, q, visit);
+      blocks_at_once(std::integral_constant<int, 1>{}, ab, &q, visit);
       q = q1;
       q1 = q2;
     }
@@ -697,7 +701,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
     __syncthreads();
     // ELL, one slice per wavefront: the first ELL_REG blocks of its entries and
     // its row (-1: none) are held in registers for the round's steps
-    constexpr int ELL_REG = !ELL ? 1 : VEC == 4 ? 7 : VEC == 2 ? 12 : 14;
+    constexpr int ELL_REG = !ELL ? 1 : VEC == 4 ? 7 : 12;  // fits 128 VGPRs without spills
     uint4 ell_q[ELL_REG];
     int32_t ell_nb = 0, ell_v = -1;
     const uint4 *ell_blw = nullptr;
@@ -799,9 +803,21 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
 #pragma unroll
                 for (int c = 0; c < VEC; ++c) acc[c] = acc[c] + xu[c];
               };
+              // GRP blocks at a time, their reads issued together: one wait per
+              // group instead of one per block where few wavefronts run
+              // (n = 100, degree 10, 1000 steps: 740 -> 626 us)
+              constexpr int GRP = VEC == 1 ? 3 : 1;
 #pragma unroll
-              for (int b = 0; b < ELL_REG; ++b)
-                if (b < ell_nb) block_gather(ab, ell_q[b], add);
+              for (int b = 0; b < ELL_REG; b += GRP) {
+                if (b >= ell_nb) break;
+                if (GRP == 3 && b + 3 <= ell_nb) {
+                  blocks_at_once(std::integral_constant<int, GRP>{}, ab, &ell_q[b], add);
+                } else if (GRP == 3 && b + 2 <= ell_nb) {
+                  blocks_at_once(std::integral_constant<int, GRP == 3 ? 2 : 1>{}, ab, &ell_q[b], add);
+                } else {
+                  blocks_at_once(std::integral_constant<int, 1>{}, ab, &ell_q[b], add);
+                }
+              }
               blocks_gather(ab, ell_blw, ELL_REG, ell_nb, add);
               if (have) {
                 row_step(acc, L0, x);
