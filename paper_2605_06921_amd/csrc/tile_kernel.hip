@@ -465,11 +465,29 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   }
 
   // lane item I = VEC trajectories (from c0) of row v, the row at slot
-  // I * VEC >> lt of the row order; returns the offset of its entries
-  auto item_pos = [&](int32_t I, int32_t &v, int32_t &c0) {
+  // I * VEC >> lt of the row order; returns the offset of its entries, -1
+  // where the slot is past the rows.
+  // A 16-byte LDS read of a wavefront runs as four passes, lanes 0-3, 12-15,
+  // 20-23, 24-27 together, then 4-11, 16-19, 28-31, and so for lanes 32-63.
+  // Rows of 32 trajectories (128 bytes, one half of the banks) are laid on
+  // the lanes so that a pass reads two whole rows: it then takes two cycles
+  // when both are in the same half (1 in 2), where eight lanes in a row
+  // would bring pieces of four rows together (3 in 4).  Random rows: 6.4
+  // against 7.4 clocks a read (5.2 without conflicts).
+  const bool pass_rows = VEC == 4 && lt == 5;
+  const int32_t nI = pass_rows ? ((n + 3) & ~3) << 3 : nT / VEC;
+  auto item_pos = [&](int32_t I, int32_t &v, int32_t &c0) -> int32_t {
     const int32_t L0 = I * VEC;
-    v = ROWORD ? (int32_t)rord[L0 >> lt] : L0 >> lt;
+    int32_t slot = L0 >> lt;
     c0 = L0 & (T - 1);
+    if (pass_rows) {
+      // row and half of 4-lane group q: 0 2 2 0 3 1 1 3 and 0 0 1 1 0 0 1 1
+      const int32_t q = (I >> 2) & 7;
+      slot = (slot & ~3) | ((0xd728 >> (2 * q)) & 3);
+      c0 = ((q & 2) << 3) | ((I & 3) << 2);
+      if (slot >= n) return -1;
+    }
+    v = ROWORD ? (int32_t)rord[slot] : slot;
     return (v << lt) | c0;
   };
 
@@ -682,7 +700,6 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
     __syncthreads();
 
     // ------------------------------------------------------------ PGA steps
-    const int32_t nI = nT / VEC;  // lane items: VEC consecutive trajectories of one row
     if constexpr (DREG > 0) {
 #pragma unroll
       for (int i = 0; i < IPT; ++i) {
@@ -857,6 +874,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
           constexpr bool CHK = decltype(chk_tag)::value;
           int32_t v, c0;
           const int32_t L0 = item_pos(I, v, c0);
+          if (L0 < 0) return L0;
           float acc[VEC];
 #pragma unroll
           for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
@@ -887,6 +905,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
             const float y = x[i] + sv;
             if (!CHK || s_act[c0 + i]) x[i] = clip_box<MAXCUT>(y);  // else copied through
           }
+          return L0;
         };
         // CHK (compile-time): stopped columns are copied through
         auto gen_step = [&](auto chk_tag, int32_t st) {
@@ -907,7 +926,10 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
             for (int kq = 0; kq < SB_ITEMS; ++kq) {
               const int32_t I = tid + kq * nthr;
               int32_t v, c0;
-              if (I < nI) lds_store<VEC>(xa + item_pos(I, v, c0), xn[kq]);
+              if (I < nI) {
+                const int32_t L0 = item_pos(I, v, c0);
+                if (L0 >= 0) lds_store<VEC>(xa + L0, xn[kq]);
+              }
             }
             __syncthreads();
           } else {
@@ -915,9 +937,8 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
             float *dst = (st & 1) ? xa : xb;
             for (int32_t I = tid; I < nI; I += nthr) {
               float x[VEC];
-              item_step(chk_tag, src, I, x);
-              int32_t v, c0;
-              lds_store<VEC>(dst + item_pos(I, v, c0), x);
+              const int32_t L0 = item_step(chk_tag, src, I, x);
+              if (L0 >= 0) lds_store<VEC>(dst + L0, x);
             }
             __syncthreads();
           }
@@ -967,9 +988,10 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
         } else if constexpr (DREG == 0) {
           // per lane item, the neighbours rounded as read from the tile in
           // LDS (the gather loop of the steps)
-          for (int32_t I = tid; I < nT / VEC; I += nthr) {
+          for (int32_t I = tid; I < nI; I += nthr) {
             int32_t v, c0;
             const int32_t L0 = item_pos(I, v, c0);
+            if (L0 < 0) continue;
             bool any = false;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) any |= c0 + i < cols && s_act[c0 + i];
@@ -1046,9 +1068,10 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
       // neighbour counts taken from the rounded neighbours read straight
       // from the iterate tile in LDS (rounding a neighbour's entry again
       // gives the same integer the state holds)
-      for (int32_t I = tid; I < nT / VEC; I += nthr) {
+      for (int32_t I = tid; I < nI; I += nthr) {
         int32_t v, c0;
         const int32_t L0 = item_pos(I, v, c0);
+        if (L0 < 0) continue;
         int32_t cnt[VEC];
 #pragma unroll
         for (int i = 0; i < VEC; ++i) cnt[i] = 0;
