@@ -61,7 +61,7 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 // per lane in the step loop, column indices staged in LDS
 struct TileCfg {
   int T, threads, vec, csr, dreg, ipt;
-  int sb;  // 1: one iterate buffer (steps gather into registers first), TILE_ELL: sliced adjacency
+  int sb;  // 1: one iterate buffer (steps gather into registers first), TILE_ELL, TILE_WIDE: see TileArgs::sb
 };
 
 struct Resources {
@@ -1249,8 +1249,9 @@ int64_t nnz_max_of(const Solve &S) {
 
 bool tile_feasible(const Solve &S, const TileCfg &c) {
   return tile_shape_ok(S.n_max, c.T, c.threads, c.vec, c.csr != 0, c.dreg, c.ipt, c.sb) &&
-         !(c.sb == TILE_ELL && S.g->weight) &&
-         (int64_t)tile_lds_bytes(S.n_max, c.T, nnz_max_of(S), c.csr != 0, c.dreg > 0, c.sb) <= tile_lds_budget();
+         !(c.sb >= TILE_ELL && S.g->weight) &&
+         (int64_t)tile_lds_bytes(S.n_max, c.T, nnz_max_of(S), c.csr != 0, c.dreg > 0, c.sb) <=
+             tile_lds_budget() - (c.sb >= TILE_ELL ? 2048 : 0);  // their static slice tables
 }
 
 // any shape at all fits (plan selection)
@@ -1383,6 +1384,10 @@ std::vector<TileCfg> tile_candidates(const Solve &S) {
         const TileCfg c{T, th, T, 0, 0, 0, TILE_ELL};
         if (tile_feasible(S, c)) out.push_back(c);
       }
+      if (!S.p->tile_vec && !S.p->tile_csr && !S.p->tile_reg && !S.p->tile_sb) {
+        const TileCfg c{T, th, 4, 0, 0, 0, TILE_WIDE};
+        if (tile_feasible(S, c)) out.push_back(c);
+      }
     }
   }
   return out;
@@ -1429,7 +1434,7 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       a.steps = tsteps;
       a.ls = 0;
       float ms = 0.f;
-      if (c.sb == TILE_ELL && launch_ell_build(a, S.s) != hipSuccess) continue;
+      if (c.sb >= TILE_ELL && launch_ell_build(a, S.s) != hipSuccess) continue;
       if (launch_tile_round(mc, w, a, c.threads, S.s) != hipSuccess) continue;  // warm-up
       HIP_TRY(hipEventRecord(e0, S.s));
       for (int rep = 0; rep < 2; ++rep) (void)launch_tile_round(mc, w, a, c.threads, S.s);
@@ -1472,7 +1477,7 @@ int solve_tile(Solve &S, int32_t *rounds_done, TileCfg *used) {
   launch_fill_i32(at<int32_t>(S.ws, S.L.err), 1, 0, S.s);
   TileArgs a = tile_args(S, cfg, x0);
   const bool mc = S.maxcut, w = S.g->weight != nullptr;
-  if (cfg.sb == TILE_ELL) {
+  if (cfg.sb >= TILE_ELL) {
     const hipError_t e = launch_ell_build(a, S.s);
     if (e != hipSuccess) return fail(MQO_ERR_HIP, "sliced adjacency: %s", hipGetErrorString(e));
   }
@@ -1934,7 +1939,7 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
   r->tile_vec_used = used.vec;
   r->tile_csr_lds_used = used.csr;
   r->tile_reg_degree_used = used.dreg;
-  r->tile_single_buffer_used = used.sb == 1;
+  r->tile_single_buffer_used = used.sb == 1 || used.sb == TILE_WIDE;
   r->ls_iterations = S.ls_iters;
   r->step_kernel_ms = S.timed_ms();
   r->step_kernel_launches = (int64_t)S.timed.size();

@@ -148,7 +148,8 @@ struct TileArgs {
   int32_t csr_lds;  // stage the graph's columns in LDS (16-bit local ids)
   int32_t dreg;     // > 0: neighbour offsets held in registers, padded to dreg
   int32_t ipt;      // lane items per thread in the register-adjacency path
-  int32_t sb;       // 1: one iterate buffer, steps gather into registers first; TILE_ELL: sliced adjacency
+  int32_t sb;       // 1: one iterate buffer, steps gather into registers first; TILE_ELL: sliced adjacency;
+                    // TILE_WIDE: one iterate buffer, wide slices
   int32_t steps, r0, r1, reset_mode, ls;
   int32_t check_every;  // > 0: early-exit test after every check_every steps of a round
   int32_t restart_every;  // > 0: round r with r % restart_every == 0 starts from x0 (a fresh start)
@@ -182,11 +183,13 @@ struct TileArgs {
   uint4 *ell_blocks;
 };
 
-constexpr int TILE_ELL = 2;  // TileArgs::sb of the sliced step loop
+constexpr int TILE_ELL = 2;   // TileArgs::sb of the sliced step loop
+constexpr int TILE_WIDE = 3;  // one iterate buffer, slices of the rows of a wavefront
 bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, int sb);
 size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb);
 size_t ell_slice_bytes(int64_t n_total, int64_t G);
 size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G);
+// writes what the shapes TILE_ELL and TILE_WIDE read (row order, slices, entries)
 hipError_t launch_ell_build(const TileArgs &a, hipStream_t s);
 hipError_t launch_tile_round(bool maxcut, bool weighted, const TileArgs &a, int threads, hipStream_t s);
 // Prop. 4.1 toy: mode 0 = single-coordinate global reset, 1 = full restarts

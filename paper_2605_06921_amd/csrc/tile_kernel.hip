@@ -23,6 +23,8 @@
 //
 // Arithmetic per element is identical to the grid kernels (same operation
 // order), so every plan gives bit-identical trajectories.
+#include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "common.h"
@@ -167,9 +169,8 @@ constexpr int ELL_MAX_ROWS = 8192;
 __host__ __device__ inline int32_t ell_slots(int32_t w) { return (w + w / 4 + 8 + 7) & ~7; }  // <= 1.25 w + 15
 __host__ __device__ inline int64_t ell_slice_base(int64_t lo, int64_t g) { return (lo >> 6) + 2 * g; }
 __host__ __device__ inline int64_t ell_block_base(int64_t lo, int64_t e0, int64_t g) {
-  return (e0 >> 8) + (lo >> 2) + (lo >> 5) + 8 * g;
+  return (e0 >> 7) + (lo >> 2) + (lo >> 5) + 8 * g;
 }
-size_t ell_slice_bytes(int64_t n_total, int64_t G) { return (size_t)ell_slice_base(n_total, G) * sizeof(int2); }
 size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G) {
   return (size_t)ell_block_base(n_total, nnz_total, G) * 1024;
 }
@@ -301,7 +302,159 @@ __global__ __launch_bounds__(256) void k_ell_slots(const int32_t *__restrict__ r
   if (lane == 0) sl->y = slots >> 3;
 }
 
+// ---------------------------------------------------------------------------
+// Wide slices (the single-buffered step of T = 16, 32 or 64 trajectories,
+// unweighted graphs): the R = 256 / T rows that a wavefront walks together
+// (T / 4 lanes each) as one slice, blocks of 4 entries per row side by side:
+// 32-bit byte offsets in the tile, one 16-byte load per lane for 4 gathers,
+// a trip count that is the same for the whole wavefront, and one addition
+// per gather for its address.  Padding as above (entries up to the slice's
+// longest row, rounded up to 4).
+//
+// The gathers are bound by the LDS passes, two rows of 32 trajectories each:
+// a pass takes two cycles when both rows lie in the same half of the banks
+// (fewer instructions alone changed nothing: 5.2 VALU per 16-byte gather
+// here, 6 in the general loop).  So rows are paired: the longest row left
+// with the one of the next 64 whose neighbours most often lie in the other
+// half at the same position of the row (39% of the reads then meet in one
+// half instead of 50%; 128 or all rows to choose from would give 38%).
+// Measured on the batch of 128 ER graphs of 700-800 vertices, p = 0.15, 512
+// trajectories, 4 rounds: 224 -> 212 ms (222 without the pairing).
+// ---------------------------------------------------------------------------
+constexpr int WIDE_BITS = 8;         // 32-bit words of a row's parities that are compared
+constexpr int WIDE_MAX_ROWS = 2048;  // 8 items x 1024 threads x 4 trajectories / 16
+constexpr int WIDE_MAX_SLICES = 128;
+
+__host__ __device__ inline int32_t wide_rows(int32_t log2T) { return 256 >> log2T; }
+__host__ __device__ inline int64_t wide_slice_base(int64_t lo, int64_t g) { return (lo >> 2) + 2 * g; }  // R >= 4
+
+// pairs in `so` (rows by descending degree), by the first wavefront; bits:
+// [n][WIDE_BITS] parities of the row's first neighbours; out: the new order
+__device__ inline void wide_pair_rows(const uint16_t *so, const int32_t *rp, const uint32_t *bits, int32_t n,
+                                      uint16_t *out) {
+  const int lane = threadIdx.x & 63;
+  int32_t at = lane < n ? lane : INT_MAX;  // place in so of the row this lane offers
+  int32_t next = 64;
+  uint32_t b[WIDE_BITS];
+  int32_t deg = 0;
+  auto fetch = [&]() {
+    if (at == INT_MAX) return;
+    const int32_t v = so[at];
+    deg = rp[v + 1] - rp[v];
+#pragma unroll
+    for (int w = 0; w < WIDE_BITS; ++w) b[w] = bits[v * WIDE_BITS + w];
+  };
+#pragma unroll
+  for (int w = 0; w < WIDE_BITS; ++w) b[w] = 0u;
+  fetch();
+  for (int32_t done = 0; done < n; done += 2) {
+    // the longest row left: the smallest place
+    int32_t first = at;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) first = min(first, __shfl_xor(first, d, 64));
+    const int la = __builtin_ctzll(__ballot(at == first));
+    const int32_t da = __shfl(deg, la, 64);
+    int32_t meet = 0;
+#pragma unroll
+    for (int w = 0; w < WIDE_BITS; ++w) {
+      const int32_t len = min(deg, da) - 32 * w;
+      const uint32_t mask = len >= 32 ? ~0u : len > 0 ? (1u << len) - 1u : 0u;
+      meet += __popc(~(b[w] ^ (uint32_t)__shfl((int)b[w], la, 64)) & mask);
+    }
+    // a much shorter partner would leave its slots empty
+    int32_t cost = meet + (da - deg);
+    cost = lane == la || at == INT_MAX ? INT_MAX : (cost << 6) | lane;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) cost = min(cost, __shfl_xor(cost, d, 64));
+    const int lb = cost == INT_MAX ? -1 : cost & 63;
+    if (lane == la) out[done] = so[at];
+    if (lane == lb) out[done + 1] = so[at];
+    if (lane == la || lane == lb) {
+      const int32_t i = lane == la ? next : next + 1;
+      at = i < n ? i : INT_MAX;
+      fetch();
+    }
+    next += 2;
+  }
+}
+
+// row order (paired), slices (first block, blocks) and entries; one
+// workgroup per graph
+__global__ __launch_bounds__(1024) void k_wide_build(const int32_t *__restrict__ row_ptr,
+                                                     const int32_t *__restrict__ col_idx,
+                                                     const int64_t *__restrict__ vtx_off, int32_t log2T, int32_t zrow,
+                                                     uint16_t *__restrict__ ord, int2 *__restrict__ slices,
+                                                     uint4 *__restrict__ blocks) {
+  __shared__ uint32_t bits[1024 * WIDE_BITS];  // T = 32: at most 1024 rows
+  __shared__ uint16_t so[WIDE_MAX_ROWS], sp[WIDE_MAX_ROWS];
+  __shared__ int2 ss[WIDE_MAX_SLICES];
+  const int32_t g = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
+  const int64_t lo = vtx_off[g];
+  const int32_t n = (int32_t)(vtx_off[g + 1] - lo);
+  const int32_t *rp = row_ptr + lo;
+  const int32_t R = wide_rows(log2T), ns = (n + R - 1) / R;
+  for (int32_t i = tid; i < n; i += nthr) {
+    so[i] = ord[lo + i];
+    sp[i] = so[i];
+  }
+  for (int32_t i = tid; i < n * WIDE_BITS; i += nthr) bits[i] = 0u;
+  __syncthreads();
+  if (log2T == 5) {
+    for (int32_t i = tid; i < n * WIDE_BITS; i += nthr) {
+      const int32_t v = i / WIDE_BITS, w = i % WIDE_BITS;
+      const int32_t j0 = rp[v] + 32 * w, j1 = min(rp[v + 1], j0 + 32);
+      uint32_t x = 0;
+      for (int32_t j = j0; j < j1; ++j) x |= (uint32_t)((col_idx[j] - (int32_t)lo) & 1) << (j - j0);
+      bits[i] = x;
+    }
+    __syncthreads();
+    if (tid < 64) wide_pair_rows(so, rp, bits, n, sp);
+    __syncthreads();
+  }
+  for (int32_t i = tid; i < n; i += nthr) ord[lo + i] = sp[i];
+  for (int32_t s = tid; s < ns; s += nthr) {
+    int32_t w = 0;
+    for (int32_t i = s * R; i < min(n, (s + 1) * R); ++i) w = max(w, rp[sp[i] + 1] - rp[sp[i]]);
+    ss[s] = make_int2(0, (w + 3) >> 2);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    int32_t b = 0;
+    for (int32_t s = 0; s < ns; ++s) {
+      ss[s].x = b;
+      b += ss[s].y;
+    }
+  }
+  __syncthreads();
+  for (int32_t s = tid; s < ns; s += nthr) slices[wide_slice_base(lo, g) + s] = ss[s];
+  if (n == 0) return;
+  uint4 *bl = blocks + ell_block_base(lo, rp[0], g) * 64;
+  const int sh = log2T + 2;
+  for (int32_t s = 0; s < ns; ++s)
+    for (int32_t k = tid; k < ss[s].y * R; k += nthr) {
+      const int32_t r = k % R, b = k / R, i = s * R + r;
+      const int32_t v = i < n ? sp[i] : -1;
+      const int32_t beg = v >= 0 ? rp[v] : 0, deg = v >= 0 ? rp[v + 1] - beg : 0;
+      uint32_t q[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        q[t] = (uint32_t)(4 * b + t < deg ? col_idx[beg + 4 * b + t] - (int32_t)lo : zrow) << sh;
+      bl[(int64_t)(ss[s].x + b) * R + r] = make_uint4(q[0], q[1], q[2], q[3]);
+    }
+}
+
+size_t ell_slice_bytes(int64_t n_total, int64_t G) {
+  return (size_t)std::max(ell_slice_base(n_total, G), wide_slice_base(n_total, G)) * sizeof(int2);
+}
+
 hipError_t launch_ell_build(const TileArgs &a, hipStream_t s) {
+  if (a.sb == TILE_WIDE) {
+    hipLaunchKernelGGL(k_ell_order, dim3((unsigned)a.G), dim3(1024), 0, s, a.row_ptr, a.vtx_off, a.ell_ord,
+                       a.ell_slices);
+    hipLaunchKernelGGL(k_wide_build, dim3((unsigned)a.G), dim3(1024), 0, s, a.row_ptr, a.col_idx, a.vtx_off, a.log2T,
+                       (int32_t)tile_zero_row(a.n_max, false), a.ell_ord, a.ell_slices, a.ell_blocks);
+    return hipGetLastError();
+  }
   const int32_t zrow = (int32_t)tile_zero_row(a.n_max, true);
   hipLaunchKernelGGL(k_ell_order, dim3((unsigned)a.G), dim3(1024), 0, s, a.row_ptr, a.vtx_off, a.ell_ord,
                      a.ell_slices);
@@ -311,7 +464,7 @@ hipError_t launch_ell_build(const TileArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool MAXCUT, bool WEIGHTED, int VEC, bool CSR_LDS, int DREG, int IPT, bool SB, bool ELL>
+template <bool MAXCUT, bool WEIGHTED, int VEC, bool CSR_LDS, int DREG, int IPT, bool SB, bool ELL, bool WIDE>
 // Four register rows per lane need more than the 128 VGPRs a 1024-thread
 // workgroup leaves, so that variant is built for at most 512 threads.
 __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a) {
@@ -419,7 +572,7 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   }
   __syncthreads();
 
-  if constexpr (ELL) {
+  if constexpr (ELL || WIDE) {
     for (int32_t i = tid; i < n; i += nthr) rord[i] = a.ell_ord[lo + i];
     __syncthreads();
   } else if constexpr (ROWORD) {
@@ -475,7 +628,9 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
   // would bring pieces of four rows together (3 in 4).  Random rows: 6.4
   // against 7.4 clocks a read (5.2 without conflicts).
   const bool pass_rows = VEC == 4 && lt == 5;
-  const int32_t nI = pass_rows ? ((n + 3) & ~3) << 3 : nT / VEC;
+  // WIDE: whole slices, so that a wavefront's items all exist
+  const int32_t wide_R = 256 >> lt, wide_n = WIDE ? (n + wide_R - 1) / wide_R : 0;
+  const int32_t nI = WIDE ? wide_n * 64 : pass_rows ? ((n + 3) & ~3) << 3 : nT / VEC;
   auto item_pos = [&](int32_t I, int32_t &v, int32_t &c0) -> int32_t {
     const int32_t L0 = I * VEC;
     int32_t slot = L0 >> lt;
@@ -485,8 +640,8 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
       const int32_t q = (I >> 2) & 7;
       slot = (slot & ~3) | ((0xd728 >> (2 * q)) & 3);
       c0 = ((q & 2) << 3) | ((I & 3) << 2);
-      if (slot >= n) return -1;
     }
+    if ((pass_rows || WIDE) && slot >= n) return -1;
     v = ROWORD ? (int32_t)rord[slot] : slot;
     return (v << lt) | c0;
   };
@@ -560,6 +715,78 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
           if (j >= end) break;
         }
       }
+    }
+  };
+
+  // WIDE: the slices of R rows (see k_wide_build)
+  __shared__ int2 wide_sl[WIDE ? WIDE_MAX_SLICES : 1];
+  if constexpr (WIDE) {
+    for (int32_t i = tid; i < wide_n; i += nthr) wide_sl[i] = a.ell_slices[wide_slice_base(lo, g) + i];
+    __syncthreads();
+  }
+  // the neighbours' entries of lane item I (slice I / 64) in the tile at src,
+  // in ascending CSR order, then zero rows up to the slice's width
+  auto wide_gather = [&](const float *src, int32_t I, auto &&visit) {
+    const int32_t s = __builtin_amdgcn_readfirstlane(I >> 6);
+    const int32_t nb = __builtin_amdgcn_readfirstlane(wide_sl[s].y);
+    if (nb == 0) return;
+    int32_t r = (I & 63) >> (lt - 2);  // the row of the slice, its first column c0
+    int32_t c0 = (I * VEC) & (T - 1);
+    if (pass_rows) {
+      const int32_t q = (I >> 2) & 7;
+      r = (r & 4) | ((0xd728 >> (2 * q)) & 3);
+      c0 = ((q & 2) << 3) | ((I & 3) << 2);
+    }
+    const uint32_t ab = lds_byte_addr(src) + 4u * (uint32_t)c0;
+    // the address apart from the lane's part is the same for the wavefront
+    const uint4 *bl = a.ell_blocks + ell_block_base(lo, e0, g) * 64 +
+                      (int64_t)__builtin_amdgcn_readfirstlane(wide_sl[s].x) * wide_R;
+    const uint32_t lane_off = (uint32_t)r * 16u;
+    auto entry = [&](int32_t b) {
+      const char *at = reinterpret_cast<const char *>(bl + (uint32_t)(min(b, nb - 1) * wide_R));
+      return *reinterpret_cast<const uint4 *>(at + lane_off);
+    };
+    auto four = [&](const uint4 &q) {
+      float x0[VEC], x1[VEC], x2[VEC], x3[VEC];
+      lds_load_addr<VEC>(ab + q.x, x0);
+      lds_load_addr<VEC>(ab + q.y, x1);
+      lds_load_addr<VEC>(ab + q.z, x2);
+      lds_load_addr<VEC>(ab + q.w, x3);
+      visit(x0);
+      visit(x1);
+      visit(x2);
+      visit(x3);
+    };
+    // four blocks on their way; a block's registers are loaded again as soon
+    // as its reads are issued (past the end with the last block)
+    uint4 q0 = entry(0), q1 = entry(1), q2 = entry(2), q3 = entry(3);
+    int32_t b = 0;
+    for (; b + 4 <= nb; b += 4) {
+      four(q0);
+      q0 = entry(b + 4);
+      four(q1);
+      q1 = entry(b + 5);
+      four(q2);
+      q2 = entry(b + 6);
+      four(q3);
+      q3 = entry(b + 7);
+    }
+    if (b < nb) four(q0);
+    if (b + 1 < nb) four(q1);
+    if (b + 2 < nb) four(q2);
+  };
+
+  // the sums of its rounded neighbours (a MaxCut padding entry rounds to -1:
+  // taken off again by the row's degree)
+  [[maybe_unused]] auto wide_count = [&](const float *src, int32_t I, int32_t v, bool have, int32_t (&cnt)[VEC]) {
+    wide_gather(src, I, [&](const float (&xu)[VEC]) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) cnt[i] += round_x<MAXCUT>(xu[i]);
+    });
+    if (MAXCUT && have) {
+      const int32_t pad = wide_sl[I >> 6].y * 4 - (rps[v + 1] - rps[v]);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) cnt[i] += pad;
     }
   };
 
@@ -874,10 +1101,17 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
           constexpr bool CHK = decltype(chk_tag)::value;
           int32_t v, c0;
           const int32_t L0 = item_pos(I, v, c0);
-          if (L0 < 0) return L0;
+          if (!WIDE && L0 < 0) return L0;  // WIDE: the wavefront's lanes walk the slice together
           float acc[VEC];
 #pragma unroll
           for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
+          if constexpr (WIDE) {
+            wide_gather(src, I, [&](const float (&xu)[VEC]) {
+#pragma unroll
+              for (int i = 0; i < VEC; ++i) acc[i] = acc[i] + xu[i];
+            });
+            if (L0 < 0) return L0;
+          } else
           row_gather(src, v, c0, [&](int32_t j, const float (&xu)[VEC]) {
             if (WEIGHTED) {
               const float w = (float)wtg[j];
@@ -991,14 +1225,18 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
           for (int32_t I = tid; I < nI; I += nthr) {
             int32_t v, c0;
             const int32_t L0 = item_pos(I, v, c0);
-            if (L0 < 0) continue;
-            bool any = false;
+            if (!WIDE && L0 < 0) continue;
+            bool any = WIDE;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) any |= c0 + i < cols && s_act[c0 + i];
             if (!any) continue;
             int32_t cnt[VEC];
 #pragma unroll
             for (int i = 0; i < VEC; ++i) cnt[i] = 0;
+            if constexpr (WIDE) {
+              wide_count(xc, I, v, L0 >= 0, cnt);
+              if (L0 < 0) continue;
+            } else
             row_gather(xc, v, c0, [&](int32_t j, const float (&xu)[VEC]) {
 #pragma unroll
               for (int i = 0; i < VEC; ++i) {
@@ -1071,10 +1309,14 @@ __global__ __launch_bounds__(IPT >= 4 ? 512 : 1024) void k_tile_round(TileArgs a
       for (int32_t I = tid; I < nI; I += nthr) {
         int32_t v, c0;
         const int32_t L0 = item_pos(I, v, c0);
-        if (L0 < 0) continue;
+        if (!WIDE && L0 < 0) continue;
         int32_t cnt[VEC];
 #pragma unroll
         for (int i = 0; i < VEC; ++i) cnt[i] = 0;
+        if constexpr (WIDE) {
+          wide_count(xf, I, v, L0 >= 0, cnt);
+          if (L0 < 0) continue;
+        } else
         row_gather(xf, v, c0, [&](int32_t j, const float (&xu)[VEC]) {
 #pragma unroll
           for (int i = 0; i < VEC; ++i) {
@@ -1294,8 +1536,13 @@ bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int
   // sliced adjacency: one lane per row, entries of 16 bits
   if (sb == TILE_ELL)
     return dreg == 0 && !csr_lds && vec == T && n_max <= ELL_MAX_ROWS && tile_rows(n_max, true) * 4 * T <= 65536;
+  if (sb == TILE_WIDE && !(dreg == 0 && !csr_lds && vec == 4 && T >= 16)) return false;
   // single buffer: every lane item of a step held in registers at once
-  if (sb) return dreg == 0 && n_max * T <= (int64_t)SB_ITEMS * vec * threads;
+  // (the lanes' rows in whole wavefronts)
+  if (sb) {
+    const int64_t rows = sb == TILE_WIDE ? (n_max + 256 / T - 1) / (256 / T) * (256 / T) : n_max;
+    return dreg == 0 && rows * T <= (int64_t)SB_ITEMS * vec * threads;
+  }
   if (dreg == 0) return true;
   // register adjacency: one trajectory per lane item, at most ipt items per
   // lane; the shapes below fit the 128-VGPR budget of 1024-thread workgroups
@@ -1309,17 +1556,17 @@ bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int
 
 size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb) {
   const bool ell = sb == TILE_ELL;
-  size_t b = tile_state_offset(n_max, T, nnz_max, csr_lds, sb == 1, !state_lds, ell);
+  size_t b = tile_state_offset(n_max, T, nnz_max, csr_lds, sb == 1 || sb == TILE_WIDE, !state_lds, ell);
   // prio, nb (4 bytes), z, flag (1 byte) per (row, trajectory); with the
   // sliced adjacency the momentum (4 bytes) too
   if (state_lds || ell) b += (size_t)n_max * T * (ell ? 14 : 10);
   return (b + 15) & ~(size_t)15;
 }
 
-template <bool MC, bool W, int VEC, bool CL, int DREG, int IPT, bool SB = false, bool ELL = false>
+template <bool MC, bool W, int VEC, bool CL, int DREG, int IPT, bool SB = false, bool ELL = false, bool WIDE = false>
 static hipError_t tile_launch_t(const TileArgs &a, int threads, hipStream_t s) {
-  const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, ELL ? TILE_ELL : SB ? 1 : 0);
-  auto kern = k_tile_round<MC, W, VEC, CL, DREG, IPT, SB, ELL>;
+  const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, ELL ? TILE_ELL : WIDE ? TILE_WIDE : SB ? 1 : 0);
+  auto kern = k_tile_round<MC, W, VEC, CL, DREG, IPT, SB, ELL, WIDE>;
   // the dynamic-LDS limit only ever grows; raise it when a launch needs more
   // (per device; callers hold the library's host lock)
   static int limit_set[64] = {0};
@@ -1354,6 +1601,7 @@ static hipError_t tile_launch_mw(const TileArgs &a, int threads, hipStream_t s) 
     }
   }
   if constexpr (!W) {
+    if (a.sb == TILE_WIDE) return tile_launch_t<MC, W, 4, false, 0, 1, true, false, true>(a, threads, s);
     if (a.sb == TILE_ELL) {
       switch (a.vec) {
         case 4: return tile_launch_t<MC, W, 4, false, 0, 1, false, true>(a, threads, s);
@@ -1393,7 +1641,7 @@ static hipError_t tile_launch_mw(const TileArgs &a, int threads, hipStream_t s) 
 hipError_t launch_tile_round(bool maxcut, bool weighted, const TileArgs &a, int threads, hipStream_t s) {
   if (!tile_shape_ok(a.n_max, a.T, threads, a.vec, a.csr_lds != 0, a.dreg, a.ipt, a.sb))
     return hipErrorInvalidValue;
-  if (weighted && (a.dreg > 0 || a.sb == TILE_ELL)) return hipErrorInvalidValue;
+  if (weighted && (a.dreg > 0 || a.sb >= TILE_ELL)) return hipErrorInvalidValue;
   if (maxcut) return weighted ? tile_launch_mw<true, true>(a, threads, s) : tile_launch_mw<true, false>(a, threads, s);
   return tile_launch_mw<false, false>(a, threads, s);
 }

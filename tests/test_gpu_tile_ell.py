@@ -72,3 +72,25 @@ def test_sliced_adjacency_agrees(mqo, tmp_path, name, T, threads, momentum, chec
         assert np.array_equal(out[key].cpu().numpy(), o[key]), key
     nnz_g = np.diff(g.row_ptr[g.vtx_offset])
     assert out["edge_updates"] == int((o["traj_steps"].reshape(g.num_graphs, -1) * nnz_g[:, None]).sum())
+
+
+WIDE = 3
+
+
+@pytest.mark.parametrize("name", list(CASES))
+@pytest.mark.parametrize("T,threads", [(16, 1024), (32, 1024), (32, 512), (64, 1024)])
+@pytest.mark.parametrize("momentum,check", [(0.0, 0), (0.4, 7)])
+def test_wide_slices_agree(mqo, tmp_path, name, T, threads, momentum, check):
+    """The single-buffered step on slices of 16, 8 or 4 rows (rows paired by
+    their neighbours' LDS halves at T = 32), partial last slices, unused
+    columns of the tile."""
+    kind, g = CASES[name]
+    if max(np.diff(g.vtx_offset)) * T > 8 * 4 * threads:
+        pytest.skip("more items than a thread holds")
+    kw = dict(batch=37, steps_per_round=25, rounds=3, alpha=0.02, rho=0.1, seed=9, check_every=check)
+    out = solve_with_shape(mqo, tmp_path, (T, threads, 4, 0, 0, 0, WIDE), kind, mqo.DeviceGraph(g, DEV),
+                           momentum=momentum, **kw)
+    assert out["tile_cols"] == T and out["tile_sb"] == 1
+    o = solver.solve(kind, g, solver.Params(mu=momentum, **kw))
+    for key in ("traj_best_value", "traj_best_x", "best_value"):
+        assert np.array_equal(out[key].cpu().numpy(), o[key]), key
