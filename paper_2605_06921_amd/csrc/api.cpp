@@ -1393,15 +1393,20 @@ std::vector<TileCfg> tile_candidates(const Solve &S) {
   return out;
 }
 
-// Time one round of up to 32 steps per candidate; keep the fastest.  Every
+// Time one round of up to 64 steps per candidate; keep the fastest.  Every
 // candidate computes bit-identical results, so this only affects speed.
 // ms_per_step (or nullptr): the chosen shape's time per PGA step.
 int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nullptr) {
   TRY(tile_graph_order(S));
   Resources &R = res();
+  // the largest degree decides which register shape is offered (none above
+  // 16 or with weights) and nothing else: graphs that differ in it alone
+  // share a choice
+  const int md = S.max_deg;
+  const int deg_class = S.g->weight || md > 16 ? 17 : md <= 3 ? 3 : md <= 4 ? 4 : md <= 8 ? 8 : 16;
   char fixed[64];
   snprintf(fixed, sizeof(fixed), "|%d|%d|%d|%d|%d|%d|%d", S.p->tile_cols, S.p->tile_threads, S.p->tile_vec,
-           S.p->tile_csr, S.p->tile_reg, S.p->tile_sb, S.max_deg);
+           S.p->tile_csr, S.p->tile_reg, S.p->tile_sb, deg_class);
   const std::string key = "tile|" + R.gpu + "|" + tile_key(S) + fixed;
   std::string cached;
   if (tune_get(key, &cached)) {
@@ -1409,13 +1414,16 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
     double ms = 0.0;
     if (std::sscanf(cached.c_str(), "%d %d %d %d %d %d %d %lf", &c.T, &c.threads, &c.vec, &c.csr, &c.dreg, &c.ipt,
                     &c.sb, &ms) == 8 &&
-        tile_feasible(S, c)) {
+        tile_feasible(S, c) && (c.dreg == 0 || c.dreg >= md)) {
       *out = c;
       if (ms_per_step) *ms_per_step = ms;
       return MQO_OK;
     }
   }
-  const std::vector<TileCfg> cands = tile_candidates(S);
+  // widest tiles first: they are the ones that fill the card on large
+  // batches, and a fast one early lets the slow ones go after their probe
+  std::vector<TileCfg> cands = tile_candidates(S);
+  std::reverse(cands.begin(), cands.end());
   if (cands.empty()) return fail(MQO_ERR_UNSUPPORTED, "no persistent tile shape fits these graphs");
   TileCfg best_c = cands[0];
   double best_t = 1e30;
@@ -1435,7 +1443,18 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       a.ls = 0;
       float ms = 0.f;
       if (c.sb >= TILE_ELL && launch_ell_build(a, S.s) != hipSuccess) continue;
-      if (launch_tile_round(mc, w, a, c.threads, S.s) != hipSuccess) continue;  // warm-up
+      // warm-up, and a probe of a few steps: a shape that takes over three
+      // times the best one's time (and a millisecond for its first launch)
+      // is not timed further.  On 128 graphs x 512 trajectories, where the
+      // narrow tiles are up to 50 times slower, tuning took 19 s without it.
+      a.steps = std::min(tsteps, 8);
+      HIP_TRY(hipEventRecord(e0, S.s));
+      if (launch_tile_round(mc, w, a, c.threads, S.s) != hipSuccess) continue;
+      HIP_TRY(hipEventRecord(e1, S.s));
+      HIP_TRY(hipEventSynchronize(e1));
+      HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+      if (ms > 3.0f * (float)best_t * (float)a.steps + 1.0f) continue;
+      a.steps = tsteps;
       HIP_TRY(hipEventRecord(e0, S.s));
       for (int rep = 0; rep < 2; ++rep) (void)launch_tile_round(mc, w, a, c.threads, S.s);
       HIP_TRY(hipEventRecord(e1, S.s));
