@@ -313,6 +313,13 @@ int mqo_objective_grad_static(const mqo_graph *g, mqo_objective obj, float param
                               const float *X, int32_t B, const float *scale,
                               double *f_out, float *grad_out, void *stream);
 
+/* The backward of an objective whose unscaled gradient is at hand:
+ * out[v][c] = (float)scale[g * B + c] * grad[v][c], g the graph of row v; the
+ * same values as mqo_objective_grad with that scale (as float) gives, without
+ * another sparse product.  Asynchronous on `stream`. */
+int mqo_scale_grad(const mqo_graph *g, int32_t B, const double *scale,
+                   const float *grad, float *out, void *stream);
+
 /* K unrolled PGA steps x_{k+1} = Pi(x_k + alpha grad(x_k)) (momentum 0).
  * Forward stores x_{j*ckpt_every} in ckpt[j] ([K/ckpt_every][n_total*B])
  * and x_K in XK.  K must be a multiple of ckpt_every.  Backward takes

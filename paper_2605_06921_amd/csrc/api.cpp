@@ -1970,9 +1970,9 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
 }
 
 // per-graph helper for the asynchronous entry points
-int check_async(const mqo_graph *g, mqo_objective obj, int32_t B) {
+int check_async(const mqo_graph *g, mqo_objective obj, int32_t B, bool weight_free = true) {
   if (obj < MQO_OBJ_MIS_H || obj > MQO_OBJ_MAXCUT_FA) return fail(MQO_ERR_INVALID_ARG, "bad objective");
-  TRY(check_graph_args(g, obj == MQO_OBJ_MIS_H));
+  TRY(check_graph_args(g, weight_free && obj == MQO_OBJ_MIS_H));
   if (B < 1) return fail(MQO_ERR_INVALID_ARG, "B must be >= 1");
   return MQO_OK;
 }
@@ -2004,13 +2004,57 @@ size_t partial_count(const mqo_graph *g, int32_t B, int32_t copies = 1) {
 
 // objective and gradient of every graph after validation; part: the float64
 // partial rows (partial_count doubles), needed when f_out is requested
+// objective_workspace: that for the largest graph, and up to 4 MiB so that
+// graphs share launches; ws_bytes: what the caller gave.
+size_t objective_workspace_min(const mqo_graph *g, int32_t B) {
+  return align_up(partial_count(g, B) * sizeof(double));
+}
+
+// graph z of a table that starts at graph g0: appends it and returns true if
+// it leaves at most max_rows partial rows (0: no limit)
+bool table_add(GraphTable &t, const mqo_graph *g, int32_t gi, StepCfg cfg, int32_t B, int64_t max_rows) {
+  if (t.count == GRAPH_TABLE) return false;
+  const int32_t z = t.count;
+  const int64_t blk = spmm_row_blocks(view_of(g, gi), cfg), sl = reduce_slices(blk, B);
+  const int64_t blocks = (z ? t.blk[z] : 0) + blk, slices = (z ? t.sl[z] : 0) + sl;
+  if (blocks > INT32_MAX || (max_rows > 0 && blocks + slices > max_rows)) return false;
+  if (z == 0) {
+    t.lo[0] = (int32_t)g->vtx_offset[gi];
+    t.blk[0] = t.sl[0] = 0;
+  }
+  t.lo[z + 1] = (int32_t)g->vtx_offset[gi + 1];
+  t.blk[z + 1] = (int32_t)blocks;
+  t.sl[z + 1] = (int32_t)slices;
+  ++t.count;
+  return true;
+}
+
 int objective_grad_run(const mqo_graph *g, mqo_objective obj, float param, const float *X, int32_t B,
-                       const float *scale, double *f_out, float *grad_out, void *part_ws, void *stream) {
+                       const float *scale, double *f_out, float *grad_out, void *part_ws, size_t ws_bytes,
+                       void *stream) {
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   drop_stale_error();
-  const bool mc = obj != MQO_OBJ_MIS_H;
   const int form = (int)obj;
   const StepCfg cfg = default_step_cfg(B, B);
+  // several graphs without hub rows: as many per launch as the table and the
+  // partials' room take (rows and columns are 32-bit in the CSR)
+  if (g->num_graphs > 1 && max_graph_hubs(g) == 0 && g->n_total <= INT32_MAX) {
+    double *part = f_out ? reinterpret_cast<double *>(part_ws) : nullptr;
+    const int64_t max_rows = f_out ? (int64_t)(ws_bytes / sizeof(double)) / B : 0;
+    for (int32_t gi = 0; gi < g->num_graphs;) {
+      GraphTable t;
+      t.count = 0;
+      while (gi + t.count < g->num_graphs && table_add(t, g, gi + t.count, cfg, B, max_rows)) {
+      }
+      if (t.count == 0) return fail(MQO_ERR_INTERNAL, "a graph's partial sums do not fit the workspace");
+      launch_objective_grad_batch(form, view_of(g, gi), t, X, scale ? scale + (int64_t)gi * B : nullptr, grad_out,
+                                  part, B, B, cfg, param, s);
+      if (f_out) launch_reduce_partials_batch(part, t, B, f_out + (int64_t)gi * B, s);
+      gi += t.count;
+    }
+    HIP_TRY(hipGetLastError());
+    return MQO_OK;
+  }
   for (int32_t gi = 0; gi < g->num_graphs; ++gi) {
     const GraphView gv = view_of(g, gi);
     const float *sc = scale ? scale + (int64_t)gi * B : nullptr;
@@ -2080,7 +2124,14 @@ int mqo_solve_maxcut(const mqo_graph *g, const mqo_params *p, const float *x0, m
 
 size_t mqo_objective_workspace_size(const mqo_graph *g, int32_t B) {
   if (check_graph_args(g, false) != MQO_OK || B < 1) return 0;
-  return align_up(partial_count(g, B) * sizeof(double));
+  size_t rows = 0;
+  if (g->num_graphs > 1 && max_graph_hubs(g) == 0)
+    for (int32_t gi = 0; gi < g->num_graphs && rows * B * sizeof(double) < ((size_t)4 << 20); ++gi) {
+      const int64_t blk = spmm_row_blocks(view_of(g, gi), default_step_cfg(B, B));
+      rows += (size_t)(blk + reduce_slices(blk, B));
+    }
+  return std::max(objective_workspace_min(g, B),
+                  std::min(align_up(rows * B * sizeof(double)), (size_t)4 << 20));
 }
 
 int mqo_objective_grad(const mqo_graph *g, mqo_objective obj, float param, const float *X, int32_t B,
@@ -2088,9 +2139,9 @@ int mqo_objective_grad(const mqo_graph *g, mqo_objective obj, float param, const
   TRY(check_async(g, obj, B));
   TRY(check_param(obj, param));
   if (!X) return fail(MQO_ERR_INVALID_ARG, "X is NULL");
-  if (f_out && (!ws || ws_bytes < mqo_objective_workspace_size(g, B)))
+  if (f_out && (!ws || ws_bytes < objective_workspace_min(g, B)))
     return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", mqo_objective_workspace_size(g, B));
-  return objective_grad_run(g, obj, param, X, B, scale, f_out, grad_out, ws, stream);
+  return objective_grad_run(g, obj, param, X, B, scale, f_out, grad_out, ws, ws_bytes, stream);
 }
 
 int mqo_objective_grad_static(const mqo_graph *g, mqo_objective obj, float param, const float *X, int32_t B,
@@ -2106,7 +2157,27 @@ int mqo_objective_grad_static(const mqo_graph *g, mqo_objective obj, float param
                   (unsigned)MQO_STATIC_SCRATCH_BYTES);
     HIP_TRY(static_scratch_address(&ws));
   }
-  return objective_grad_run(g, obj, param, X, B, scale, f_out, grad_out, ws, stream);
+  return objective_grad_run(g, obj, param, X, B, scale, f_out, grad_out, ws, MQO_STATIC_SCRATCH_BYTES, stream);
+}
+
+int mqo_scale_grad(const mqo_graph *g, int32_t B, const double *scale, const float *grad, float *out, void *stream) {
+  TRY(check_async(g, MQO_OBJ_MIS_H, B, false));
+  if (!scale || !grad || !out) return fail(MQO_ERR_INVALID_ARG, "scale, grad and out are required");
+  if (g->n_total > INT32_MAX) return fail(MQO_ERR_INVALID_ARG, "more rows than a 32-bit index holds");
+  drop_stale_error();
+  for (int32_t gi = 0; gi < g->num_graphs;) {
+    GraphTable t;
+    t.count = 0;
+    while (gi + t.count < g->num_graphs && t.count < GRAPH_TABLE) {
+      if (t.count == 0) t.lo[0] = (int32_t)g->vtx_offset[gi];
+      t.lo[t.count + 1] = (int32_t)g->vtx_offset[gi + t.count + 1];
+      ++t.count;
+    }
+    launch_scale_rows(t, scale + (int64_t)gi * B, grad, out, B, reinterpret_cast<hipStream_t>(stream));
+    gi += t.count;
+  }
+  HIP_TRY(hipGetLastError());
+  return MQO_OK;
 }
 size_t mqo_unrolled_workspace_size(const mqo_graph *g, int32_t B, int32_t ckpt_every) {
   if (check_graph_args(g, false) != MQO_OK || B < 1 || ckpt_every < 1) return 0;

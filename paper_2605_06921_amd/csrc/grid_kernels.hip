@@ -1935,6 +1935,130 @@ __device__ __forceinline__ void objective_terms(float x, float acc, float W, flo
   }
 }
 
+// the table's graph of workgroup (or row) b: the last z with first[z] <= b
+__device__ __forceinline__ int32_t table_find(const int32_t *first, int32_t count, int64_t b) {
+  int32_t lo = 0, hi = count;
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (first[mid] <= b)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// The row workgroups of every graph of a table in one launch: the sums of
+// each row and each partial row are those of the graph's own launch.  What
+// bounds a batch of small graphs is the launches (two per graph): forward
+// and backward of 64 graphs of 100-200 vertices with 32 trajectories took
+// 909 us in 256 launches and 118 us in the three left, most of that torch's
+// autograd on the host.
+template <int VEC, int OBJ, bool WEIGHTED, int ROWS>
+__global__ __launch_bounds__(256) void k_objective_grad_batch(GraphView g, GraphTable t, const float *__restrict__ X,
+                                                              const float *__restrict__ scale,
+                                                              float *__restrict__ grad, double *__restrict__ part,
+                                                              int32_t ncols, int32_t ld, int32_t lanes_log2,
+                                                              float param) {
+  const Blk blk = xcd_blk(g.xcd_local);
+  const int32_t z = table_find(t.blk, t.count, blk.x);
+  g.lo = t.lo[z];
+  g.n = t.lo[z + 1] - t.lo[z];
+  int64_t v[ROWS];
+  bool own[ROWS];
+  int32_t col;
+  float acc[ROWS][VEC];
+  int32_t wsum[ROWS];
+  group_gather<VEC, WEIGHTED, ROWS>(g, X, blk.x - t.blk[z], blk.y, ncols, ld, lanes_log2, v, own, col, acc, wsum);
+  double fv[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) fv[i] = 0.0;
+  bool any = false;
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) {
+    if (!own[k] || col >= ncols) continue;
+    any = true;
+    float x[VEC], gr[VEC];
+    load_vec<VEC>(X + v[k] * ld + col, x);
+    const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? (float)wsum[k] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      double f;
+      objective_terms<OBJ>(x[i], acc[k][i], W, param, scale ? scale[z * ncols + col + i] : 1.0f, gr[i], f);
+      fv[i] += f;
+    }
+    if (grad) store_vec<VEC>(grad + v[k] * ld + col, gr);
+  }
+  if (part) block_column_partials<VEC>(fv, any, col, ncols, lanes_log2, part, blk.x);
+}
+
+// k_reduce_partials for every graph of a table (blockIdx.z).  slices 1: the
+// graphs of more than F partial rows, one slice of p = max(F, ceil(rows / F))
+// rows per blockIdx.y, into the rows t.sl[z] + y after the partials; slices
+// 0: every graph's final sum, from its slices or its at most F partial rows.
+__global__ __launch_bounds__(256) void k_reduce_partials_batch(double *__restrict__ part, GraphTable t, int32_t ncols,
+                                                               int32_t wlog2, int64_t F, int32_t slices,
+                                                               double *__restrict__ out) {
+  __shared__ double s[256];
+  const int32_t z = blockIdx.z;
+  const int32_t W = 1 << wlog2, R = 256 >> wlog2;
+  const int32_t c = blockIdx.x * W + (threadIdx.x & (W - 1));
+  const int32_t r = threadIdx.x >> wlog2;
+  const int64_t rows = t.blk[z + 1] - t.blk[z], nsl = t.sl[z + 1] - t.sl[z];
+  const int64_t first_slice = t.blk[t.count] + t.sl[z];
+  int64_t b0 = t.blk[z], b1 = t.blk[z + 1];
+  if (slices) {
+    if ((int64_t)blockIdx.y >= nsl) return;
+    const int64_t p = max(F, (rows + F - 1) / F);
+    b0 += blockIdx.y * p;
+    b1 = min(b1, b0 + p);
+  } else if (nsl > 0) {
+    b0 = first_slice;
+    b1 = b0 + nsl;
+  }
+  double a = 0.0;
+  if (c < ncols) {
+#pragma unroll 8
+    for (int64_t b = b0 + r; b < b1; b += R) a += part[b * ncols + c];
+  }
+  s[threadIdx.x] = a;
+  __syncthreads();
+  for (int32_t off = R >> 1; off > 0; off >>= 1) {
+    if (r < off) s[threadIdx.x] += s[threadIdx.x + (off << wlog2)];
+    __syncthreads();
+  }
+  if (r == 0 && c < ncols) {
+    if (slices)
+      part[(first_slice + blockIdx.y) * ncols + c] = s[threadIdx.x];
+    else
+      out[(int64_t)z * ncols + c] = s[threadIdx.x];
+  }
+}
+
+// The backward of an objective from its unscaled gradient, one pass instead
+// of another sparse product (preferential-attachment graph, n = 1e5, 64
+// trajectories: 39 us of gathers against 10 us; the call with its forward
+// 124 -> 92 us where the host keeps up).  Four columns at a time where ncols
+// is a multiple of 4 and both arrays are 16-byte aligned.
+template <int VEC>
+__global__ __launch_bounds__(256) void k_scale_rows(GraphTable t, const double *__restrict__ scale,
+                                                    const float *__restrict__ grad, float *__restrict__ out,
+                                                    int32_t ncols) {
+  const int32_t per_row = ncols / VEC;
+  const int64_t count = (int64_t)(t.lo[t.count] - t.lo[0]) * per_row;
+  const int64_t base = (int64_t)t.lo[0] * ncols;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t v = t.lo[0] + i / per_row;
+    const int32_t c = (int32_t)(i % per_row) * VEC;
+    const int32_t z = table_find(t.lo, t.count, v);
+    float g[VEC];
+    load_vec<VEC>(grad + base + i * VEC, g);
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) g[k] = (float)scale[(int64_t)z * ncols + c + k] * g[k];
+    store_vec<VEC>(out + base + i * VEC, g);
+  }
+}
+
 template <int VEC, int OBJ, bool WEIGHTED, int ROWS, int KB = 4>
 __global__ __launch_bounds__(256) void k_objective_grad(GraphView g, const float *__restrict__ X,
                                                         const float *__restrict__ scale, float *__restrict__ grad,
@@ -2665,6 +2789,75 @@ void launch_objective_grad(int form, const GraphView &g, const float *X, const f
     dispatch_form<ObjLaunch<2>>(form, w, g, X, scale, grad, part, ncols, ld, ll, param, s);
   else
     dispatch_form<ObjLaunch<1>>(form, w, g, X, scale, grad, part, ncols, ld, ll, param, s);
+}
+
+template <int VEC>
+struct ObjBatchLaunch {
+  template <int OBJ, bool W>
+  static void run(const GraphView &g, const GraphTable &t, const float *X, const float *scale, float *grad,
+                  double *part, int32_t ncols, int32_t ld, int ll, float param, hipStream_t s) {
+    const size_t lds = part ? PARTIAL_LDS(VEC) : 0;
+    dim3 grid = grid_rows(1, ncols, ll, VEC, 256);
+    grid.x = (unsigned)t.blk[t.count];
+    if (spmm_rows(g, ll) == 2)
+      MQO_LAUNCH((k_objective_grad_batch<VEC, OBJ, W, 2>), grid, dim3(256), lds, s, g, t, X, scale, grad, part, ncols,
+                 ld, ll, param);
+    else
+      MQO_LAUNCH((k_objective_grad_batch<VEC, OBJ, W, 1>), grid, dim3(256), lds, s, g, t, X, scale, grad, part, ncols,
+                 ld, ll, param);
+  }
+};
+
+void launch_objective_grad_batch(int form, const GraphView &g, const GraphTable &t, const float *X,
+                                 const float *scale, float *grad, double *part, int32_t ncols, int32_t ld,
+                                 StepCfg cfg, float param, hipStream_t s) {
+  const bool w = g.weight != nullptr;
+  const int ll = cfg.lanes_log2;
+  if (cfg.vec == 4)
+    dispatch_form<ObjBatchLaunch<4>>(form, w, g, t, X, scale, grad, part, ncols, ld, ll, param, s);
+  else if (cfg.vec == 2)
+    dispatch_form<ObjBatchLaunch<2>>(form, w, g, t, X, scale, grad, part, ncols, ld, ll, param, s);
+  else
+    dispatch_form<ObjBatchLaunch<1>>(form, w, g, t, X, scale, grad, part, ncols, ld, ll, param, s);
+}
+
+void launch_scale_rows(const GraphTable &t, const double *scale, const float *grad, float *out, int32_t ncols,
+                       hipStream_t s) {
+  const bool v4 = ncols % 4 == 0 && (((uintptr_t)grad | (uintptr_t)out) & 15) == 0;
+  const int64_t count = (int64_t)(t.lo[t.count] - t.lo[0]) * ncols / (v4 ? 4 : 1);
+  if (count == 0) return;
+  const unsigned blocks = blocks_for(count < (1 << 22) ? count : (1 << 22));
+  if (v4)
+    MQO_LAUNCH(k_scale_rows<4>, dim3(blocks), dim3(256), 0, s, t, scale, grad, out, ncols);
+  else
+    MQO_LAUNCH(k_scale_rows<1>, dim3(blocks), dim3(256), 0, s, t, scale, grad, out, ncols);
+}
+
+// log2 of the columns a reduction workgroup takes
+static inline int32_t reduce_wlog2(int32_t ncols) {
+  int32_t w = 0;
+  while ((1 << w) < ncols && w < 6) ++w;
+  return w;
+}
+
+int64_t reduce_slices(int64_t nblk, int32_t ncols) {
+  const int64_t F = 8 * (int64_t)(256 >> reduce_wlog2(ncols));
+  if (nblk <= F) return 0;
+  const int64_t p = std::max(F, (nblk + F - 1) / F);
+  return (nblk + p - 1) / p;
+}
+
+void launch_reduce_partials_batch(double *part, const GraphTable &t, int32_t ncols, double *out, hipStream_t s) {
+  const int32_t wlog2 = reduce_wlog2(ncols);
+  const unsigned cx = (unsigned)((ncols + (1 << wlog2) - 1) >> wlog2);
+  const int64_t F = 8 * (int64_t)(256 >> wlog2);
+  int32_t most = 0;
+  for (int32_t z = 0; z < t.count; ++z) most = std::max(most, t.sl[z + 1] - t.sl[z]);
+  if (most > 0)
+    MQO_LAUNCH(k_reduce_partials_batch, dim3(cx, (unsigned)most, (unsigned)t.count), dim3(256), 0, s, part, t, ncols,
+               wlog2, F, 1, out);
+  MQO_LAUNCH(k_reduce_partials_batch, dim3(cx, 1, (unsigned)t.count), dim3(256), 0, s, part, t, ncols, wlog2, F, 0,
+             out);
 }
 
 void launch_reduce_partials(double *part, int64_t nblk, int32_t ncols, double *out, bool accumulate, hipStream_t s) {

@@ -117,6 +117,28 @@ void launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx, const 
                           int32_t G, int64_t n, int64_t nnz, int32_t *err, hipStream_t s);
 void launch_objective_grad(int form, const GraphView &g, const float *X, const float *scale, float *grad,
                            double *part, int32_t ncols, int32_t ld, StepCfg cfg, float param, hipStream_t s);
+// Consecutive graphs of a batch in one launch (passed by value, so that a
+// captured launch keeps it): graph z of the table has rows lo[z] .. lo[z + 1]
+// and row workgroups blk[z] .. blk[z + 1], whose partials are the rows of the
+// same numbers; sl[z]: its first row among the reduction's slices.
+constexpr int GRAPH_TABLE = 64;
+struct GraphTable {
+  int32_t count;
+  int32_t lo[GRAPH_TABLE + 1];
+  int32_t blk[GRAPH_TABLE + 1];
+  int32_t sl[GRAPH_TABLE + 1];
+};
+// g: any of the graphs, for the arrays and flags they share (no hub lists)
+void launch_objective_grad_batch(int form, const GraphView &g, const GraphTable &t, const float *X,
+                                 const float *scale, float *grad, double *part, int32_t ncols, int32_t ld,
+                                 StepCfg cfg, float param, hipStream_t s);
+// slices the reduction of nblk partial rows of ncols columns goes through (0: none)
+int64_t reduce_slices(int64_t nblk, int32_t ncols);
+// out [t.count][ncols]; the slices follow the t.blk[t.count] partial rows
+void launch_reduce_partials_batch(double *part, const GraphTable &t, int32_t ncols, double *out, hipStream_t s);
+// out[v][c] = (float)scale[g ncols + c] * grad[v][c], g the row's graph (t.lo)
+void launch_scale_rows(const GraphTable &t, const double *scale, const float *grad, float *out, int32_t ncols,
+                       hipStream_t s);
 // partial rows [nblk][ncols] followed by room for reduce_rows(nblk) more
 // rows (the reduction's intermediate levels)
 inline int64_t reduce_rows(int64_t nblk) { return nblk / 7 + 64; }

@@ -85,6 +85,7 @@ def _load():
         "mqo_solve_maxcut": (i32, [G, P, vp, R, vp, sz, vp]),
         "mqo_objective_workspace_size": (sz, [G, i32]),
         "mqo_objective_grad": (i32, [G, i32, f32, vp, i32, vp, vp, vp, vp, sz, vp]),
+        "mqo_scale_grad": (i32, [G, i32, vp, vp, vp, vp]),
         "mqo_objective_grad_static": (i32, [G, i32, f32, vp, i32, vp, vp, vp, vp]),
         "mqo_unrolled_workspace_size": (sz, [G, i32, i32]),
         "mqo_pga_unrolled_forward": (i32, [G, i32, f32, f32, i32, i32, vp, vp, vp, i32, vp, sz, vp]),
@@ -514,25 +515,36 @@ def objective_grad_static(kind, dg: DeviceGraph, X: torch.Tensor, param: float, 
 
 
 class Objective(torch.autograd.Function):
-    """f(X) per trajectory (h of Eq. (3) or f_B of Eq. (7)); the backward is
-    the hand-written SpMM gradient kernel: dL/dX = dL/df_b * (c + H x)."""
+    """f(X) per trajectory (h of Eq. (3) or f_B of Eq. (7)); the gradient is
+    dL/dX = dL/df_b * (c + H x).  Where a gradient will be asked for, the
+    forward's sparse product writes c + H x too (the backward then only
+    scales it); otherwise the backward runs the product."""
 
     @staticmethod
-    def forward(ctx, X, dg, kind, param):
-        f, _ = objective_grad(kind, dg, X, param, want_grad=False)
-        ctx.save_for_backward(X)
+    def forward(ctx, X, dg, kind, param, want_grad=None):
+        if want_grad is None:
+            want_grad = ctx.needs_input_grad[0]
+        f, grad = objective_grad(kind, dg, X, param, want_grad=want_grad and X.is_contiguous())
+        # X is kept in both cases: a change to it before the backward is refused
+        ctx.save_for_backward(X, grad)
         ctx.dg, ctx.kind, ctx.param = dg, kind, param
         return f
 
     @staticmethod
     def backward(ctx, grad_f):
-        (X,) = ctx.saved_tensors
-        _, grad = objective_grad(ctx.kind, ctx.dg, X, ctx.param, scale=grad_f, want_f=False)
-        return grad, None, None, None
+        X, grad = ctx.saved_tensors
+        if grad is None:
+            _, out = objective_grad(ctx.kind, ctx.dg, X, ctx.param, scale=grad_f, want_f=False)
+        else:
+            dg, scale = ctx.dg, grad_f.to(torch.float64).contiguous()
+            out = torch.empty_like(grad)
+            _check(_lib.mqo_scale_grad(dg.struct, X.shape[1], _ptr(scale), _ptr(grad), _ptr(out),
+                                       _stream(dg.device)), "mqo_scale_grad")
+        return out, None, None, None, None
 
 
 def objective(X, dg, kind, param):
-    return Objective.apply(X, dg, kind, param)
+    return Objective.apply(X, dg, kind, param, torch.is_grad_enabled() and X.requires_grad)
 
 
 def unrolled_forward(kind, dg: DeviceGraph, X0: torch.Tensor, alpha: float, K: int, ckpt_every: int, param: float,
