@@ -7,6 +7,7 @@
 // traj0 + c.
 #include <algorithm>
 #include <climits>
+#include <initializer_list>
 
 #include "common.h"
 #include "kernels.h"
@@ -675,61 +676,132 @@ __global__ __launch_bounds__(256) void k_ls_prio(uint32_t *__restrict__ PRIO, in
   }
 }
 
+// VEC 32-bit words from p (16-byte aligned when VEC = 4)
+template <int VEC>
+__device__ __forceinline__ void load_w(const int32_t *p, int32_t (&o)[VEC]) {
+  if constexpr (VEC == 4) {
+    const int4 t = *reinterpret_cast<const int4 *>(p);
+    o[0] = t.x;
+    o[1] = t.y;
+    o[2] = t.z;
+    o[3] = t.w;
+  } else {
+    o[0] = *p;
+  }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_w(int32_t *p, const int32_t (&o)[VEC]) {
+  if constexpr (VEC == 4)
+    *reinterpret_cast<int4 *>(p) = make_int4(o[0], o[1], o[2], o[3]);
+  else
+    *p = o[0];
+}
+
+// VEC flags as bytes (4-byte aligned when VEC = 4)
+template <int VEC>
+__device__ __forceinline__ void store_flags(int8_t *p, const bool (&f)[VEC]) {
+  if constexpr (VEC == 4)
+    *reinterpret_cast<uint32_t *>(p) =
+        (f[0] ? 1u : 0u) | (f[1] ? 0x100u : 0u) | (f[2] ? 0x10000u : 0u) | (f[3] ? 0x1000000u : 0u);
+  else
+    *p = f[0] ? 1 : 0;
+}
+
+template <int VEC>
+__device__ __forceinline__ uint32_t load_flags(const int8_t *p) {
+  if constexpr (VEC == 4) return *reinterpret_cast<const uint32_t *>(p);
+  return (uint32_t)(uint8_t)*p;
+}
+
+// one store of the "still searching" flag per wavefront with a true lane
+__device__ __forceinline__ void raise_flag(bool any, int32_t *active) {
+  const unsigned long long bal = __ballot(any);
+  if (any && (int)(threadIdx.x & 63) == __builtin_ctzll(bal)) *active = 1;
+}
+
 // F[v] = v in P and its key beats every neighbour in P.  active[0] is set
 // when P is non-empty.  When prev_active is given and *prev_active == 0
 // the search has already stopped and the kernel does nothing.
-template <bool MAXCUT>
+// Once the search has settled an iteration is one pass over the states and
+// counts, so a lane takes VEC = 4 columns where rows allow 4- and 16-byte
+// access (1000 x 1000 torus, 32 trajectories: select 33 us and apply 25 us an
+// iteration, with one column per lane 63 and 41); the neighbours of its
+// candidates are read for the four columns together.
+template <bool MAXCUT, int VEC>
 __global__ __launch_bounds__(256) void k_ls_select(GraphView g, const int8_t *__restrict__ Z,
                                                    const int32_t *__restrict__ NB, const uint32_t *__restrict__ PRIO,
                                                    int8_t *__restrict__ F, int32_t *active,
                                                    const int32_t *prev_active, int32_t ncols, int32_t ld,
                                                    int32_t lanes_log2) {
   if (prev_active && *prev_active == 0) return;
-  const RowMap m = map_rows<1>(g.n, ncols, lanes_log2);
+  const RowMap m = map_rows<VEC>(g.n, ncols, lanes_log2);
   if (!m.active) return;
   const int64_t v = g.lo + m.row;
   const int64_t e = v * ld + m.col;
-  int32_t k1;
-  const bool p = ls_candidate_t<MAXCUT>(Z[e], NB[e], k1);
-  int8_t f = 0;
-  // one store of the "still searching" flag per wavefront
-  const unsigned long long bal = __ballot(p);
-  if (p && (int)(threadIdx.x & 63) == __builtin_ctzll(bal)) *active = 1;
-  if (p) {
-    const uint32_t pv = PRIO[e];
-    f = 1;
+  int32_t z[VEC], nb[VEC], k1[VEC];
+  load_z<VEC>(Z + e, z);
+  load_w<VEC>(NB + e, nb);
+  bool f[VEC], any = false;
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    f[i] = ls_candidate_t<MAXCUT>(z[i], nb[i], k1[i]);
+    any = any || f[i];
+  }
+  raise_flag(any, active);
+  if (any) {
+    int32_t pv[VEC];
+    load_w<VEC>(reinterpret_cast<const int32_t *>(PRIO) + e, pv);
     const int32_t beg = g.row_ptr[v], end = g.row_ptr[v + 1];
-    for (int32_t j = beg; j < end; ++j) {
+    for (int32_t j = beg; j < end && any; ++j) {
       const int64_t u = g.col_idx[j];
       const int64_t eu = u * ld + m.col;
-      int32_t k1u;
-      if (ls_candidate_t<MAXCUT>(Z[eu], NB[eu], k1u) && key_beats(k1u, PRIO[eu], u, k1, pv, v)) {
-        f = 0;
-        break;
+      int32_t zu[VEC], nbu[VEC];
+      load_z<VEC>(Z + eu, zu);
+      load_w<VEC>(NB + eu, nbu);
+      any = false;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        int32_t k1u;
+        if (f[i] && ls_candidate_t<MAXCUT>(zu[i], nbu[i], k1u) &&
+            key_beats(k1u, k1u == k1[i] ? PRIO[eu + i] : 0u, u, k1[i], (uint32_t)pv[i], v))
+          f[i] = false;
+        any = any || f[i];
       }
     }
   }
-  F[e] = f;
+  store_flags<VEC>(F + e, f);
 }
 
-template <bool MAXCUT, bool WEIGHTED>
+template <bool MAXCUT, bool WEIGHTED, int VEC>
 __global__ __launch_bounds__(256) void k_ls_apply(GraphView g, const int8_t *__restrict__ F, int8_t *__restrict__ Z,
                                                   int32_t *__restrict__ NB, const int32_t *active, int32_t ncols,
                                                   int32_t ld, int32_t lanes_log2) {
   if (*active == 0) return;
-  const RowMap m = map_rows<1>(g.n, ncols, lanes_log2);
+  const RowMap m = map_rows<VEC>(g.n, ncols, lanes_log2);
   if (!m.active) return;
   const int64_t v = g.lo + m.row;
   const int64_t e = v * ld + m.col;
-  if (!F[e]) return;
-  const int32_t z = Z[e];
-  const int32_t zn = MAXCUT ? -z : 1 - z;
-  Z[e] = (int8_t)zn;
-  const int32_t d = zn - z;
+  const uint32_t f = load_flags<VEC>(F + e);
+  if (!f) return;
+  int32_t d[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    d[i] = 0;
+    if ((f >> (8 * i)) & 1u) {
+      const int32_t z = Z[e + i];
+      const int32_t zn = MAXCUT ? -z : 1 - z;
+      Z[e + i] = (int8_t)zn;
+      d[i] = zn - z;
+    }
+  }
   const int32_t beg = g.row_ptr[v], end = g.row_ptr[v + 1];
   for (int32_t j = beg; j < end; ++j) {
     const int64_t u = g.col_idx[j];
-    atomicAdd(&NB[u * ld + m.col], WEIGHTED ? d * g.weight[j] : d);
+    const int32_t w = WEIGHTED ? g.weight[j] : 1;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+      if (d[i]) atomicAdd(&NB[u * ld + m.col + i], WEIGHTED ? d[i] * w : d[i]);
   }
 }
 
@@ -1192,133 +1264,150 @@ __device__ __forceinline__ bool pair_beats(int32_t ga, uint32_t ha, int32_t mina
 
 // Best improving cut edge at v: gain g_v + g_u + 2 w > 0 (g = s t the 1-flip
 // gains), largest pair key.  BG = gain, BH = hash, BP = CSR position or -1.
-template <bool WEIGHTED>
+// VEC = 4 columns per lane where rows allow 16-byte access (184 us on the
+// 1000 x 1000 torus with 32 trajectories, 317 with one column per lane).
+template <bool WEIGHTED, int VEC>
 __global__ __launch_bounds__(256) void k_flip2_best(GraphView g, const int8_t *__restrict__ Z,
                                                     const int32_t *__restrict__ NB, const uint32_t *__restrict__ PRIO,
                                                     int32_t *__restrict__ BG, uint32_t *__restrict__ BH,
                                                     int32_t *__restrict__ BP, int32_t ncols, int32_t ld,
                                                     int32_t lanes_log2) {
-  const RowMap m = map_rows<1>(g.n, ncols, lanes_log2);
+  const RowMap m = map_rows<VEC>(g.n, ncols, lanes_log2);
   if (!m.active) return;
   const int64_t v = g.lo + m.row;
   const int64_t e = v * ld + m.col;
-  const int32_t sv = Z[e];
-  const int32_t gv = sv * NB[e];
-  const uint32_t pv = PRIO[e];
-  int32_t bg = 0, bp = -1, bmin = 0, bmax = 0;
-  uint32_t bh = 0;
+  const int32_t *PR = reinterpret_cast<const int32_t *>(PRIO);
+  int32_t sv[VEC], gv[VEC], pv[VEC];
+  load_z<VEC>(Z + e, sv);
+  load_w<VEC>(NB + e, gv);
+  load_w<VEC>(PR + e, pv);
+  int32_t bg[VEC], bp[VEC], bmin[VEC], bmax[VEC], bh[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    gv[i] *= sv[i];
+    bg[i] = bmin[i] = bmax[i] = bh[i] = 0;
+    bp[i] = -1;
+  }
   const int32_t beg = g.row_ptr[v], end = g.row_ptr[v + 1];
-  // the neighbours four at a time: their states loaded together, then
-  // compared (the best pair key is a maximum, so the order of the
-  // comparisons does not change it)
-  for (int32_t j0 = beg; j0 < end; j0 += 4) {
-    int32_t uq[4], sq[4], nq[4], wq[4];
-    uint32_t pq[4];
+  // the neighbours TN at a time: their states loaded together, then compared
+  // (the best pair key is a maximum, so the order of the comparisons does not
+  // change it); past the row's end v itself, which is no cut edge
+  constexpr int TN = VEC == 4 ? 2 : 4;
+  for (int32_t j0 = beg; j0 < end; j0 += TN) {
+    int32_t uq[TN], wq[TN], sq[TN][VEC], nq[TN][VEC], pq[TN][VEC];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) uq[t] = j0 + t < end ? g.col_idx[j0 + t] : -1;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (uq[t] >= 0) {
-        const int64_t eu = (int64_t)uq[t] * ld + m.col;
-        sq[t] = Z[eu];
-        nq[t] = NB[eu];
-        pq[t] = PRIO[eu];
-        wq[t] = WEIGHTED ? g.weight[j0 + t] : 1;
-      } else {
-        sq[t] = sv;  // no neighbour: skipped below
-        nq[t] = 0;
-        pq[t] = 0u;
-        wq[t] = 0;
-      }
+    for (int t = 0; t < TN; ++t) {
+      uq[t] = j0 + t < end ? g.col_idx[j0 + t] : (int32_t)v;
+      wq[t] = WEIGHTED && j0 + t < end ? g.weight[j0 + t] : 1;
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int32_t u = uq[t], su = sq[t];
-      if (u < 0 || su == sv) continue;
-      const int32_t gain = gv + su * nq[t] + 2 * wq[t];
-      if (gain <= 0) continue;
-      const uint32_t h = pv + pq[t];
+    for (int t = 0; t < TN; ++t) {
+      const int64_t eu = (int64_t)uq[t] * ld + m.col;
+      load_z<VEC>(Z + eu, sq[t]);
+      load_w<VEC>(NB + eu, nq[t]);
+      load_w<VEC>(PR + eu, pq[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+      const int32_t u = uq[t];
       const int32_t mn = (int32_t)v < u ? (int32_t)v : u, mx = (int32_t)v < u ? u : (int32_t)v;
-      if (bp < 0 || pair_beats(gain, h, mn, mx, bg, bh, bmin, bmax)) {
-        bg = gain;
-        bh = h;
-        bp = j0 + t;
-        bmin = mn;
-        bmax = mx;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        const int32_t gain = gv[i] + sq[t][i] * nq[t][i] + 2 * wq[t];
+        const uint32_t h = (uint32_t)pv[i] + (uint32_t)pq[t][i];
+        const bool better = sq[t][i] != sv[i] && gain > 0 &&
+                            (bp[i] < 0 || pair_beats(gain, h, mn, mx, bg[i], (uint32_t)bh[i], bmin[i], bmax[i]));
+        bg[i] = better ? gain : bg[i];
+        bh[i] = better ? (int32_t)h : bh[i];
+        bp[i] = better ? j0 + t : bp[i];
+        bmin[i] = better ? mn : bmin[i];
+        bmax[i] = better ? mx : bmax[i];
       }
     }
   }
-  BG[e] = bg;
-  BH[e] = bh;
-  BP[e] = bp;
+  store_w<VEC>(BG + e, bg);
+  store_w<VEC>(reinterpret_cast<int32_t *>(BH) + e, bh);
+  store_w<VEC>(BP + e, bp);
 }
 
 // The lower end v of a mutual pair (v, u) applies it (F[v] = 1) when no
-// other vertex adjacent to v or u holds a larger best-pair key.
+// other vertex adjacent to v or u holds a larger best-pair key.  (VEC = 4 as
+// above: 109 us against 145, the application 76 against 94.)
+template <int VEC>
 __global__ __launch_bounds__(256) void k_flip2_select(GraphView g, const int32_t *__restrict__ BG,
                                                       const uint32_t *__restrict__ BH,
                                                       const int32_t *__restrict__ BP, int8_t *__restrict__ F,
                                                       int32_t *active, int32_t ncols, int32_t ld,
                                                       int32_t lanes_log2) {
-  const RowMap m = map_rows<1>(g.n, ncols, lanes_log2);
+  const RowMap m = map_rows<VEC>(g.n, ncols, lanes_log2);
   if (!m.active) return;
   const int64_t v = g.lo + m.row;
-  const int64_t e = v * ld + m.col;
-  const int32_t bp = BP[e];
-  bool f = false;
-  if (bp >= 0) {
-    const int32_t u = g.col_idx[bp];
-    const int64_t eu = (int64_t)u * ld + m.col;
+  const int64_t e0 = v * ld + m.col;
+  int32_t bp[VEC];
+  load_w<VEC>(BP + e0, bp);
+  bool f[VEC], any = false;
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    f[i] = false;
+    if (bp[i] < 0) continue;
+    const int32_t col = m.col + i;
+    const int32_t u = g.col_idx[bp[i]];
+    const int64_t eu = (int64_t)u * ld + col;
     const int32_t bpu = BP[eu];
     if ((int32_t)v < u && bpu >= 0 && g.col_idx[bpu] == (int32_t)v) {
-      const int32_t gk = BG[e];
-      const uint32_t hk = BH[e];
-      f = true;
-      for (int k = 0; k < 2 && f; ++k) {
+      const int32_t gk = BG[e0 + i];
+      const uint32_t hk = BH[e0 + i];
+      f[i] = true;
+      for (int k = 0; k < 2 && f[i]; ++k) {
         const int32_t x = k ? u : (int32_t)v;
         const int32_t beg = g.row_ptr[x], end = g.row_ptr[x + 1];
         for (int32_t j = beg; j < end; ++j) {
           const int32_t y = g.col_idx[j];
           if (y == (int32_t)v || y == u) continue;
-          const int64_t ey = (int64_t)y * ld + m.col;
+          const int64_t ey = (int64_t)y * ld + col;
           const int32_t bpy = BP[ey];
           if (bpy < 0) continue;
           const int32_t yp = g.col_idx[bpy];
           if (pair_beats(BG[ey], BH[ey], y < yp ? y : yp, y < yp ? yp : y, gk, hk, (int32_t)v, u)) {
-            f = false;
+            f[i] = false;
             break;
           }
         }
       }
     }
+    any = any || f[i];
   }
-  const unsigned long long bal = __ballot(f);
-  if (f && (int)(threadIdx.x & 63) == __builtin_ctzll(bal)) *active = 1;
-  F[e] = f ? 1 : 0;
+  raise_flag(any, active);
+  store_flags<VEC>(F + e0, f);
 }
 
-template <bool WEIGHTED>
+template <bool WEIGHTED, int VEC>
 __global__ __launch_bounds__(256) void k_flip2_apply(GraphView g, const int8_t *__restrict__ F,
                                                      const int32_t *__restrict__ BP, int8_t *__restrict__ Z,
                                                      int32_t *__restrict__ NB, const int32_t *active, int32_t ncols,
                                                      int32_t ld, int32_t lanes_log2) {
   if (*active == 0) return;
-  const RowMap m = map_rows<1>(g.n, ncols, lanes_log2);
+  const RowMap m = map_rows<VEC>(g.n, ncols, lanes_log2);
   if (!m.active) return;
   const int64_t v = g.lo + m.row;
   const int64_t e = v * ld + m.col;
-  if (!F[e]) return;
-  const int32_t x2[2] = {(int32_t)v, g.col_idx[BP[e]]};
+  const uint32_t f = load_flags<VEC>(F + e);
+  if (!f) return;
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int32_t x = x2[k];
-    const int64_t ex = (int64_t)x * ld + m.col;
-    const int32_t sx = Z[ex];
-    Z[ex] = (int8_t)(-sx);
-    const int32_t d = -2 * sx;
-    const int32_t beg = g.row_ptr[x], end = g.row_ptr[x + 1];
-    for (int32_t j = beg; j < end; ++j)
-      atomicAdd(&NB[(int64_t)g.col_idx[j] * ld + m.col], WEIGHTED ? d * g.weight[j] : d);
+  for (int i = 0; i < VEC; ++i) {
+    if (!((f >> (8 * i)) & 1u)) continue;
+    const int32_t x2[2] = {(int32_t)v, g.col_idx[BP[e + i]]};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int32_t x = x2[k];
+      const int64_t ex = (int64_t)x * ld + m.col + i;
+      const int32_t sx = Z[ex];
+      Z[ex] = (int8_t)(-sx);
+      const int32_t d = -2 * sx;
+      const int32_t beg = g.row_ptr[x], end = g.row_ptr[x + 1];
+      for (int32_t j = beg; j < end; ++j)
+        atomicAdd(&NB[(int64_t)g.col_idx[j] * ld + m.col + i], WEIGHTED ? d * g.weight[j] : d);
+    }
   }
 }
 
@@ -2543,18 +2632,37 @@ void launch_swap_prio(uint32_t *PRIO, int64_t lo, int64_t n, int32_t ncols, int3
              (uint64_t)PURPOSE_SWAP);
 }
 
+// whether the per-column searches take four columns per lane: 4-byte access
+// to the states and flags, 16-byte access to the 32-bit arrays
+static inline bool four_columns(int32_t ncols, int32_t ld, std::initializer_list<const void *> bytes,
+                                std::initializer_list<const void *> words) {
+  if (ncols % 4 != 0 || ld % 4 != 0) return false;
+  for (const void *p : bytes)
+    if ((uintptr_t)p & 3) return false;
+  for (const void *p : words)
+    if ((uintptr_t)p & 15) return false;
+  return true;
+}
+
 void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, const int32_t *NB,
                             const uint32_t *PRIO, int32_t *T0, int32_t *T1, int32_t *T2, uint32_t *TB, int32_t ncols,
                             int32_t ld, double mean_degree, hipStream_t s) {
   const int ll = lanes_log2_for(ncols);
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   if (maxcut) {
-    if (g.weight)
-      MQO_LAUNCH(k_flip2_best<true>, grid, dim3(256), 0, s, g, Z, NB, PRIO, T0, reinterpret_cast<uint32_t *>(T1), T2,
-                 ncols, ld, ll);
-    else
-      MQO_LAUNCH(k_flip2_best<false>, grid, dim3(256), 0, s, g, Z, NB, PRIO, T0, reinterpret_cast<uint32_t *>(T1),
-                 T2, ncols, ld, ll);
+    uint32_t *bh = reinterpret_cast<uint32_t *>(T1);
+    if (four_columns(ncols, ld, {Z}, {NB, PRIO, T0, T1, T2})) {
+      const int ll4 = lanes_log2_for(ncols / 4);
+      const dim3 grid4 = grid_rows(g.n, ncols, ll4, 4, 256);
+      if (g.weight)
+        MQO_LAUNCH((k_flip2_best<true, 4>), grid4, dim3(256), 0, s, g, Z, NB, PRIO, T0, bh, T2, ncols, ld, ll4);
+      else
+        MQO_LAUNCH((k_flip2_best<false, 4>), grid4, dim3(256), 0, s, g, Z, NB, PRIO, T0, bh, T2, ncols, ld, ll4);
+    } else if (g.weight) {
+      MQO_LAUNCH((k_flip2_best<true, 1>), grid, dim3(256), 0, s, g, Z, NB, PRIO, T0, bh, T2, ncols, ld, ll);
+    } else {
+      MQO_LAUNCH((k_flip2_best<false, 1>), grid, dim3(256), 0, s, g, Z, NB, PRIO, T0, bh, T2, ncols, ld, ll);
+    }
   } else {
     // owners of the proposed insertions, -1 elsewhere
     MQO_LAUNCH(k_fill_rows_i32, grid, dim3(256), 0, s, T2, g.lo, g.n, -1, ncols, ld, ll);
@@ -2575,12 +2683,22 @@ void launch_pair_apply(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, 
   const int ll = lanes_log2_for(ncols);
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   if (maxcut) {
-    MQO_LAUNCH(k_flip2_select, grid, dim3(256), 0, s, g, T0, reinterpret_cast<const uint32_t *>(T1), T2, F, active,
-               ncols, ld, ll);
+    const uint32_t *bh = reinterpret_cast<const uint32_t *>(T1);
+    if (four_columns(ncols, ld, {F}, {T2})) {
+      const int ll4 = lanes_log2_for(ncols / 4);
+      const dim3 grid4 = grid_rows(g.n, ncols, ll4, 4, 256);
+      MQO_LAUNCH(k_flip2_select<4>, grid4, dim3(256), 0, s, g, T0, bh, T2, F, active, ncols, ld, ll4);
+      if (g.weight)
+        MQO_LAUNCH((k_flip2_apply<true, 4>), grid4, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll4);
+      else
+        MQO_LAUNCH((k_flip2_apply<false, 4>), grid4, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll4);
+      return;
+    }
+    MQO_LAUNCH(k_flip2_select<1>, grid, dim3(256), 0, s, g, T0, bh, T2, F, active, ncols, ld, ll);
     if (g.weight)
-      MQO_LAUNCH(k_flip2_apply<true>, grid, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll);
+      MQO_LAUNCH((k_flip2_apply<true, 1>), grid, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll);
     else
-      MQO_LAUNCH(k_flip2_apply<false>, grid, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll);
+      MQO_LAUNCH((k_flip2_apply<false, 1>), grid, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll);
   } else {
     if (mean_degree >= 24.0) {
       const dim3 wgrid = grid_rows(g.n, ncols, 6, 1, 256);  // one wavefront per (row, 64 columns)
@@ -2613,16 +2731,28 @@ void launch_ls_iteration(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB
     }
     return;
   }
-  if (maxcut) {
-    MQO_LAUNCH(k_ls_select<true>, grid, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld, ll);
-    if (w)
-      MQO_LAUNCH((k_ls_apply<true, true>), grid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, ll);
-    else
-      MQO_LAUNCH((k_ls_apply<true, false>), grid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, ll);
-  } else {
-    MQO_LAUNCH(k_ls_select<false>, grid, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld, ll);
-    MQO_LAUNCH((k_ls_apply<false, false>), grid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, ll);
+#define MQO_LS(MC, W, VEC, GRID, LL)                                                                                \
+  MQO_LAUNCH((k_ls_select<MC, VEC>), GRID, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld, LL); \
+  MQO_LAUNCH((k_ls_apply<MC, W, VEC>), GRID, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, LL);
+#define MQO_LS_FORM(VEC, GRID, LL)          \
+  if (maxcut) {                             \
+    if (w) {                                \
+      MQO_LS(true, true, VEC, GRID, LL)     \
+    } else {                                \
+      MQO_LS(true, false, VEC, GRID, LL)    \
+    }                                       \
+  } else {                                  \
+    MQO_LS(false, false, VEC, GRID, LL)     \
   }
+  if (four_columns(ncols, ld, {Z, F}, {NB, PRIO})) {
+    const int ll4 = lanes_log2_for(ncols / 4);
+    const dim3 grid4 = grid_rows(g.n, ncols, ll4, 4, 256);
+    MQO_LS_FORM(4, grid4, ll4)
+  } else {
+    MQO_LS_FORM(1, grid, ll)
+  }
+#undef MQO_LS_FORM
+#undef MQO_LS
 }
 
 void launch_accept(const int8_t *Z, int8_t *Zb, const int64_t *value, int64_t *best, int64_t lo, int64_t n,
