@@ -805,6 +805,27 @@ __global__ __launch_bounds__(256) void k_ls_apply(GraphView g, const int8_t *__r
   }
 }
 
+// The live columns of (row v, chunk of 64) as a mask (see LiveCols)
+__device__ __forceinline__ unsigned long long live_mask(const LiveCols &live, int64_t v, int32_t chunk,
+                                                        int32_t nchunk) {
+  return live.words ? live.words[(int64_t)live.rgraph[v] * nchunk + chunk] : ~0ull;
+}
+
+// The row searches: a wavefront takes per_wave chunks of 64 columns of one
+// row, those with live columns (row_grid).  Launched for one chunk each the 128-graph ER
+// batch (96 000 rows x 512 columns) is 767 000 wavefronts, 41 us of dispatch
+// for a kernel with nothing to do (an iteration of the search is ten of them);
+// with eight chunks a wavefront it is 6.
+#define MQO_ROW_CHUNKS(...)                                                                                      \
+  const int64_t row =                                                                                            \
+      __builtin_amdgcn_readfirstlane((int32_t)((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));    \
+  if (row >= g.n) return; /* the whole wavefront */                                                              \
+  const int32_t nchunk = (ncols + 63) >> 6, chunk1 = min(nchunk, ((int32_t)blockIdx.y + 1) * per_wave);           \
+  for (int32_t chunk = (int32_t)blockIdx.y * per_wave; chunk < chunk1; ++chunk) {                                \
+    const unsigned long long lm = live_mask(live, g.lo + row, chunk, nchunk);                                     \
+    if (lm) __VA_ARGS__;                                                                                         \
+  }
+
 // The same iteration with one wavefront per (row v, 64 columns), for graphs
 // of large mean degree.  When few of the 64 columns move (the usual case
 // once the search has settled) each candidate column's neighbours are tested
@@ -815,21 +836,18 @@ __global__ __launch_bounds__(256) void k_ls_apply(GraphView g, const int8_t *__r
 constexpr int LS_ROW_FEW = 16;
 
 template <bool MAXCUT>
-__global__ __launch_bounds__(256) void k_ls_select_rows(GraphView g, const int8_t *__restrict__ Z,
-                                                        const int32_t *__restrict__ NB,
-                                                        const uint32_t *__restrict__ PRIO, int8_t *__restrict__ F,
-                                                        int32_t *active, const int32_t *prev_active, int32_t ncols,
-                                                        int32_t ld) {
-  if (prev_active && *prev_active == 0) return;
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= g.n) return;  // the whole wavefront
+__device__ __forceinline__ void ls_select_rows_chunk(
+    int64_t row, int32_t chunk, int32_t nchunk, unsigned long long lm, GraphView g, const int8_t *__restrict__ Z,
+    const int32_t *__restrict__ NB, const uint32_t *__restrict__ PRIO, int8_t *__restrict__ F, int32_t *active, const
+    int32_t *prev_active, int32_t ncols, int32_t ld, LiveCols live) {
   const int32_t lane = threadIdx.x & 63;
-  const int32_t c0 = (int32_t)blockIdx.y * 64;
+  const int32_t c0 = (int32_t)chunk * 64;
   const int32_t cc = ncols - c0 < 64 ? ncols - c0 : 64;
   const int32_t v = __builtin_amdgcn_readfirstlane((int32_t)(g.lo + row));
   const int64_t e = (int64_t)v * ld + c0 + lane;
   int32_t k1 = 0;
-  const bool p = lane < cc && ls_candidate_t<MAXCUT>(Z[e], NB[e], k1);
+  const bool mine = lane < cc && ((lm >> lane) & 1ull);
+  const bool p = mine && ls_candidate_t<MAXCUT>(Z[e], NB[e], k1);
   const uint32_t pv = p ? PRIO[e] : 0u;
   unsigned long long cand = __ballot(p);
   if (p && lane == __builtin_ctzll(cand)) *active = 1;
@@ -875,22 +893,31 @@ __global__ __launch_bounds__(256) void k_ls_select_rows(GraphView g, const int8_
       }
     }
   }
-  if (lane < cc) F[e] = win ? 1 : 0;
+  if (mine) F[e] = win ? 1 : 0;
+}
+
+template <bool MAXCUT>
+__global__ __launch_bounds__(256) void k_ls_select_rows(GraphView g, const int8_t *__restrict__ Z,
+                                                        const int32_t *__restrict__ NB,
+                                                        const uint32_t *__restrict__ PRIO, int8_t *__restrict__ F,
+                                                        int32_t *active, const int32_t *prev_active, int32_t ncols,
+                                                        int32_t ld, LiveCols live, int32_t per_wave) {
+  if (prev_active && *prev_active == 0) return;
+  MQO_ROW_CHUNKS(ls_select_rows_chunk<MAXCUT>(row, chunk, nchunk, lm, g, Z, NB, PRIO, F, active, prev_active, ncols,
+                                              ld, live))
 }
 
 template <bool MAXCUT, bool WEIGHTED>
-__global__ __launch_bounds__(256) void k_ls_apply_rows(GraphView g, const int8_t *__restrict__ F,
-                                                       int8_t *__restrict__ Z, int32_t *__restrict__ NB,
-                                                       const int32_t *active, int32_t ncols, int32_t ld) {
-  if (*active == 0) return;
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= g.n) return;  // the whole wavefront
+__device__ __forceinline__ void ls_apply_rows_chunk(
+    int64_t row, int32_t chunk, int32_t nchunk, unsigned long long lm, GraphView g, const int8_t *__restrict__ F,
+    int8_t *__restrict__ Z, int32_t *__restrict__ NB, const int32_t *active, int32_t ncols, int32_t ld, LiveCols live)
+    {
   const int32_t lane = threadIdx.x & 63;
-  const int32_t c0 = (int32_t)blockIdx.y * 64;
+  const int32_t c0 = (int32_t)chunk * 64;
   const int32_t cc = ncols - c0 < 64 ? ncols - c0 : 64;
   const int32_t v = __builtin_amdgcn_readfirstlane((int32_t)(g.lo + row));
   const int64_t e = (int64_t)v * ld + c0 + lane;
-  const bool f = lane < cc && F[e] != 0;
+  const bool f = lane < cc && ((lm >> lane) & 1ull) && F[e] != 0;
   int32_t d = 0;
   if (f) {
     const int32_t z = Z[e];
@@ -917,6 +944,15 @@ __global__ __launch_bounds__(256) void k_ls_apply_rows(GraphView g, const int8_t
   }
 }
 
+template <bool MAXCUT, bool WEIGHTED>
+__global__ __launch_bounds__(256) void k_ls_apply_rows(GraphView g, const int8_t *__restrict__ F,
+                                                       int8_t *__restrict__ Z, int32_t *__restrict__ NB,
+                                                       const int32_t *active, int32_t ncols, int32_t ld,
+                                                       LiveCols live, int32_t per_wave) {
+  if (*active == 0) return;
+  MQO_ROW_CHUNKS(ls_apply_rows_chunk<MAXCUT, WEIGHTED>(row, chunk, nchunk, lm, g, F, Z, NB, active, ncols, ld, live))
+}
+
 // ---------------------------------------------------------------------------
 // pair moves of the paper's own searches, parallel rule: the (1,2)-swap of
 // Def. 2.3 (MIS) and the 2-flip of Def. 2.5 (MaxCut).  One thread per
@@ -936,29 +972,42 @@ __device__ __forceinline__ bool has_edge(const GraphView &g, int32_t a, int32_t 
   return lo < end && g.col_idx[lo] == b;
 }
 
-__global__ __launch_bounds__(256) void k_fill_rows_i32(int32_t *__restrict__ A, int64_t lo, int64_t n, int32_t v,
-                                                       int32_t ncols, int32_t ld, int32_t lanes_log2) {
-  const RowMap m = map_rows<1>(n, ncols, lanes_log2);
-  if (m.active) A[(lo + m.row) * ld + m.col] = v;
-}
-
 // Tightness bits: word (u, chunk) bit l = 1 iff column 64 chunk + l has
-// z_u = 0 and m_u = 1 (u is outside I with exactly one neighbour in I).
-// One wavefront per (row, chunk of 64 columns).
+// z_u = 0 and m_u = 1 (u is outside I with exactly one neighbour in I), for
+// chunks with live columns, whose owners of proposed insertions are cleared
+// (-1).  One wavefront per (row, TB_CHUNKS chunks of 64 columns), their loads
+// issued together (5 bytes per lane and chunk: with one chunk a wavefront the
+// pass ran at 1.5 TB/s).
+constexpr int TB_CHUNKS = 8;
+
 __global__ __launch_bounds__(256) void k_tight_bits(GraphView g, const int8_t *__restrict__ Z,
                                                     const int32_t *__restrict__ NB,
-                                                    unsigned long long *__restrict__ TB, int32_t ncols, int32_t ld) {
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+                                                    unsigned long long *__restrict__ TB, int32_t *__restrict__ OWN,
+                                                    int32_t ncols, int32_t ld, LiveCols live) {
+  const int64_t row =
+      __builtin_amdgcn_readfirstlane((int32_t)((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
   if (row >= g.n) return;  // the whole wavefront
   const int32_t lane = threadIdx.x & 63;
-  const int32_t col = (int32_t)blockIdx.y * 64 + lane;
-  bool t = false;
-  if (col < ncols) {
-    const int64_t e = (g.lo + row) * ld + col;
-    t = Z[e] == 0 && NB[e] == 1;
+  const int32_t nchunk = (ncols + 63) >> 6, k0 = (int32_t)blockIdx.y * TB_CHUNKS;
+  int32_t z[TB_CHUNKS], m[TB_CHUNKS];
+  bool on[TB_CHUNKS];
+#pragma unroll
+  for (int k = 0; k < TB_CHUNKS; ++k) {
+    const int32_t col = (k0 + k) * 64 + lane;
+    on[k] = k0 + k < nchunk && live_mask(live, g.lo + row, k0 + k, nchunk) != 0ull;
+    z[k] = m[k] = 0;
+    if (on[k] && col < ncols) {
+      const int64_t e = (g.lo + row) * ld + col;
+      z[k] = Z[e];
+      m[k] = NB[e];
+      OWN[e] = -1;
+    }
   }
-  const unsigned long long bal = __ballot(t);
-  if (lane == 0) TB[(g.lo + row) * gridDim.y + blockIdx.y] = bal;
+#pragma unroll
+  for (int k = 0; k < TB_CHUNKS; ++k) {
+    const unsigned long long bal = __ballot(z[k] == 0 && m[k] == 1);
+    if (on[k] && lane == 0) TB[(g.lo + row) * nchunk + k0 + k] = bal;
+  }
 }
 
 // v in I proposes the first pair (u, w) of its neighbours in CSR order with
@@ -971,19 +1020,17 @@ __global__ __launch_bounds__(256) void k_tight_bits(GraphView g, const int8_t *_
 // a tight u are tested for adjacency in parallel, the lowest position
 // winning; so the first pair in CSR order is found in a few wavefront-wide
 // steps.
-__global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t *__restrict__ Z,
-                                                      const unsigned long long *__restrict__ TB,
-                                                      int32_t *__restrict__ PU, int32_t *__restrict__ PW,
-                                                      int32_t *__restrict__ OWN, int32_t ncols, int32_t ld) {
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= g.n) return;  // the whole wavefront
+__device__ __forceinline__ void swap_propose_chunk(
+    int64_t row, int32_t chunk, int32_t nchunk, unsigned long long lm, GraphView g, const int8_t *__restrict__ Z,
+    const unsigned long long *__restrict__ TB, int32_t *__restrict__ PU, int32_t *__restrict__ PW, int32_t
+    *__restrict__ OWN, int32_t ncols, int32_t ld, LiveCols live) {
   const int32_t lane = threadIdx.x & 63;
-  const int32_t c0 = (int32_t)blockIdx.y * 64;
+  const int32_t c0 = (int32_t)chunk * 64;
   const int32_t cc = ncols - c0 < 64 ? ncols - c0 : 64;  // columns in this chunk
-  const int64_t nchunk = gridDim.y;
   const int32_t v = __builtin_amdgcn_readfirstlane((int32_t)(g.lo + row));
   const int64_t e = (int64_t)v * ld + c0 + lane;
-  const bool in_i = lane < cc && Z[e] == 1;
+  const bool mine = lane < cc && ((lm >> lane) & 1ull);
+  const bool in_i = mine && Z[e] == 1;
   unsigned long long act = __ballot(in_i);
   const int32_t beg = __builtin_amdgcn_readfirstlane(g.row_ptr[v]);
   const int32_t deg = __builtin_amdgcn_readfirstlane(g.row_ptr[v + 1]) - beg;
@@ -995,15 +1042,15 @@ __global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t 
   if (act) {  // uniform: some column has v in I
     if (lane < deg) {
       ru0 = g.col_idx[beg + lane];
-      rt0 = TB[(int64_t)ru0 * nchunk + blockIdx.y];
+      rt0 = TB[(int64_t)ru0 * nchunk + chunk];
     }
     if (nk > 1 && 64 + lane < deg) {
       ru1 = g.col_idx[beg + 64 + lane];
-      rt1 = TB[(int64_t)ru1 * nchunk + blockIdx.y];
+      rt1 = TB[(int64_t)ru1 * nchunk + chunk];
     }
   }
-  // neighbour chunk k of the row: its ids and tightness words (0 past the row)
-  auto chunk = [&](int32_t k, int32_t &uk, unsigned long long &tk) {
+  // neighbours 64 k .. of the row: its ids and tightness words (0 past the row)
+  auto nbrs = [&](int32_t k, int32_t &uk, unsigned long long &tk) {
     if (k == 0) {
       uk = ru0;
       tk = rt0;
@@ -1013,7 +1060,7 @@ __global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t 
     } else {
       const int32_t pk = 64 * k + lane;
       uk = pk < deg ? g.col_idx[beg + pk] : 0;
-      tk = pk < deg ? TB[(int64_t)uk * nchunk + blockIdx.y] : 0ull;
+      tk = pk < deg ? TB[(int64_t)uk * nchunk + chunk] : 0ull;
     }
   };
   int32_t my_u = -1, my_w = -1;  // lane l: result of column c0 + l
@@ -1025,7 +1072,7 @@ __global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t 
     for (int32_t k = 0; k < nk && !found; ++k) {
       int32_t uk;
       unsigned long long tbk;
-      chunk(k, uk, tbk);
+      nbrs(k, uk, tbk);
       unsigned long long mk = __ballot(((tbk >> c) & 1ull) != 0);
       while (mk && !found) {
         const int32_t i = __builtin_ctzll(mk);
@@ -1040,7 +1087,7 @@ __global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t 
         for (int32_t k2 = k; k2 < nk && !found; ++k2) {
           int32_t w2;
           unsigned long long tb2;
-          chunk(k2, w2, tb2);
+          nbrs(k2, w2, tb2);
           const bool t2 = (k2 > k || lane > i) && ((tb2 >> c) & 1ull);
           unsigned long long cm = __ballot(t2);  // candidate partners, in CSR order
           while (cm && !found) {
@@ -1066,13 +1113,21 @@ __global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t 
       my_w = fw;
     }
   }
-  if (lane >= cc) return;
+  if (!mine) return;
   if (my_u >= 0) {
     OWN[(int64_t)my_u * ld + c0 + lane] = v;
     OWN[(int64_t)my_w * ld + c0 + lane] = v;
   }
   PU[e] = my_u;
   PW[e] = my_w;
+}
+
+__global__ __launch_bounds__(256) void k_swap_propose(GraphView g, const int8_t *__restrict__ Z,
+                                                      const unsigned long long *__restrict__ TB,
+                                                      int32_t *__restrict__ PU, int32_t *__restrict__ PW,
+                                                      int32_t *__restrict__ OWN, int32_t ncols, int32_t ld,
+                                                      LiveCols live, int32_t per_wave) {
+  MQO_ROW_CHUNKS(swap_propose_chunk(row, chunk, nchunk, lm, g, Z, TB, PU, PW, OWN, ncols, ld, live))
 }
 
 // The same proposals with one thread per (v, column), for graphs of small
@@ -1174,21 +1229,19 @@ __global__ __launch_bounds__(256) void k_swap_apply(GraphView g, const int8_t *_
 // coalesced index load and one owner gather per 64 neighbours) instead of
 // one lane walking 2 x degree neighbours, and the neighbour-count updates
 // of a winner are issued 64 at a time.
-__global__ __launch_bounds__(256) void k_swap_select_rows(GraphView g, const int32_t *__restrict__ PU,
-                                                          const int32_t *__restrict__ PW,
-                                                          const int32_t *__restrict__ OWN,
-                                                          const uint32_t *__restrict__ PRIO, int8_t *__restrict__ F,
-                                                          int32_t *active, int32_t ncols, int32_t ld) {
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= g.n) return;  // the whole wavefront
+__device__ __forceinline__ void swap_select_rows_chunk(
+    int64_t row, int32_t chunk, int32_t nchunk, unsigned long long lm, GraphView g, const int32_t *__restrict__ PU,
+    const int32_t *__restrict__ PW, const int32_t *__restrict__ OWN, const uint32_t *__restrict__ PRIO, int8_t
+    *__restrict__ F, int32_t *active, int32_t ncols, int32_t ld, LiveCols live, unsigned long long *moved) {
   const int32_t lane = threadIdx.x & 63;
-  const int32_t c0 = (int32_t)blockIdx.y * 64;
+  const int32_t c0 = (int32_t)chunk * 64;
   const int32_t cc = ncols - c0 < 64 ? ncols - c0 : 64;
   const int32_t v = __builtin_amdgcn_readfirstlane((int32_t)(g.lo + row));
   const int64_t e = (int64_t)v * ld + c0 + lane;
-  const int32_t pu = lane < cc ? PU[e] : -1;
-  const int32_t pw = lane < cc ? PW[e] : -1;
-  const uint32_t pv = lane < cc ? PRIO[e] : 0u;
+  const bool mine = lane < cc && ((lm >> lane) & 1ull);
+  const int32_t pu = mine ? PU[e] : -1;
+  const int32_t pw = pu >= 0 ? PW[e] : -1;
+  const uint32_t pv = pu >= 0 ? PRIO[e] : 0u;
   bool win = pu >= 0;
   unsigned long long prop = __ballot(pu >= 0);
   while (prop) {
@@ -1214,24 +1267,33 @@ __global__ __launch_bounds__(256) void k_swap_select_rows(GraphView g, const int
     if (lane == c) win = !lose;
   }
   const unsigned long long bal = __ballot(win);
-  if (win && lane == __builtin_ctzll(bal)) *active = 1;
-  if (lane < cc) F[e] = win ? 1 : 0;
+  if (win && lane == __builtin_ctzll(bal)) {
+    *active = 1;
+    if (moved) atomicOr(moved + (int64_t)live.rgraph[v] * nchunk + chunk, bal);
+  }
+  if (mine) F[e] = win ? 1 : 0;
 }
 
-__global__ __launch_bounds__(256) void k_swap_apply_rows(GraphView g, const int8_t *__restrict__ F,
-                                                         const int32_t *__restrict__ PU,
-                                                         const int32_t *__restrict__ PW, int8_t *__restrict__ Z,
-                                                         int32_t *__restrict__ NB, const int32_t *active,
-                                                         int32_t ncols, int32_t ld) {
-  if (*active == 0) return;
-  const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= g.n) return;  // the whole wavefront
+__global__ __launch_bounds__(256) void k_swap_select_rows(GraphView g, const int32_t *__restrict__ PU,
+                                                          const int32_t *__restrict__ PW,
+                                                          const int32_t *__restrict__ OWN,
+                                                          const uint32_t *__restrict__ PRIO, int8_t *__restrict__ F,
+                                                          int32_t *active, int32_t ncols, int32_t ld, LiveCols live,
+                                                          unsigned long long *moved, int32_t per_wave) {
+  MQO_ROW_CHUNKS(swap_select_rows_chunk(row, chunk, nchunk, lm, g, PU, PW, OWN, PRIO, F, active, ncols, ld, live,
+                                        moved))
+}
+
+__device__ __forceinline__ void swap_apply_rows_chunk(
+    int64_t row, int32_t chunk, int32_t nchunk, unsigned long long lm, GraphView g, const int8_t *__restrict__ F,
+    const int32_t *__restrict__ PU, const int32_t *__restrict__ PW, int8_t *__restrict__ Z, int32_t *__restrict__ NB,
+    const int32_t *active, int32_t ncols, int32_t ld, LiveCols live) {
   const int32_t lane = threadIdx.x & 63;
-  const int32_t c0 = (int32_t)blockIdx.y * 64;
+  const int32_t c0 = (int32_t)chunk * 64;
   const int32_t cc = ncols - c0 < 64 ? ncols - c0 : 64;
   const int32_t v = __builtin_amdgcn_readfirstlane((int32_t)(g.lo + row));
   const int64_t e = (int64_t)v * ld + c0 + lane;
-  const bool f = lane < cc && F[e] != 0;
+  const bool f = lane < cc && ((lm >> lane) & 1ull) && F[e] != 0;
   const int32_t pu = f ? PU[e] : -1;
   const int32_t pw = f ? PW[e] : -1;
   unsigned long long wins = __ballot(f);
@@ -1250,6 +1312,15 @@ __global__ __launch_bounds__(256) void k_swap_apply_rows(GraphView g, const int8
       for (int32_t m = lane; m < xd; m += 64) atomicAdd(&NB[(int64_t)g.col_idx[xb + m] * ld + col], d);
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_swap_apply_rows(GraphView g, const int8_t *__restrict__ F,
+                                                         const int32_t *__restrict__ PU,
+                                                         const int32_t *__restrict__ PW, int8_t *__restrict__ Z,
+                                                         int32_t *__restrict__ NB, const int32_t *active,
+                                                         int32_t ncols, int32_t ld, LiveCols live, int32_t per_wave) {
+  if (*active == 0) return;
+  MQO_ROW_CHUNKS(swap_apply_rows_chunk(row, chunk, nchunk, lm, g, F, PU, PW, Z, NB, active, ncols, ld, live))
 }
 
 // Total order of 2-flip pairs (gain, (prio_v + prio_u) mod 2^32, -min, -max):
@@ -2037,6 +2108,34 @@ __device__ __forceinline__ int32_t table_find(const int32_t *first, int32_t coun
   return lo;
 }
 
+// The priorities of a pair search for the rows of a table's graphs
+// (blockIdx.y: purposes LS and SWAP) and the graph of every row: thread per
+// (block of 8 rows, column).  Per graph and purpose it was a launch of 3 us
+// (128 graphs: 0.86 ms of a 16 ms search).
+__global__ __launch_bounds__(256) void k_pair_prio(uint32_t *__restrict__ PRIO_LS, uint32_t *__restrict__ PRIO_SW,
+                                                   int32_t *__restrict__ rgraph, GraphTable t, int32_t z0,
+                                                   int32_t ncols, int32_t ld, uint64_t seed, uint64_t traj0,
+                                                   uint64_t stride, uint64_t round) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= (int64_t)t.blk[t.count] * ncols) return;
+  const int32_t c = (int32_t)(idx % ncols);
+  const int64_t b = idx / ncols;
+  const int32_t z = table_find(t.blk, t.count, b);
+  const int64_t lo = t.lo[z], n = t.lo[z + 1] - lo, vb = b - t.blk[z];
+  uint32_t *PRIO = blockIdx.y ? PRIO_SW : PRIO_LS;
+  uint32_t r[8];
+  philox_block8(r, seed, blockIdx.y ? PURPOSE_SWAP : PURPOSE_LS, traj0 + (uint64_t)z * stride + c, round,
+                (uint64_t)vb);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int64_t v = vb * 8 + i;
+    if (v < n) {
+      PRIO[(lo + v) * ld + c] = r[i];
+      if (rgraph && c == 0 && blockIdx.y == 0) rgraph[lo + v] = z0 + z;
+    }
+  }
+}
+
 // The row workgroups of every graph of a table in one launch: the sums of
 // each row and each partial row are those of the graph's own launch.  What
 // bounds a batch of small graphs is the launches (two per graph): forward
@@ -2625,11 +2724,24 @@ void launch_ls_prio(uint32_t *PRIO, int64_t lo, int64_t n, int32_t ncols, int32_
              (uint64_t)PURPOSE_LS);
 }
 
-void launch_swap_prio(uint32_t *PRIO, int64_t lo, int64_t n, int32_t ncols, int32_t ld, uint64_t seed,
-                      uint64_t traj0, uint64_t round, hipStream_t s) {
-  const int64_t count = ((n + 7) >> 3) * ncols;
-  MQO_LAUNCH(k_ls_prio, dim3(blocks_for(count)), dim3(256), 0, s, PRIO, lo, n, ncols, ld, seed, traj0, round,
-             (uint64_t)PURPOSE_SWAP);
+void launch_pair_prio(uint32_t *PRIO_LS, uint32_t *PRIO_SW, int32_t *rgraph, const GraphTable &t, int32_t z0,
+                      int32_t ncols, int32_t ld, uint64_t seed, uint64_t traj0, uint64_t stride, uint64_t round,
+                      hipStream_t s) {
+  const int64_t count = (int64_t)t.blk[t.count] * ncols;
+  MQO_LAUNCH(k_pair_prio, dim3(blocks_for(count), 2), dim3(256), 0, s, PRIO_LS, PRIO_SW, rgraph, t, z0, ncols, ld,
+             seed, traj0, stride, round);
+}
+
+// Grid of a row search: four wavefronts a workgroup, each per_wave chunks of
+// 64 columns of a row.  With every column live one chunk (a wavefront with
+// eight chunks of many candidates one after the other made the 1-flip search
+// from a random start 18% slower); with the columns that are left, as many as
+// leave 64 wavefronts for each CU, at most 8.
+static inline dim3 row_grid(int64_t nrows, int32_t ncols, const LiveCols &live, int32_t *per_wave) {
+  const int64_t chunks = (ncols + 63) / 64;
+  const int64_t room = live.words ? nrows * chunks / (256 * 64) : 1;
+  *per_wave = (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(chunks, 8), room));
+  return dim3((unsigned)((nrows + 3) / 4), (unsigned)((chunks + *per_wave - 1) / *per_wave), 1);
 }
 
 // whether the per-column searches take four columns per lane: 4-byte access
@@ -2646,7 +2758,7 @@ static inline bool four_columns(int32_t ncols, int32_t ld, std::initializer_list
 
 void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, const int32_t *NB,
                             const uint32_t *PRIO, int32_t *T0, int32_t *T1, int32_t *T2, uint32_t *TB, int32_t ncols,
-                            int32_t ld, double mean_degree, hipStream_t s) {
+                            int32_t ld, double mean_degree, hipStream_t s, LiveCols live) {
   const int ll = lanes_log2_for(ncols);
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   if (maxcut) {
@@ -2664,14 +2776,14 @@ void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, co
       MQO_LAUNCH((k_flip2_best<false, 1>), grid, dim3(256), 0, s, g, Z, NB, PRIO, T0, bh, T2, ncols, ld, ll);
     }
   } else {
-    // owners of the proposed insertions, -1 elsewhere
-    MQO_LAUNCH(k_fill_rows_i32, grid, dim3(256), 0, s, T2, g.lo, g.n, -1, ncols, ld, ll);
-    // one wavefront per (row, 64 columns)
-    const dim3 wgrid = grid_rows(g.n, ncols, 6, 1, 256);
+    int32_t per_wave;
+    const dim3 wgrid = row_grid(g.n, ncols, live, &per_wave);
     unsigned long long *tb = reinterpret_cast<unsigned long long *>(TB);
-    MQO_LAUNCH(k_tight_bits, wgrid, dim3(256), 0, s, g, Z, NB, tb, ncols, ld);
+    // T2: owners of the proposed insertions, -1 elsewhere
+    const dim3 tgrid(wgrid.x, (unsigned)((ncols + 64 * TB_CHUNKS - 1) / (64 * TB_CHUNKS)));
+    MQO_LAUNCH(k_tight_bits, tgrid, dim3(256), 0, s, g, Z, NB, tb, T2, ncols, ld, live);
     if (mean_degree >= 24.0)
-      MQO_LAUNCH(k_swap_propose, wgrid, dim3(256), 0, s, g, Z, tb, T0, T1, T2, ncols, ld);
+      MQO_LAUNCH(k_swap_propose, wgrid, dim3(256), 0, s, g, Z, tb, T0, T1, T2, ncols, ld, live, per_wave);
     else
       MQO_LAUNCH(k_swap_propose_lanes, grid, dim3(256), 0, s, g, Z, tb, T0, T1, T2, ncols, ld, ll);
   }
@@ -2679,7 +2791,7 @@ void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, co
 
 void launch_pair_apply(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, const uint32_t *PRIO, int8_t *F,
                        const int32_t *T0, const int32_t *T1, const int32_t *T2, int32_t *active, int32_t ncols,
-                       int32_t ld, double mean_degree, hipStream_t s) {
+                       int32_t ld, double mean_degree, hipStream_t s, LiveCols live, unsigned long long *moved) {
   const int ll = lanes_log2_for(ncols);
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   if (maxcut) {
@@ -2701,9 +2813,11 @@ void launch_pair_apply(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, 
       MQO_LAUNCH((k_flip2_apply<false, 1>), grid, dim3(256), 0, s, g, F, T2, Z, NB, active, ncols, ld, ll);
   } else {
     if (mean_degree >= 24.0) {
-      const dim3 wgrid = grid_rows(g.n, ncols, 6, 1, 256);  // one wavefront per (row, 64 columns)
-      MQO_LAUNCH(k_swap_select_rows, wgrid, dim3(256), 0, s, g, T0, T1, T2, PRIO, F, active, ncols, ld);
-      MQO_LAUNCH(k_swap_apply_rows, wgrid, dim3(256), 0, s, g, F, T0, T1, Z, NB, active, ncols, ld);
+      int32_t per_wave;
+      const dim3 wgrid = row_grid(g.n, ncols, live, &per_wave);
+      MQO_LAUNCH(k_swap_select_rows, wgrid, dim3(256), 0, s, g, T0, T1, T2, PRIO, F, active, ncols, ld, live,
+                 moved, per_wave);
+      MQO_LAUNCH(k_swap_apply_rows, wgrid, dim3(256), 0, s, g, F, T0, T1, Z, NB, active, ncols, ld, live, per_wave);
     } else {
       MQO_LAUNCH(k_swap_select, grid, dim3(256), 0, s, g, T0, T1, T2, PRIO, F, active, ncols, ld, ll);
       MQO_LAUNCH(k_swap_apply, grid, dim3(256), 0, s, g, F, T0, T1, Z, NB, active, ncols, ld, ll);
@@ -2713,21 +2827,27 @@ void launch_pair_apply(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, 
 
 void launch_ls_iteration(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, const uint32_t *PRIO, int8_t *F,
                          int32_t *active, const int32_t *prev_active, int32_t ncols, int32_t ld, double mean_degree,
-                         hipStream_t s) {
+                         hipStream_t s, LiveCols live) {
   const int ll = lanes_log2_for(ncols);
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   const bool w = g.weight != nullptr;
   if (mean_degree >= 24.0) {
-    const dim3 wgrid = grid_rows(g.n, ncols, 6, 1, 256);  // one wavefront per (row, 64 columns)
+    int32_t per_wave;
+    const dim3 wgrid = row_grid(g.n, ncols, live, &per_wave);
     if (maxcut) {
-      MQO_LAUNCH(k_ls_select_rows<true>, wgrid, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld);
+      MQO_LAUNCH(k_ls_select_rows<true>, wgrid, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld,
+                 live, per_wave);
       if (w)
-        MQO_LAUNCH((k_ls_apply_rows<true, true>), wgrid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld);
+        MQO_LAUNCH((k_ls_apply_rows<true, true>), wgrid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, live,
+                 per_wave);
       else
-        MQO_LAUNCH((k_ls_apply_rows<true, false>), wgrid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld);
+        MQO_LAUNCH((k_ls_apply_rows<true, false>), wgrid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, live,
+                 per_wave);
     } else {
-      MQO_LAUNCH(k_ls_select_rows<false>, wgrid, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld);
-      MQO_LAUNCH((k_ls_apply_rows<false, false>), wgrid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld);
+      MQO_LAUNCH(k_ls_select_rows<false>, wgrid, dim3(256), 0, s, g, Z, NB, PRIO, F, active, prev_active, ncols, ld,
+                 live, per_wave);
+      MQO_LAUNCH((k_ls_apply_rows<false, false>), wgrid, dim3(256), 0, s, g, F, Z, NB, active, ncols, ld, live,
+                 per_wave);
     }
     return;
   }

@@ -53,12 +53,16 @@ void launch_evaluate(bool maxcut, const GraphView &g, const int8_t *Z, int32_t *
                      int64_t *conflicts, int8_t *fixed, int32_t ncols, int32_t ld, hipStream_t s);
 void launch_ls_prio(uint32_t *PRIO, int64_t lo, int64_t n, int32_t ncols, int32_t ld, uint64_t seed, uint64_t traj0,
                     uint64_t round, hipStream_t s);
+// Columns a pair search still works on (row searches of dense graphs): bit l
+// of word (graph of the row, chunk) is column 64 chunk + l.  rgraph: the
+// word row of every row, counted from rows' first; words nullptr = all.
+struct LiveCols {
+  const unsigned long long *words;
+  const int32_t *rgraph;
+};
 void launch_ls_iteration(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, const uint32_t *PRIO, int8_t *F,
                          int32_t *active, const int32_t *prev_active, int32_t ncols, int32_t ld, double mean_degree,
-                         hipStream_t s);
-// priorities of purpose SWAP for the pair moves
-void launch_swap_prio(uint32_t *PRIO, int64_t lo, int64_t n, int32_t ncols, int32_t ld, uint64_t seed,
-                      uint64_t traj0, uint64_t round, hipStream_t s);
+                         hipStream_t s, LiveCols live = {nullptr, nullptr});
 // One parallel pair-move iteration ((1,2)-swap for MIS, 2-flip for MaxCut)
 // on a 1-flip optimum, in two launches: the candidates (MIS proposals /
 // best improving pair per vertex) into T0..T2 (int32 scratch [n][ld] each),
@@ -67,10 +71,12 @@ void launch_swap_prio(uint32_t *PRIO, int64_t lo, int64_t n, int32_t ncols, int3
 // TB: tightness bits, 8 * rows * ceil(ncols / 64) bytes, 8-byte aligned
 void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, const int32_t *NB,
                             const uint32_t *PRIO, int32_t *T0, int32_t *T1, int32_t *T2, uint32_t *TB, int32_t ncols,
-                            int32_t ld, double mean_degree, hipStream_t s);
+                            int32_t ld, double mean_degree, hipStream_t s, LiveCols live);
+// moved (or nullptr): the words of LiveCols in which the columns that applied
+// a move are set (the caller clears them)
 void launch_pair_apply(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, const uint32_t *PRIO, int8_t *F,
                        const int32_t *T0, const int32_t *T1, const int32_t *T2, int32_t *active, int32_t ncols,
-                       int32_t ld, double mean_degree, hipStream_t s);
+                       int32_t ld, double mean_degree, hipStream_t s, LiveCols live, unsigned long long *moved);
 void launch_accept(const int8_t *Z, int8_t *Zb, const int64_t *value, int64_t *best, int64_t lo, int64_t n,
                    int32_t ncols, int32_t ld, int32_t ldb, bool first, hipStream_t s);
 size_t reset_scratch_bytes(int32_t ncols);
@@ -128,6 +134,12 @@ struct GraphTable {
   int32_t blk[GRAPH_TABLE + 1];
   int32_t sl[GRAPH_TABLE + 1];
 };
+// priorities of purposes LS and SWAP for the rows of the table's graphs (t.blk:
+// their blocks of 8 rows): graph z's column c is trajectory traj0 + z stride
+// + c.  rgraph (or nullptr): z0 + z for every row.
+void launch_pair_prio(uint32_t *PRIO_LS, uint32_t *PRIO_SW, int32_t *rgraph, const GraphTable &t, int32_t z0,
+                      int32_t ncols, int32_t ld, uint64_t seed, uint64_t traj0, uint64_t stride, uint64_t round,
+                      hipStream_t s);
 // g: any of the graphs, for the arrays and flags they share (no hub lists)
 void launch_objective_grad_batch(int form, const GraphView &g, const GraphTable &t, const float *X,
                                  const float *scale, float *grad, double *part, int32_t ncols, int32_t ld,
