@@ -2267,39 +2267,43 @@ int mqo_pga_unrolled_backward(const mqo_graph *g, mqo_objective obj, float param
     return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", mqo_unrolled_workspace_size(g, B, ckpt_every));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   drop_stale_error();
-  const bool mc = obj != MQO_OBJ_MIS_H;
   const int form = (int)obj;
   const StepCfg cfg = default_step_cfg(B, B);
   const int64_t nb = g->n_total * B;
   const size_t slot = align_up((size_t)nb * sizeof(float));
   char *base = reinterpret_cast<char *>(ws);
-  std::vector<float *> states(ckpt_every);
-  for (int32_t i = 1; i < ckpt_every; ++i) states[i] = reinterpret_cast<float *>(base + slot * (i - 1));
-  float *lamA = reinterpret_cast<float *>(base + slot * (ckpt_every - 1));
-  float *lamB = reinterpret_cast<float *>(base + slot * ckpt_every);
-  float *mu = reinterpret_cast<float *>(base + slot * (ckpt_every + 1));
-  double *part = reinterpret_cast<double *>(base + slot * (ckpt_every + 2));
-  const int32_t nseg = K / ckpt_every;
+  // slots: the kept gradients of a segment's steps, two for its states and,
+  // after them, for mu, and lam
+  const int32_t c = ckpt_every;
+  auto at_slot = [&](int32_t i) { return reinterpret_cast<float *>(base + slot * i); };
+  float *lam = at_slot(c + 2);
+  double *part = reinterpret_cast<double *>(base + slot * (c + 3));
+  const int32_t nseg = K / c;
   for (int32_t gi = 0; gi < g->num_graphs; ++gi) {
     const GraphView gv = view_of(g, gi);
     const int64_t nblk = spmm_row_blocks(gv, cfg) + gv.nhub;
-    launch_copy_f32(dL_dXK + gv.lo * B, lamA + gv.lo * B, gv.n * B, s);
     launch_fill_i64(reinterpret_cast<int64_t *>(dL_dalpha + (int64_t)gi * B), B, 0, s);  // +0.0
-    float *cur = lamA, *nxt = lamB;
     for (int32_t j = nseg - 1; j >= 0; --j) {
-      states[0] = const_cast<float *>(ckpt + (int64_t)j * nb);
-      for (int32_t i = 1; i < ckpt_every; ++i)
-        launch_pga_step(form, gv, states[i - 1], states[i], nullptr, B, B, cfg, alpha, 0.0f, param, s);
+      const float *x = ckpt + (int64_t)j * nb;
+      for (int32_t i = 0; i < c; ++i) {
+        float *xn = i + 1 < c ? at_slot(c + (i & 1)) : nullptr;
+        launch_adjoint_grad(form, gv, x, xn, at_slot(i), B, B, cfg, alpha, param, s);
+        x = xn;
+      }
       // the segment's steps write consecutive partial slabs of nblk rows,
       // summed in one fixed-order reduction per segment
-      for (int32_t i = ckpt_every - 1; i >= 0; --i) {
-        double *slab = part + (int64_t)(ckpt_every - 1 - i) * nblk * B;
-        launch_adjoint_step(form, gv, states[i], cur, mu, nxt, slab, B, B, cfg, alpha, param, s);
-        std::swap(cur, nxt);
+      const float *top = j == nseg - 1 ? dL_dXK : lam;
+      float *mu = at_slot(c), *next = at_slot(c + 1);
+      launch_adjoint_mask(gv, top, at_slot(c - 1), mu, part, B, B, cfg, s);
+      for (int32_t i = c - 1; i >= 0; --i) {
+        const float *kept = i > 0 ? at_slot(i - 1) : nullptr;
+        float *out = i > 0 ? next : j > 0 ? lam : dL_dX0;
+        launch_adjoint_lambda(form, gv, mu, kept, out, part + (int64_t)(c - i) * nblk * B, B, B, cfg, alpha, param,
+                              s);
+        std::swap(mu, next);
       }
-      launch_reduce_partials(part, (int64_t)ckpt_every * nblk, B, dL_dalpha + (int64_t)gi * B, true, s);
+      launch_reduce_partials(part, (int64_t)c * nblk, B, dL_dalpha + (int64_t)gi * B, true, s);
     }
-    launch_copy_f32(cur + gv.lo * B, dL_dX0 + gv.lo * B, gv.n * B, s);
   }
   if (dL_dalpha_sum) launch_sum_f64(dL_dalpha, (int64_t)g->num_graphs * B, dL_dalpha_sum, s);
   HIP_TRY(hipGetLastError());

@@ -387,23 +387,30 @@ __device__ __forceinline__ bool is_hub_row(const GraphView &g, int64_t v) {
 // neighbour sums and their weight sums W_v.  Every lane of the group must call it.  ROWS = 2 is
 // launched for near-regular graphs only: two rows of equal degree go in
 // lockstep, otherwise one after the other.
-template <int VEC, bool WEIGHTED, int ROWS, int KB = 4>
-__device__ __forceinline__ void group_gather(const GraphView &g, const float *__restrict__ X, int64_t bx, int32_t by,
-                                             int32_t ncols, int32_t ld, int32_t lanes_log2, int64_t (&v)[ROWS],
-                                             bool (&own)[ROWS], int32_t &col, float (&acc)[ROWS][VEC],
-                                             int32_t (&wsum)[ROWS]) {
+template <int VEC, int ROWS>
+__device__ __forceinline__ void group_rows(const GraphView &g, int64_t bx, int32_t by, int32_t lanes_log2,
+                                           int64_t (&v)[ROWS], bool (&own)[ROWS], int32_t &col) {
   const int32_t lanes = 1 << lanes_log2;
   const int32_t rpb = blockDim.x >> lanes_log2;
   const int64_t r0 = bx * ROWS * rpb + (threadIdx.x >> lanes_log2);
   col = (int32_t)(by * lanes + (threadIdx.x & (lanes - 1))) * VEC;
-  const bool colok = col < ncols;
 #pragma unroll
   for (int k = 0; k < ROWS; ++k) {
     const int64_t r = r0 + (int64_t)k * rpb;
     v[k] = g.lo + r;
     own[k] = r < g.n && !is_hub_row(g, v[k]);
-    wsum[k] = 0;
   }
+}
+
+template <int VEC, bool WEIGHTED, int ROWS, int KB = 4>
+__device__ __forceinline__ void group_gather(const GraphView &g, const float *__restrict__ X, int64_t bx, int32_t by,
+                                             int32_t ncols, int32_t ld, int32_t lanes_log2, int64_t (&v)[ROWS],
+                                             bool (&own)[ROWS], int32_t &col, float (&acc)[ROWS][VEC],
+                                             int32_t (&wsum)[ROWS]) {
+  group_rows<VEC, ROWS>(g, bx, by, lanes_log2, v, own, col);
+  const bool colok = col < ncols;
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) wsum[k] = 0;
   if constexpr (ROWS == 2) {
     if (own[0] && own[1] &&
         g.row_ptr[v[0] + 1] - g.row_ptr[v[0]] == g.row_ptr[v[1] + 1] - g.row_ptr[v[1]]) {
@@ -2333,41 +2340,58 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double *__restric
   }
 }
 
-// adjoint, part 1: recompute g(x_k), the clip mask, mu = mask * lam_next,
-// and partials of <mu, g> for dL/dalpha (rows as in k_objective_grad)
+// The adjoint of a segment of steps.  Going forward through it again, every
+// step keeps its gradient with the clip mask in it (k_adj_grad); going
+// backward, mu_k = mask_k lam_{k+1} and lam_k = mu_k + alpha (H mu_k), and one
+// sparse product gives lam_k, mu_{k-1} and the partials of <mu_{k-1},
+// g_{k-1}> for dL/dalpha together (k_adj_lambda).  That is two sparse products
+// a step; with the gradient recomputed for the mask as well it was 2.8 (K =
+// 20, checkpoints every 5: 56 products for the backward, now 40).  What
+// bounds each is the neighbour gathers; the kept gradients add one write and
+// one read of an array per step.  Random 5-regular n = 1e5, 64 trajectories,
+// forward and backward: 2.25 -> 1.94 ms.
+//
+// A kept gradient of a clipped entry (mask 0, mu = 0) is one of two NaNs: its
+// product <mu, g> is 0, or NaN where g is not finite.  An entry inside the box
+// never holds a NaN.
+constexpr uint32_t CLIPPED = 0x7fc00001u, CLIPPED_NAN = 0x7fc00002u;
+
 template <int OBJ>
-__device__ __forceinline__ void adjoint_mu(float x, float ln, float acc, float W, float alpha, float param, float &mu,
-                                           double &dv) {
+__device__ __forceinline__ float adjoint_grad(float x, float acc, float W, float alpha, float param, float &xn) {
   constexpr bool MAXCUT = OBJ != OBJ_H;
   const float gr = grad_of<OBJ>(acc, x, W, param);
   const float s = alpha * gr;
   const float z = x + s;
+  xn = clip_box<MAXCUT>(z);
   const bool mask = z >= box_lo<MAXCUT>() && z <= box_hi();
-  mu = mask ? ln : 0.0f;
-  dv = (double)mu * (double)gr;
+  const bool finite = (__float_as_uint(gr) & 0x7f800000u) != 0x7f800000u;
+  return mask ? gr : __uint_as_float(finite ? CLIPPED : CLIPPED_NAN);
 }
 
+__device__ __forceinline__ void adjoint_mu(float ln, float kept, float &mu, double &dv) {
+  const uint32_t b = __float_as_uint(kept);
+  const bool clipped = b == CLIPPED || b == CLIPPED_NAN;
+  mu = clipped ? 0.0f : ln;
+  dv = clipped ? (b == CLIPPED ? 0.0 : (double)kept) : (double)ln * (double)kept;
+}
+
+// x_{k+1} into Xn (unless nullptr) and the kept gradient of step k into GK
 template <int VEC, int OBJ, bool WEIGHTED, int ROWS, int KB = 4>
-__global__ __launch_bounds__(256) void k_adj_mu(GraphView g, const float *__restrict__ Xk,
-                                                const float *__restrict__ lam_next, float *__restrict__ mu_out,
-                                                double *__restrict__ part, int32_t ncols, int32_t ld,
-                                                int32_t lanes_log2, float alpha, float param) {
+__global__ __launch_bounds__(256) void k_adj_grad(GraphView g, const float *__restrict__ Xk, float *__restrict__ Xn,
+                                                  float *__restrict__ GK, int32_t ncols, int32_t ld,
+                                                  int32_t lanes_log2, float alpha, float param) {
   const int64_t nhb = hub_blocks(g, ncols);
-  const int64_t nrb = gridDim.x - nhb;
   const Blk blk = xcd_blk(g.xcd_local);
   if (blk.x < nhb) {
     if (blk.y != 0) return;
     const HubItem it = hub_item(g, ncols, blk.x);
     const float acc = hub_gather<WEIGHTED>(g, Xk, it, ld);
     if ((int32_t)threadIdx.x < it.cw) {
-      const int32_t c = it.c0 + threadIdx.x;
-      const int64_t e = it.v * ld + c;
-      float mu;
-      double dv;
+      const int64_t e = it.v * ld + it.c0 + threadIdx.x;
       const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? weighted_degree<WEIGHTED>(g, it.v) : 0.0f;
-      adjoint_mu<OBJ>(Xk[e], lam_next[e], acc, W, alpha, param, mu, dv);
-      mu_out[e] = mu;
-      part[(nrb + it.h) * ncols + c] = dv;
+      float xn;
+      GK[e] = adjoint_grad<OBJ>(Xk[e], acc, W, alpha, param, xn);
+      if (Xn) Xn[e] = xn;
     }
     return;
   }
@@ -2377,6 +2401,49 @@ __global__ __launch_bounds__(256) void k_adj_mu(GraphView g, const float *__rest
   float acc[ROWS][VEC];
   int32_t wsum[ROWS];
   group_gather<VEC, WEIGHTED, ROWS, KB>(g, Xk, blk.x - nhb, blk.y, ncols, ld, lanes_log2, v, own, col, acc, wsum);
+  if (col >= ncols) return;
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) {
+    if (!own[k]) continue;
+    float x[VEC], xn[VEC], kept[VEC];
+    load_vec<VEC>(Xk + v[k] * ld + col, x);
+    const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? (float)wsum[k] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) kept[i] = adjoint_grad<OBJ>(x[i], acc[k][i], W, alpha, param, xn[i]);
+    store_vec<VEC>(GK + v[k] * ld + col, kept);
+    if (Xn) store_vec<VEC>(Xn + v[k] * ld + col, xn);
+  }
+}
+
+// mu_k from lam_{k+1} at the top of a segment, where the sparse product that
+// gave lam ran before the segment's gradients were known; the rows and their
+// partials lie as in the sparse products
+template <int VEC, int ROWS>
+__global__ __launch_bounds__(256) void k_adj_mask(GraphView g, const float *__restrict__ lam,
+                                                  const float *__restrict__ GK, float *__restrict__ mu_out,
+                                                  double *__restrict__ part, int32_t ncols, int32_t ld,
+                                                  int32_t lanes_log2) {
+  const int64_t nhb = hub_blocks(g, ncols);
+  const int64_t nrb = gridDim.x - nhb;
+  const Blk blk = xcd_blk(g.xcd_local);
+  if (blk.x < nhb) {
+    if (blk.y != 0) return;
+    const HubItem it = hub_item(g, ncols, blk.x);
+    if ((int32_t)threadIdx.x < it.cw) {
+      const int32_t c = it.c0 + threadIdx.x;
+      const int64_t e = it.v * ld + c;
+      float mu;
+      double dv;
+      adjoint_mu(lam[e], GK[e], mu, dv);
+      mu_out[e] = mu;
+      part[(nrb + it.h) * ncols + c] = dv;
+    }
+    return;
+  }
+  int64_t v[ROWS];
+  bool own[ROWS];
+  int32_t col;
+  group_rows<VEC, ROWS>(g, blk.x - nhb, blk.y, lanes_log2, v, own, col);
   double dv[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) dv[i] = 0.0;
@@ -2385,14 +2452,13 @@ __global__ __launch_bounds__(256) void k_adj_mu(GraphView g, const float *__rest
   for (int k = 0; k < ROWS; ++k) {
     if (!own[k] || col >= ncols) continue;
     any = true;
-    float x[VEC], ln[VEC], mu[VEC];
-    load_vec<VEC>(Xk + v[k] * ld + col, x);
-    load_vec<VEC>(lam_next + v[k] * ld + col, ln);
-    const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? (float)wsum[k] : 0.0f;
+    float ln[VEC], kept[VEC], mu[VEC];
+    load_vec<VEC>(lam + v[k] * ld + col, ln);
+    load_vec<VEC>(GK + v[k] * ld + col, kept);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       double d;
-      adjoint_mu<OBJ>(x[i], ln[i], acc[k][i], W, alpha, param, mu[i], d);
+      adjoint_mu(ln[i], kept[i], mu[i], d);
       dv[i] += d;
     }
     store_vec<VEC>(mu_out + v[k] * ld + col, mu);
@@ -2400,7 +2466,7 @@ __global__ __launch_bounds__(256) void k_adj_mu(GraphView g, const float *__rest
   block_column_partials<VEC>(dv, any, col, ncols, lanes_log2, part, blk.x - nhb);
 }
 
-// adjoint, part 2: lam_k = mu + alpha (H mu), H the objective's Hessian:
+// lam_k = mu_k + alpha (H mu_k), H the objective's Hessian:
 // -gamma A (h), -2 A (f_B, f_A), (D - A) / 2 (f_L), 2 (D - A + lambda I) (f_P)
 template <int OBJ>
 __device__ __forceinline__ float adjoint_lambda(float mv, float acc, float W, float alpha, float param) {
@@ -2424,20 +2490,31 @@ __device__ __forceinline__ float adjoint_lambda(float mv, float acc, float W, fl
   return mv + t;
 }
 
+// GK: the kept gradient of step k - 1: out = mu_{k-1}, with its partials;
+// nullptr (the bottom of a segment): out = lam_k
 template <int VEC, int OBJ, bool WEIGHTED, int ROWS, int KB = 4>
-__global__ __launch_bounds__(256) void k_adj_lambda(GraphView g, const float *__restrict__ mu, float *__restrict__ lam,
-                                                    int32_t ncols, int32_t ld, int32_t lanes_log2, float alpha,
-                                                    float param) {
+__global__ __launch_bounds__(256) void k_adj_lambda(GraphView g, const float *__restrict__ mu,
+                                                    const float *__restrict__ GK, float *__restrict__ out_,
+                                                    double *__restrict__ part, int32_t ncols, int32_t ld,
+                                                    int32_t lanes_log2, float alpha, float param) {
   const int64_t nhb = hub_blocks(g, ncols);
+  const int64_t nrb = gridDim.x - nhb;
   const Blk blk = xcd_blk(g.xcd_local);
   if (blk.x < nhb) {
     if (blk.y != 0) return;
     const HubItem it = hub_item(g, ncols, blk.x);
     const float acc = hub_gather<WEIGHTED>(g, mu, it, ld);
     if ((int32_t)threadIdx.x < it.cw) {
-      const int64_t e = it.v * ld + it.c0 + threadIdx.x;
+      const int32_t c = it.c0 + threadIdx.x;
+      const int64_t e = it.v * ld + c;
       const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? weighted_degree<WEIGHTED>(g, it.v) : 0.0f;
-      lam[e] = adjoint_lambda<OBJ>(mu[e], acc, W, alpha, param);
+      float o = adjoint_lambda<OBJ>(mu[e], acc, W, alpha, param);
+      if (GK) {
+        double dv;
+        adjoint_mu(o, GK[e], o, dv);
+        part[(nrb + it.h) * ncols + c] = dv;
+      }
+      out_[e] = o;
     }
     return;
   }
@@ -2447,17 +2524,32 @@ __global__ __launch_bounds__(256) void k_adj_lambda(GraphView g, const float *__
   float acc[ROWS][VEC];
   int32_t wsum[ROWS];
   group_gather<VEC, WEIGHTED, ROWS, KB>(g, mu, blk.x - nhb, blk.y, ncols, ld, lanes_log2, v, own, col, acc, wsum);
-  if (col >= ncols) return;
+  double dv[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) dv[i] = 0.0;
+  bool any = false;
 #pragma unroll
   for (int k = 0; k < ROWS; ++k) {
-    if (!own[k]) continue;
+    if (!own[k] || col >= ncols) continue;
+    any = true;
     float mv[VEC], out[VEC];
     load_vec<VEC>(mu + v[k] * ld + col, mv);
     const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? (float)wsum[k] : 0.0f;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) out[i] = adjoint_lambda<OBJ>(mv[i], acc[k][i], W, alpha, param);
-    store_vec<VEC>(lam + v[k] * ld + col, out);
+    if (GK) {
+      float kept[VEC];
+      load_vec<VEC>(GK + v[k] * ld + col, kept);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        double d;
+        adjoint_mu(out[i], kept[i], out[i], d);
+        dv[i] += d;
+      }
+    }
+    store_vec<VEC>(out_ + v[k] * ld + col, out);
   }
+  if (GK) block_column_partials<VEC>(dv, any, col, ncols, lanes_log2, part, blk.x - nhb);
 }
 
 // ===========================================================================
@@ -3133,42 +3225,83 @@ void launch_reduce_partials(double *part, int64_t nblk, int32_t ncols, double *o
 }
 
 template <int VEC>
-struct AdjLaunch {
+struct AdjGradLaunch {
   template <int OBJ, bool W>
-  static void run(const GraphView &g, const float *Xk, const float *lam_next, float *mu, float *lam, double *part,
-                  int32_t ncols, int32_t ld, int ll, float alpha, float param, hipStream_t s) {
+  static void run(const GraphView &g, const float *Xk, float *Xn, float *GK, int32_t ncols, int32_t ld, int ll,
+                  float alpha, float param, hipStream_t s) {
     const dim3 grid = spmm_grid(g, ncols, ll, VEC);
-    const size_t lds_mu = std::max(g.nhub ? hub_lds(W) : 0, PARTIAL_LDS(VEC)), lds_lam = g.nhub ? hub_lds(W) : 0;
-    if (spmm_rows(g, ll) == 2) {
-      MQO_LAUNCH((k_adj_mu<VEC, OBJ, W, 2>), grid, dim3(256), lds_mu, s, g, Xk, lam_next, mu, part, ncols, ld, ll,
-                 alpha, param);
-      MQO_LAUNCH((k_adj_lambda<VEC, OBJ, W, 2>), grid, dim3(256), lds_lam, s, g, mu, lam, ncols, ld, ll, alpha, param);
-      return;
-    }
-    if (g.nhub > 0) {  // uneven degrees: eight gathers in flight per lane group
-      MQO_LAUNCH((k_adj_mu<VEC, OBJ, W, 1, 8>), grid, dim3(256), lds_mu, s, g, Xk, lam_next, mu, part, ncols, ld, ll,
-                 alpha, param);
-      MQO_LAUNCH((k_adj_lambda<VEC, OBJ, W, 1, 8>), grid, dim3(256), lds_lam, s, g, mu, lam, ncols, ld, ll, alpha,
+    const size_t lds = g.nhub ? hub_lds(W) : 0;
+    if (spmm_rows(g, ll) == 2)
+      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 2>), grid, dim3(256), lds, s, g, Xk, Xn, GK, ncols, ld, ll, alpha, param);
+    else if (g.nhub > 0)  // uneven degrees: eight gathers in flight per lane group
+      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 1, 8>), grid, dim3(256), lds, s, g, Xk, Xn, GK, ncols, ld, ll, alpha,
                  param);
-      return;
-    }
-    MQO_LAUNCH((k_adj_mu<VEC, OBJ, W, 1>), grid, dim3(256), lds_mu, s, g, Xk, lam_next, mu, part, ncols, ld, ll,
-               alpha, param);
-    MQO_LAUNCH((k_adj_lambda<VEC, OBJ, W, 1>), grid, dim3(256), lds_lam, s, g, mu, lam, ncols, ld, ll, alpha, param);
+    else
+      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 1>), grid, dim3(256), lds, s, g, Xk, Xn, GK, ncols, ld, ll, alpha, param);
   }
 };
 
-void launch_adjoint_step(int form, const GraphView &g, const float *Xk, const float *lam_next, float *mu,
-                         float *lam, double *part, int32_t ncols, int32_t ld, StepCfg cfg, float alpha, float param,
-                         hipStream_t s) {
+template <int VEC>
+struct AdjLambdaLaunch {
+  template <int OBJ, bool W>
+  static void run(const GraphView &g, const float *mu, const float *GK, float *out, double *part, int32_t ncols,
+                  int32_t ld, int ll, float alpha, float param, hipStream_t s) {
+    const dim3 grid = spmm_grid(g, ncols, ll, VEC);
+    const size_t lds = std::max(g.nhub ? hub_lds(W) : 0, GK ? PARTIAL_LDS(VEC) : 0);
+    if (spmm_rows(g, ll) == 2)
+      MQO_LAUNCH((k_adj_lambda<VEC, OBJ, W, 2>), grid, dim3(256), lds, s, g, mu, GK, out, part, ncols, ld, ll, alpha,
+                 param);
+    else if (g.nhub > 0)
+      MQO_LAUNCH((k_adj_lambda<VEC, OBJ, W, 1, 8>), grid, dim3(256), lds, s, g, mu, GK, out, part, ncols, ld, ll,
+                 alpha, param);
+    else
+      MQO_LAUNCH((k_adj_lambda<VEC, OBJ, W, 1>), grid, dim3(256), lds, s, g, mu, GK, out, part, ncols, ld, ll, alpha,
+                 param);
+  }
+};
+
+void launch_adjoint_grad(int form, const GraphView &g, const float *Xk, float *Xn, float *GK, int32_t ncols,
+                         int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s) {
   const bool w = g.weight != nullptr;
   const int ll = cfg.lanes_log2;
   if (cfg.vec == 4)
-    dispatch_form<AdjLaunch<4>>(form, w, g, Xk, lam_next, mu, lam, part, ncols, ld, ll, alpha, param, s);
+    dispatch_form<AdjGradLaunch<4>>(form, w, g, Xk, Xn, GK, ncols, ld, ll, alpha, param, s);
   else if (cfg.vec == 2)
-    dispatch_form<AdjLaunch<2>>(form, w, g, Xk, lam_next, mu, lam, part, ncols, ld, ll, alpha, param, s);
+    dispatch_form<AdjGradLaunch<2>>(form, w, g, Xk, Xn, GK, ncols, ld, ll, alpha, param, s);
   else
-    dispatch_form<AdjLaunch<1>>(form, w, g, Xk, lam_next, mu, lam, part, ncols, ld, ll, alpha, param, s);
+    dispatch_form<AdjGradLaunch<1>>(form, w, g, Xk, Xn, GK, ncols, ld, ll, alpha, param, s);
+}
+
+void launch_adjoint_lambda(int form, const GraphView &g, const float *mu, const float *GK, float *out, double *part,
+                           int32_t ncols, int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s) {
+  const bool w = g.weight != nullptr;
+  const int ll = cfg.lanes_log2;
+  if (cfg.vec == 4)
+    dispatch_form<AdjLambdaLaunch<4>>(form, w, g, mu, GK, out, part, ncols, ld, ll, alpha, param, s);
+  else if (cfg.vec == 2)
+    dispatch_form<AdjLambdaLaunch<2>>(form, w, g, mu, GK, out, part, ncols, ld, ll, alpha, param, s);
+  else
+    dispatch_form<AdjLambdaLaunch<1>>(form, w, g, mu, GK, out, part, ncols, ld, ll, alpha, param, s);
+}
+
+void launch_adjoint_mask(const GraphView &g, const float *lam, const float *GK, float *mu, double *part,
+                         int32_t ncols, int32_t ld, StepCfg cfg, hipStream_t s) {
+  const int ll = cfg.lanes_log2;
+  const dim3 grid = spmm_grid(g, ncols, ll, cfg.vec);
+  const bool pairs = spmm_rows(g, ll) == 2;
+#define MQO_MASK(VV)                                                                                            \
+  if (pairs)                                                                                                    \
+    MQO_LAUNCH((k_adj_mask<VV, 2>), grid, dim3(256), PARTIAL_LDS(VV), s, g, lam, GK, mu, part, ncols, ld, ll);  \
+  else                                                                                                          \
+    MQO_LAUNCH((k_adj_mask<VV, 1>), grid, dim3(256), PARTIAL_LDS(VV), s, g, lam, GK, mu, part, ncols, ld, ll);
+  if (cfg.vec == 4) {
+    MQO_MASK(4)
+  } else if (cfg.vec == 2) {
+    MQO_MASK(2)
+  } else {
+    MQO_MASK(1)
+  }
+#undef MQO_MASK
 }
 
 }  // namespace mqo
