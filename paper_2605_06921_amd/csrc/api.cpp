@@ -291,9 +291,11 @@ int64_t max_graph_rows(const mqo_graph *g) {
 // ---------------------------------------------------------------------------
 struct Layout {
   size_t X, Xt, V, Z, Zb, NB, PRIO, F, value, best, acc, act, voff, rpat, bestb, dmax, err, reset, tzs, tnb, tprio,
-      tfl, tvm, tls, gorder, lsval, pX, pXt, pV, colact, fixedc, steps, pz[2], pv[2], ph[2], chash, ptaken, psrc,
+      tfl, tvm, tail, tls, gorder, lsval, pX, pXt, pV, colact, fixedc, steps, pz[2], pv[2], ph[2], chash, ptaken, psrc,
       pbase, solz, solv, choice, rgraph, live, eord, estart, eblock, total;
 };
+
+constexpr int TAIL_INTS = 4;  // Layout::tail before the counters: edge updates, tile error, unused
 
 // K: pool slots per graph (0 = no pool); the pool buffers come last, so the
 // other offsets do not depend on K
@@ -320,17 +322,22 @@ Layout make_layout(const mqo_graph *g, int32_t B, int32_t K = 0) {
   L.acc = take(3 * (size_t)B * 8);
   L.act = take(64 * 4);
   L.voff = take((G + 1) * 8);
-  L.rpat = take((G + 1) * 4);
   L.bestb = take(G * 4);
-  L.dmax = take(64);
-  L.err = take(64);
+  // what a solve reads back after validation, in one range: the error words,
+  // the largest degree, row_ptr at the graph boundaries
+  L.err = take(128 + (G + 1) * 4);
+  L.dmax = L.err + 64;
+  L.rpat = L.err + 128;
   L.reset = take(reset_scratch_bytes(B));
   L.tzs = take(tiles_elems);
   L.tnb = take(tiles_elems * 4);  // also the pair search's tightness bits (8 n_total ceil(B/64) bytes)
   L.tprio = take(tiles_elems * 4);  // also the pair search's SWAP priorities (n_total * B <= tiles_elems)
   L.tfl = take(tiles_elems);
   L.tvm = take(tiles_elems * 4);
-  L.tls = take(G * (int64_t)(B + 63) * 4);
+  // what it reads back at its end: the edge updates (int64), the tile kernel's
+  // error word, the workgroups' search iterations
+  L.tail = take(TAIL_INTS * 4 + G * (int64_t)(B + 63) * 4);
+  L.tls = L.tail + TAIL_INTS * 4;
   L.gorder = take(G * 4);  // persistent plan: graphs in launch order
   L.lsval = take((size_t)B * 8);  // the searches' discarded values (not the round's)
   L.pX = take(n * 4);  // plain plan: one trajectory as contiguous vectors
@@ -410,6 +417,22 @@ int read_back_many(const std::vector<std::pair<const int32_t *, int>> &parts, st
   Resources &r = res();
   int total = 0;
   for (const auto &pt : parts) total += pt.second;
+  // ranges of one buffer that lie together: one copy of all of it
+  const int32_t *first = parts[0].first, *end = first;
+  for (const auto &pt : parts) {
+    first = std::min(first, pt.first);
+    end = std::max(end, pt.first + pt.second);
+  }
+  if (end - first <= 1024) {
+    HIP_TRY(hipMemcpyAsync(r.pinned, first, (end - first) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    out.clear();
+    for (const auto &pt : parts) {
+      const int32_t *p = r.pinned + (pt.first - first);
+      out.insert(out.end(), p, p + pt.second);
+    }
+    return MQO_OK;
+  }
   if (total > 1024) {  // larger than the pinned buffer: one at a time
     out.clear();
     for (const auto &pt : parts) {
@@ -432,17 +455,16 @@ int read_back_many(const std::vector<std::pair<const int32_t *, int>> &parts, st
 // Device-side canonical-form check with one synchronisation: the column
 // and hub checks guard their own reads, so they run in the same pass as the
 // row_ptr check.  voff_dev must already hold vtx_offset; err_dev has room
-// for 4 ints.  When rpat_dev / dmax_dev are given, it also returns the
+// for 4 ints (17 with dmax_dev = err_dev + 16).  When rpat_dev / dmax_dev are given, it also returns the
 // row_ptr entries at the graph boundaries (rp, G+1 values) and the largest
 // degree (max_deg).
 int validate_on_device(const mqo_graph *g, int64_t *voff_dev, int32_t *err_dev, hipStream_t s,
                        int32_t *rpat_dev = nullptr, int32_t *dmax_dev = nullptr, std::vector<int32_t> *rp = nullptr,
                        int32_t *max_deg = nullptr) {
-  launch_fill_i32(err_dev, 4, 0, s);
-  launch_validate_rows(g->row_ptr, g->n_total, g->nnz_total, err_dev, s);
-  if (g->nnz_total > 0)
-    launch_validate_cols(g->row_ptr, g->col_idx, g->weight, voff_dev, g->num_graphs, g->n_total, g->nnz_total,
-                         err_dev + 1, s);
+  // (the largest degree lies 16 words after the error words: cleared together)
+  launch_fill_i32(err_dev, dmax_dev ? 17 : 4, 0, s);
+  launch_validate_graph(g->row_ptr, g->col_idx, g->weight, voff_dev, g->num_graphs, g->n_total, g->nnz_total, err_dev,
+                        rpat_dev, dmax_dev, s);
   const bool hubs = g->hub_offset != nullptr;
   if (hubs) {
     for (int32_t i = 0; i < g->num_graphs; ++i) {
@@ -454,14 +476,8 @@ int validate_on_device(const mqo_graph *g, int64_t *voff_dev, int32_t *err_dev, 
     launch_count_hubs(g->row_ptr, g->n_total, g->hub_min_degree, err_dev + 3, s);
   }
   std::vector<std::pair<const int32_t *, int>> parts{{err_dev, 4}};
-  if (rpat_dev) {
-    launch_gather_rowptr(g->row_ptr, voff_dev, g->num_graphs, rpat_dev, s);
-    parts.push_back({rpat_dev, g->num_graphs + 1});
-  }
-  if (dmax_dev) {
-    launch_degree_max(g->row_ptr, g->n_total, dmax_dev, s);
-    parts.push_back({dmax_dev, 1});
-  }
+  if (rpat_dev) parts.push_back({rpat_dev, g->num_graphs + 1});
+  if (dmax_dev) parts.push_back({dmax_dev, 1});
   HIP_TRY(hipGetLastError());
   std::vector<int32_t> e;
   TRY(read_back_many(parts, e, s));
@@ -505,7 +521,8 @@ struct Solve {
   int64_t ls_iters = 0;
   int64_t search_alt = 0;  // pair iterations that applied a move, summed over the pass searches
   StepCfg step_cfg{0, 0};  // streaming plans: the step kernel's launch shape (of the first loop)
-  int32_t deferred_tile_wg = 0;  // > 0: the tile counters sit in the pinned buffer after the final sync
+  int32_t deferred_tile_wg = 0;  // > 0: the tile counters are read back with the solve's last synchronisation
+  bool trials = false;           // the tuner ran steps, whose counters the solve clears
   std::vector<int32_t> gorder;   // persistent plan: graphs in launch order (uploaded once, G > 1)
   std::vector<std::pair<hipEvent_t, hipEvent_t>> timed;  // around the step launches
   // MQO_TRACE: HIP events around every phase of the solve, on its stream
@@ -1359,7 +1376,7 @@ TileArgs tile_args(Solve &S, const TileCfg &c, const float *x0) {
   a.fl = at<int8_t>(S.ws, S.L.tfl);
   a.vm = at<float>(S.ws, S.L.tvm);
   a.ls_iters = at<int32_t>(S.ws, S.L.tls);
-  a.err = at<int32_t>(S.ws, S.L.err);
+  a.err = at<int32_t>(S.ws, S.L.tail) + 2;
   a.check_every = S.p->check_every;
   a.restart_every = S.p->restart_every;
   a.steps_done = at<int64_t>(S.ws, S.L.steps);
@@ -1454,6 +1471,7 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
   std::vector<TileCfg> cands = tile_candidates(S);
   std::reverse(cands.begin(), cands.end());
   if (cands.empty()) return fail(MQO_ERR_UNSUPPORTED, "no persistent tile shape fits these graphs");
+  S.trials = true;
   TileCfg best_c = cands[0];
   double best_t = 1e30;
   const int tsteps = std::max(1, std::min(S.p->steps_per_round, 64));
@@ -1519,10 +1537,13 @@ int solve_tile(Solve &S, int32_t *rounds_done, TileCfg *used) {
     x0 = X;
   }
   TileCfg cfg{};
+  S.trials = false;
   TRY(tune_tile(S, x0, &cfg));
   *used = cfg;
-  launch_fill_i64(at<int64_t>(S.ws, S.L.steps), (int64_t)S.G * S.B, 0, S.s);  // the tuner's trials counted too
-  launch_fill_i32(at<int32_t>(S.ws, S.L.err), 1, 0, S.s);
+  if (S.trials) {  // the tuner's steps counted too
+    launch_fill_i64(at<int64_t>(S.ws, S.L.steps), (int64_t)S.G * S.B, 0, S.s);
+    launch_fill_i32(at<int32_t>(S.ws, S.L.tail), TAIL_INTS, 0, S.s);
+  }
   TileArgs a = tile_args(S, cfg, x0);
   const bool mc = S.maxcut, w = S.g->weight != nullptr;
   if (cfg.sb >= TILE_ELL) {
@@ -1585,12 +1606,8 @@ int solve_tile(Solve &S, int32_t *rounds_done, TileCfg *used) {
     S.phase_end(PH_TILE, ph);
     TRY(S.end_timed(e0));
     r = a.r1;
-    if (r == S.p->rounds && r0_is_whole(a, S) && nwg < 1019) {
+    if (r == S.p->rounds && r0_is_whole(a, S) && nwg + TAIL_INTS <= 1024) {
       // the whole solve in one launch: read back with the final synchronisation
-      Resources &Rs = res();
-      HIP_TRY(hipMemcpyAsync(Rs.pinned, a.ls_iters, nwg * sizeof(int32_t), hipMemcpyDeviceToHost, S.s));
-      HIP_TRY(hipMemcpyAsync(Rs.pinned + nwg, at<int32_t>(S.ws, S.L.err), sizeof(int32_t), hipMemcpyDeviceToHost,
-                             S.s));
       S.deferred_tile_wg = nwg;
     } else {
       TRY(read_back_i32(a.ls_iters, nwg, lsi, S.s));
@@ -1629,27 +1646,37 @@ int solve_tile(Solve &S, int32_t *rounds_done, TileCfg *used) {
   }
   if (!S.deferred_tile_wg) {
     std::vector<int32_t> err;
-    TRY(read_back_i32(at<int32_t>(S.ws, S.L.err), 1, err, S.s));
+    TRY(read_back_i32(at<int32_t>(S.ws, S.L.tail) + 2, 1, err, S.s));
     if (err[0]) return fail(MQO_ERR_INTERNAL, "local search did not terminate");
   }
   *rounds_done = r;
   return MQO_OK;
 }
 
-// Consume the tile counters the persistent plan left in the pinned buffer
-// (after a synchronisation), before anything else reads back through it.
-int settle_deferred(Solve &S) {
-  if (!S.deferred_tile_wg) return MQO_OK;
+// The solve's tail words (edge updates, tile error) and, where the persistent
+// plan left them for later, its workgroups' counters: one copy and one
+// synchronisation.  edge_updates or nullptr (in the middle of a solve).  With
+// this, one copy after validation and fewer fills a small solve went from 22
+// launches and copies outside its steps to 13 (n = 100, one trajectory, 1000
+// steps: 613 -> 500 us).
+int read_tail(Solve &S, int64_t *edge_updates) {
+  int32_t *pin = res().pinned;
+  const int32_t wg = S.deferred_tile_wg;
+  HIP_TRY(hipMemcpyAsync(pin, at<int32_t>(S.ws, S.L.tail), (TAIL_INTS + wg) * sizeof(int32_t),
+                         hipMemcpyDeviceToHost, S.s));
   HIP_TRY(hipStreamSynchronize(S.s));
-  const int32_t *pin = res().pinned;
+  if (edge_updates) std::memcpy(edge_updates, pin, sizeof(int64_t));
+  if (!wg) return MQO_OK;
   int64_t mx = 0;
-  for (int32_t i = 0; i < S.deferred_tile_wg; ++i) mx = std::max<int64_t>(mx, pin[i]);
+  for (int32_t i = 0; i < wg; ++i) mx = std::max<int64_t>(mx, pin[TAIL_INTS + i]);
   S.ls_iters += mx;
-  const bool bad = pin[S.deferred_tile_wg] != 0;
   S.deferred_tile_wg = 0;
-  if (bad) return fail(MQO_ERR_INTERNAL, "local search did not terminate");
+  if (pin[2]) return fail(MQO_ERR_INTERNAL, "local search did not terminate");
   return MQO_OK;
 }
+
+// Consume the counters the persistent plan deferred, before a search adds its own.
+int settle_deferred(Solve &S) { return S.deferred_tile_wg ? read_tail(S, nullptr) : MQO_OK; }
 
 // Philox round index of the search closing the pass of the outer loop that
 // round r belongs to: rounds + the pass number
@@ -1944,6 +1971,7 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
   int plan = p->plan;
   if (plan == MQO_PLAN_AUTO) TRY(choose_plan(S, &plan));
   launch_fill_i64(at<int64_t>(ws, L.steps), (int64_t)S.G * S.B, 0, s);  // after the plan's trial rounds
+  launch_fill_i32(at<int32_t>(ws, L.tail), TAIL_INTS, 0, s);
   int32_t rounds_done = 0;
   TileCfg used{0, 0, 0, 0, 0, 0};
   if (plan == MQO_PLAN_PERSISTENT)
@@ -1971,16 +1999,13 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
   }
   // traj_best_value / traj_best_x, when given, held the incumbents all along
   // exact edge updates: sum over trajectories of executed steps x nnz of the graph
-  int64_t *eu_dev = at<int64_t>(ws, L.dmax);  // max degree is on the host already
-  launch_edge_updates(at<int64_t>(ws, L.steps), at<int32_t>(ws, L.rpat), S.G, S.B, eu_dev, s);
-  int64_t *eu_host = reinterpret_cast<int64_t *>(res().pinned + 1020);  // 8-byte aligned, after the tile counters
-  HIP_TRY(hipMemcpyAsync(eu_host, eu_dev, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+  launch_edge_updates(at<int64_t>(ws, L.steps), at<int32_t>(ws, L.rpat), S.G, S.B, at<int64_t>(ws, L.tail), s);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(s));
-  TRY(settle_deferred(S));
+  int64_t edge_updates = 0;
+  TRY(read_tail(S, &edge_updates));
   r->rounds_executed = rounds_done;
   r->steps_executed = (int64_t)rounds_done * p->steps_per_round;
-  r->edge_updates = *eu_host;
+  r->edge_updates = edge_updates;
   r->plan_used = plan;
   r->tile_cols_used = used.T;
   r->tile_threads_used = used.threads;

@@ -1973,32 +1973,38 @@ __global__ void k_copy_best_x(const int8_t *__restrict__ Zb, int32_t B, const in
   out[v] = Zb[v * B + best_b[lo]];
 }
 
-__global__ void k_gather_rowptr(const int32_t *__restrict__ row_ptr, const int64_t *__restrict__ voff, int32_t G,
-                                int32_t *__restrict__ out) {
-  const int32_t g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g <= G) out[g] = row_ptr[voff[g]];
-}
-
 // ---------------------------------------------------------------------------
-// graph validation (two phases: row_ptr first, then columns)
+// graph validation in one launch, a thread per row: the row_ptr entries (err[0])
+// and, for rows whose range is inside [0, nnz], so that no read leaves
+// col_idx, the columns (err[1]); with rpat also row_ptr at the graph
+// boundaries and the largest degree.  As five launches and three copies back
+// it was most of what a solve of a small graph spends outside its steps (see
+// the note at the solve's read-back).
 // ---------------------------------------------------------------------------
-__global__ void k_validate_rows(const int32_t *__restrict__ row_ptr, int64_t n, int64_t nnz, int32_t *err) {
+__global__ void k_validate_graph(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
+                                 const int32_t *__restrict__ weight, const int64_t *__restrict__ voff, int32_t G,
+                                 int64_t n, int64_t nnz, int32_t *err, int32_t *__restrict__ rpat,
+                                 int32_t *__restrict__ dmax) {
   const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v == 0 && (row_ptr[0] != 0 || (int64_t)row_ptr[n] != nnz)) atomicOr(err, 1);
+  if (rpat)
+    for (int64_t i = v; i <= G; i += (int64_t)gridDim.x * blockDim.x) rpat[i] = row_ptr[voff[i]];
+  int32_t beg = 0, end = 0;
   if (v < n) {
-    const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-    if (a > b || a < 0 || (int64_t)b > nnz) atomicOr(err, 1);
+    beg = row_ptr[v];
+    end = row_ptr[v + 1];
   }
-}
-
-// Runs in the same pass as k_validate_rows: rows whose row_ptr range is not
-// inside [0, nnz] are skipped here (k_validate_rows flags them), so no read
-// leaves col_idx.
-__global__ void k_validate_cols(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
-                                const int32_t *__restrict__ weight, const int64_t *__restrict__ voff, int32_t G,
-                                int64_t n, int64_t nnz, int32_t *err) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (dmax) {
+    int32_t d = end - beg;
+    for (int off = 32; off > 0; off >>= 1) d = max(d, __shfl_xor(d, off, 64));
+    if ((threadIdx.x & 63) == 0 && d > 0) atomicMax(dmax, d);
+  }
   if (v >= n) return;
+  if (beg > end || beg < 0 || (int64_t)end > nnz) {
+    atomicOr(err, 1);
+    return;
+  }
+  ++err;  // the column checks
   int32_t glo = 0, ghi = G;
   while (ghi - glo > 1) {
     const int32_t mid = (glo + ghi) >> 1;
@@ -2008,8 +2014,6 @@ __global__ void k_validate_cols(const int32_t *__restrict__ row_ptr, const int32
       ghi = mid;
   }
   const int64_t lo = voff[glo], hi = voff[glo + 1];
-  const int32_t beg = row_ptr[v], end = row_ptr[v + 1];
-  if (beg < 0 || beg > end || (int64_t)end > nnz) return;
   int64_t prev = -1;
   for (int32_t j = beg; j < end; ++j) {
     const int64_t c = col_idx[j];
@@ -2576,11 +2580,6 @@ void launch_init_uniform(bool maxcut, float *X, int64_t lo, int64_t n, int32_t n
                start);
 }
 
-void launch_degree_max(const int32_t *row_ptr, int64_t n, int32_t *out, hipStream_t s) {
-  MQO_LAUNCH(k_fill_i32, dim3(1), dim3(64), 0, s, out, (int64_t)1, 0);
-  MQO_LAUNCH(k_degree_max, dim3(blocks_for(n < 262144 ? n : 262144)), dim3(256), 0, s, row_ptr, (int64_t)0, n, out);
-}
-
 void launch_init_degree(bool maxcut, float *X, const int32_t *row_ptr, int32_t *dmax_scratch, int64_t lo, int64_t n,
                         int32_t ncols, int32_t ld, uint64_t seed, uint64_t traj0, float sigma, hipStream_t s,
                         uint64_t start) {
@@ -2720,7 +2719,7 @@ __global__ void k_add_i64(int64_t *p, int64_t count, int64_t v) {
 }
 
 // out += sum over trajectories t = g*B + b of steps[t] * nnz_g, nnz_g from
-// the row_ptr entries at the graph boundaries (rpat[G+1]); out zeroed first
+// the row_ptr entries at the graph boundaries (rpat[G+1])
 __global__ void k_edge_updates(const int64_t *__restrict__ steps, const int32_t *__restrict__ rpat, int32_t G,
                                int32_t B, unsigned long long *out) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2743,7 +2742,6 @@ void launch_add_i64(int64_t *p, int64_t count, int64_t v, hipStream_t s) {
 
 void launch_edge_updates(const int64_t *steps, const int32_t *rpat, int32_t G, int32_t B, int64_t *out,
                          hipStream_t s) {
-  launch_fill_i64(out, 1, 0, s);
   MQO_LAUNCH(k_edge_updates, dim3(blocks_for((int64_t)G * B)), dim3(256), 0, s, steps, rpat, G, B,
              reinterpret_cast<unsigned long long *>(out));
 }
@@ -3052,14 +3050,6 @@ void launch_copy_best_x(const int8_t *Zb, int32_t B, const int64_t *voff, int32_
   MQO_LAUNCH(k_copy_best_x, dim3(blocks_for(n_total)), dim3(256), 0, s, Zb, B, voff, G, best_b, out, n_total);
 }
 
-void launch_gather_rowptr(const int32_t *row_ptr, const int64_t *voff, int32_t G, int32_t *out, hipStream_t s) {
-  MQO_LAUNCH(k_gather_rowptr, dim3(blocks_for(G + 1)), dim3(256), 0, s, row_ptr, voff, G, out);
-}
-
-void launch_validate_rows(const int32_t *row_ptr, int64_t n, int64_t nnz, int32_t *err, hipStream_t s) {
-  MQO_LAUNCH(k_validate_rows, dim3(blocks_for(n)), dim3(256), 0, s, row_ptr, n, nnz, err);
-}
-
 // hub list of one graph: each entry a row of [lo, lo + n) with degree >
 // min_deg, strictly ascending (err |= 64 otherwise)
 __global__ void k_validate_hubs(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ hubs, int64_t count,
@@ -3088,9 +3078,11 @@ void launch_count_hubs(const int32_t *row_ptr, int64_t n, int32_t min_deg, int32
   MQO_LAUNCH(k_count_hubs, dim3(blocks_for(n)), dim3(256), 0, s, row_ptr, n, min_deg, count);
 }
 
-void launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx, const int32_t *weight, const int64_t *voff,
-                          int32_t G, int64_t n, int64_t nnz, int32_t *err, hipStream_t s) {
-  MQO_LAUNCH(k_validate_cols, dim3(blocks_for(n)), dim3(256), 0, s, row_ptr, col_idx, weight, voff, G, n, nnz, err);
+void launch_validate_graph(const int32_t *row_ptr, const int32_t *col_idx, const int32_t *weight,
+                           const int64_t *voff, int32_t G, int64_t n, int64_t nnz, int32_t *err, int32_t *rpat,
+                           int32_t *dmax, hipStream_t s) {
+  MQO_LAUNCH(k_validate_graph, dim3(blocks_for(n)), dim3(256), 0, s, row_ptr, col_idx, weight, voff, G, n, nnz, err,
+             rpat, dmax);
 }
 
 int64_t grid_blocks_x(int64_t nrows, StepCfg cfg) { return grid_rows(nrows, 1, cfg.lanes_log2, 1, 256).x; }

@@ -27,7 +27,6 @@ void launch_init_uniform(bool maxcut, float *X, int64_t lo, int64_t n, int32_t n
 void launch_init_degree(bool maxcut, float *X, const int32_t *row_ptr, int32_t *dmax_scratch, int64_t lo, int64_t n,
                         int32_t ncols, int32_t ld, uint64_t seed, uint64_t traj0, float sigma, hipStream_t s,
                         uint64_t start = 0);
-void launch_degree_max(const int32_t *row_ptr, int64_t n, int32_t *out, hipStream_t s);
 // form: OBJ_H / OBJ_FB / OBJ_FL / OBJ_FP / OBJ_FA (common.h).
 // colact: per-column active flags (0 = stopped for the round: copied
 // through), or nullptr for all active
@@ -36,7 +35,7 @@ void launch_pga_step(int form, const GraphView &g, const float *X, float *Xn, fl
 void launch_active_update(int8_t *colact, const int8_t *fixed, int32_t ncols, hipStream_t s);
 void launch_fill_i8(int8_t *p, int64_t count, int8_t v, hipStream_t s);
 void launch_add_i64(int64_t *p, int64_t count, int64_t v, hipStream_t s);
-// *out = sum_t steps[t] * nnz of t's graph (rpat: row_ptr at the G+1 graph boundaries)
+// *out += sum_t steps[t] * nnz of t's graph (rpat: row_ptr at the G+1 graph boundaries)
 void launch_edge_updates(const int64_t *steps, const int32_t *rpat, int32_t G, int32_t B, int64_t *out,
                          hipStream_t s);
 void launch_count_steps(const int8_t *colact, int64_t *steps, int32_t ncols, int32_t len, hipStream_t s);
@@ -113,14 +112,14 @@ void launch_strided_copy_i8(const int8_t *src, int32_t lds, int32_t cs, int8_t *
 void launch_pick_best(const int64_t *best, int32_t G, int32_t B, int64_t *best_value, int32_t *best_b, hipStream_t s);
 void launch_copy_best_x(const int8_t *Zb, int32_t B, const int64_t *voff, int32_t G, const int32_t *best_b,
                         int8_t *out, int64_t n_total, hipStream_t s);
-void launch_gather_rowptr(const int32_t *row_ptr, const int64_t *voff, int32_t G, int32_t *out, hipStream_t s);
-void launch_validate_rows(const int32_t *row_ptr, int64_t n, int64_t nnz, int32_t *err, hipStream_t s);
 void launch_validate_hubs(const int32_t *row_ptr, const int32_t *hubs, int64_t count, int64_t lo, int64_t n,
                           int32_t min_deg, int32_t *err, hipStream_t s);
 void launch_count_hubs(const int32_t *row_ptr, int64_t n, int32_t min_deg, int32_t *count, hipStream_t s);
-// safe to run in the same pass as the row check (skips rows with a bad range)
-void launch_validate_cols(const int32_t *row_ptr, const int32_t *col_idx, const int32_t *weight, const int64_t *voff,
-                          int32_t G, int64_t n, int64_t nnz, int32_t *err, hipStream_t s);
+// err[0]: row_ptr, err[1]: columns (both cleared by the caller); rpat (G + 1)
+// and dmax (cleared) or nullptr
+void launch_validate_graph(const int32_t *row_ptr, const int32_t *col_idx, const int32_t *weight,
+                           const int64_t *voff, int32_t G, int64_t n, int64_t nnz, int32_t *err, int32_t *rpat,
+                           int32_t *dmax, hipStream_t s);
 void launch_objective_grad(int form, const GraphView &g, const float *X, const float *scale, float *grad,
                            double *part, int32_t ncols, int32_t ld, StepCfg cfg, float param, hipStream_t s);
 // Consecutive graphs of a batch in one launch (passed by value, so that a
