@@ -1812,6 +1812,9 @@ int trial_plan_ms(Solve &S, int plan, double *ms) {
   int st = hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess ? MQO_OK
                                                                                    : fail(MQO_ERR_HIP, "event create");
   if (st == MQO_OK) {
+    // the caller's workspace comes as it is, and the trial reads the tile
+    // kernel's error word back
+    launch_fill_i32(at<int32_t>(S.ws, S.L.tail), TAIL_INTS, 0, S.s);
     (void)hipEventRecord(e0, S.s);
     int32_t rounds_done = 0;
     TileCfg used{};
