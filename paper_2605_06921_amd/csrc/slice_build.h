@@ -198,9 +198,14 @@ __global__ __launch_bounds__(256) void k_ell_slots(const int32_t *__restrict__ r
 // Measured on the batch of 128 ER graphs of 700-800 vertices, p = 0.15, 512
 // trajectories, 4 rounds: 224 -> 212 ms (222 without the pairing).
 // ---------------------------------------------------------------------------
-constexpr int WIDE_BITS = 8;         // 32-bit words of a row's parities that are compared
-constexpr int WIDE_MAX_ROWS = 2048;  // 8 items x 1024 threads x 4 trajectories / 16
-constexpr int WIDE_MAX_SLICES = 128;
+constexpr int WIDE_BITS = 8;           // 32-bit words of a row's parities that are compared
+constexpr int WIDE_MAX_ELEMS = 32768;  // rows x trajectories of a tile: 8 lane items of 4 in 1024 threads
+constexpr int WIDE_PAIR_LOG2T = 5;     // the width whose rows are paired
+// the largest graph of a width; the arrays of k_wide_build and the step loop's
+// slice table are sized by it, and the host offers no larger one
+__host__ __device__ constexpr int32_t wide_max_rows(int32_t log2T) { return WIDE_MAX_ELEMS >> log2T; }
+constexpr int WIDE_MAX_ROWS = wide_max_rows(4);
+constexpr int WIDE_MAX_SLICES = WIDE_MAX_ELEMS / 256;
 
 __host__ __device__ inline int32_t wide_rows(int32_t log2T) { return 256 >> log2T; }
 __host__ __device__ inline int64_t wide_slice_base(int64_t lo, int64_t g) { return (lo >> 2) + 2 * g; }  // R >= 4
@@ -262,7 +267,7 @@ __global__ __launch_bounds__(1024) void k_wide_build(const int32_t *__restrict__
                                                      const int64_t *__restrict__ vtx_off, int32_t log2T, int32_t zrow,
                                                      uint16_t *__restrict__ ord, int2 *__restrict__ slices,
                                                      uint4 *__restrict__ blocks) {
-  __shared__ uint32_t bits[1024 * WIDE_BITS];  // T = 32: at most 1024 rows
+  __shared__ uint32_t bits[wide_max_rows(WIDE_PAIR_LOG2T) * WIDE_BITS];  // used at that width alone
   __shared__ uint16_t so[WIDE_MAX_ROWS], sp[WIDE_MAX_ROWS];
   __shared__ int2 ss[WIDE_MAX_SLICES];
   const int32_t g = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
@@ -274,9 +279,8 @@ __global__ __launch_bounds__(1024) void k_wide_build(const int32_t *__restrict__
     so[i] = ord[lo + i];
     sp[i] = so[i];
   }
-  for (int32_t i = tid; i < n * WIDE_BITS; i += nthr) bits[i] = 0u;
   __syncthreads();
-  if (log2T == 5) {
+  if (log2T == WIDE_PAIR_LOG2T) {
     for (int32_t i = tid; i < n * WIDE_BITS; i += nthr) {
       const int32_t v = i / WIDE_BITS, w = i % WIDE_BITS;
       const int32_t j0 = rp[v] + 32 * w, j1 = min(rp[v + 1], j0 + 32);

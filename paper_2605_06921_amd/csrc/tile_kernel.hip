@@ -34,6 +34,7 @@ namespace mqo {
 
 constexpr int TILE_MAX_T = 64;
 constexpr int SB_ITEMS = 8;  // lane items per thread of a single-buffered step
+static_assert(WIDE_MAX_ELEMS == SB_ITEMS * 4 * 1024, "the wide slices' arrays hold what a workgroup steps");
 
 template <int VEC>
 __device__ __forceinline__ void lds_load(const float *p, float (&o)[VEC]) {
@@ -1223,7 +1224,7 @@ bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int
   // sliced adjacency: one lane per row, entries of 16 bits
   if (sb == TILE_ELL)
     return dreg == 0 && !csr_lds && vec == T && n_max <= ELL_MAX_ROWS && tile_rows(n_max, true) * 4 * T <= 65536;
-  if (sb == TILE_WIDE && !(dreg == 0 && !csr_lds && vec == 4 && T >= 16)) return false;
+  if (sb == TILE_WIDE && !(dreg == 0 && !csr_lds && vec == 4 && T >= 16 && n_max * T <= WIDE_MAX_ELEMS)) return false;
   // single buffer: every lane item of a step held in registers at once
   // (the lanes' rows in whole wavefronts)
   if (sb) {
