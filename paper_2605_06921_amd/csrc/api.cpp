@@ -1386,12 +1386,17 @@ TileArgs tile_args(Solve &S, const TileCfg &c, const float *x0) {
   return a;
 }
 
+// Version of the persistent shapes' times, part of the tile and plan keys.
+// Entries without it may hold a time of wide slices whose rows were all row 0
+// (16 trajectories, graphs above 1152 rows): those shapes looked too fast.
+constexpr int TILE_KEY_VERSION = 2;
+
 std::string tile_key(const Solve &S) {
   char buf[256];
   const double deg = (double)S.g->nnz_total / (double)S.g->n_total;
-  snprintf(buf, sizeof(buf), "%d|%d|%d|%lld|%d|%d|%d|%d", (int)S.maxcut, S.g->weight != nullptr,
-           S.p->momentum != 0.0f, (long long)S.n_max, (int)std::lround(std::log2(deg + 1.0) * 4), S.B, S.G,
-           S.p->local_search);
+  snprintf(buf, sizeof(buf), "v%d|%d|%d|%d|%lld|%d|%d|%d|%d", TILE_KEY_VERSION, (int)S.maxcut,
+           S.g->weight != nullptr, S.p->momentum != 0.0f, (long long)S.n_max,
+           (int)std::lround(std::log2(deg + 1.0) * 4), S.B, S.G, S.p->local_search);
   return buf;
 }
 
