@@ -2310,8 +2310,8 @@ int mqo_pga_unrolled_backward(const mqo_graph *g, mqo_objective obj, float param
   const int64_t nb = g->n_total * B;
   const size_t slot = align_up((size_t)nb * sizeof(float));
   char *base = reinterpret_cast<char *>(ws);
-  // slots: the kept gradients of a segment's steps, two for its states and,
-  // after them, for mu, and lam
+  // slots: the kept gradients of a segment's steps but the last, one unused,
+  // two for its states and, after them, for mu, and lam
   const int32_t c = ckpt_every;
   auto at_slot = [&](int32_t i) { return reinterpret_cast<float *>(base + slot * i); };
   float *lam = at_slot(c + 2);
@@ -2323,16 +2323,16 @@ int mqo_pga_unrolled_backward(const mqo_graph *g, mqo_objective obj, float param
     launch_fill_i64(reinterpret_cast<int64_t *>(dL_dalpha + (int64_t)gi * B), B, 0, s);  // +0.0
     for (int32_t j = nseg - 1; j >= 0; --j) {
       const float *x = ckpt + (int64_t)j * nb;
-      for (int32_t i = 0; i < c; ++i) {
-        float *xn = i + 1 < c ? at_slot(c + (i & 1)) : nullptr;
+      for (int32_t i = 0; i + 1 < c; ++i) {
+        float *xn = at_slot(c + (i & 1));
         launch_adjoint_grad(form, gv, x, xn, at_slot(i), B, B, cfg, alpha, param, s);
         x = xn;
       }
       // the segment's steps write consecutive partial slabs of nblk rows,
       // summed in one fixed-order reduction per segment
       const float *top = j == nseg - 1 ? dL_dXK : lam;
-      float *mu = at_slot(c), *next = at_slot(c + 1);
-      launch_adjoint_mask(gv, top, at_slot(c - 1), mu, part, B, B, cfg, s);
+      float *mu = at_slot(c + ((c - 1) & 1)), *next = at_slot(c + (c & 1));  // x lies in `next`
+      launch_adjoint_top(form, gv, x, top, mu, part, B, B, cfg, alpha, param, s);
       for (int32_t i = c - 1; i >= 0; --i) {
         const float *kept = i > 0 ? at_slot(i - 1) : nullptr;
         float *out = i > 0 ? next : j > 0 ? lam : dL_dX0;

@@ -387,30 +387,23 @@ __device__ __forceinline__ bool is_hub_row(const GraphView &g, int64_t v) {
 // neighbour sums and their weight sums W_v.  Every lane of the group must call it.  ROWS = 2 is
 // launched for near-regular graphs only: two rows of equal degree go in
 // lockstep, otherwise one after the other.
-template <int VEC, int ROWS>
-__device__ __forceinline__ void group_rows(const GraphView &g, int64_t bx, int32_t by, int32_t lanes_log2,
-                                           int64_t (&v)[ROWS], bool (&own)[ROWS], int32_t &col) {
-  const int32_t lanes = 1 << lanes_log2;
-  const int32_t rpb = blockDim.x >> lanes_log2;
-  const int64_t r0 = bx * ROWS * rpb + (threadIdx.x >> lanes_log2);
-  col = (int32_t)(by * lanes + (threadIdx.x & (lanes - 1))) * VEC;
-#pragma unroll
-  for (int k = 0; k < ROWS; ++k) {
-    const int64_t r = r0 + (int64_t)k * rpb;
-    v[k] = g.lo + r;
-    own[k] = r < g.n && !is_hub_row(g, v[k]);
-  }
-}
-
 template <int VEC, bool WEIGHTED, int ROWS, int KB = 4>
 __device__ __forceinline__ void group_gather(const GraphView &g, const float *__restrict__ X, int64_t bx, int32_t by,
                                              int32_t ncols, int32_t ld, int32_t lanes_log2, int64_t (&v)[ROWS],
                                              bool (&own)[ROWS], int32_t &col, float (&acc)[ROWS][VEC],
                                              int32_t (&wsum)[ROWS]) {
-  group_rows<VEC, ROWS>(g, bx, by, lanes_log2, v, own, col);
+  const int32_t lanes = 1 << lanes_log2;
+  const int32_t rpb = blockDim.x >> lanes_log2;
+  const int64_t r0 = bx * ROWS * rpb + (threadIdx.x >> lanes_log2);
+  col = (int32_t)(by * lanes + (threadIdx.x & (lanes - 1))) * VEC;
   const bool colok = col < ncols;
 #pragma unroll
-  for (int k = 0; k < ROWS; ++k) wsum[k] = 0;
+  for (int k = 0; k < ROWS; ++k) {
+    const int64_t r = r0 + (int64_t)k * rpb;
+    v[k] = g.lo + r;
+    own[k] = r < g.n && !is_hub_row(g, v[k]);
+    wsum[k] = 0;
+  }
   if constexpr (ROWS == 2) {
     if (own[0] && own[1] &&
         g.row_ptr[v[0] + 1] - g.row_ptr[v[0]] == g.row_ptr[v[1] + 1] - g.row_ptr[v[1]]) {
@@ -2345,7 +2338,8 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double *__restric
 }
 
 // The adjoint of a segment of steps.  Going forward through it again, every
-// step keeps its gradient with the clip mask in it (k_adj_grad); going
+// step but the last keeps its gradient with the clip mask in it, and the last
+// gives its mu, since its lam is known (k_adj_grad); going
 // backward, mu_k = mask_k lam_{k+1} and lam_k = mu_k + alpha (H mu_k), and one
 // sparse product gives lam_k, mu_{k-1} and the partials of <mu_{k-1},
 // g_{k-1}> for dL/dalpha together (k_adj_lambda).  That is two sparse products
@@ -2379,23 +2373,35 @@ __device__ __forceinline__ void adjoint_mu(float ln, float kept, float &mu, doub
   dv = clipped ? (b == CLIPPED ? 0.0 : (double)kept) : (double)ln * (double)kept;
 }
 
-// x_{k+1} into Xn (unless nullptr) and the kept gradient of step k into GK
-template <int VEC, int OBJ, bool WEIGHTED, int ROWS, int KB = 4>
+// TOP false: x_{k+1} into Xn and the kept gradient of step k into out.  TOP
+// true (a segment's last step, whose lam_{k+1} is known): mu_k into out, with
+// its partials.
+template <int VEC, int OBJ, bool WEIGHTED, int ROWS, int KB, bool TOP>
 __global__ __launch_bounds__(256) void k_adj_grad(GraphView g, const float *__restrict__ Xk, float *__restrict__ Xn,
-                                                  float *__restrict__ GK, int32_t ncols, int32_t ld,
+                                                  const float *__restrict__ lam, float *__restrict__ out,
+                                                  double *__restrict__ part, int32_t ncols, int32_t ld,
                                                   int32_t lanes_log2, float alpha, float param) {
   const int64_t nhb = hub_blocks(g, ncols);
+  const int64_t nrb = gridDim.x - nhb;
   const Blk blk = xcd_blk(g.xcd_local);
   if (blk.x < nhb) {
     if (blk.y != 0) return;
     const HubItem it = hub_item(g, ncols, blk.x);
     const float acc = hub_gather<WEIGHTED>(g, Xk, it, ld);
     if ((int32_t)threadIdx.x < it.cw) {
-      const int64_t e = it.v * ld + it.c0 + threadIdx.x;
+      const int32_t c = it.c0 + threadIdx.x;
+      const int64_t e = it.v * ld + c;
       const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? weighted_degree<WEIGHTED>(g, it.v) : 0.0f;
       float xn;
-      GK[e] = adjoint_grad<OBJ>(Xk[e], acc, W, alpha, param, xn);
-      if (Xn) Xn[e] = xn;
+      float o = adjoint_grad<OBJ>(Xk[e], acc, W, alpha, param, xn);
+      if constexpr (TOP) {
+        double dv;
+        adjoint_mu(lam[e], o, o, dv);
+        part[(nrb + it.h) * ncols + c] = dv;
+      } else {
+        Xn[e] = xn;
+      }
+      out[e] = o;
     }
     return;
   }
@@ -2405,49 +2411,6 @@ __global__ __launch_bounds__(256) void k_adj_grad(GraphView g, const float *__re
   float acc[ROWS][VEC];
   int32_t wsum[ROWS];
   group_gather<VEC, WEIGHTED, ROWS, KB>(g, Xk, blk.x - nhb, blk.y, ncols, ld, lanes_log2, v, own, col, acc, wsum);
-  if (col >= ncols) return;
-#pragma unroll
-  for (int k = 0; k < ROWS; ++k) {
-    if (!own[k]) continue;
-    float x[VEC], xn[VEC], kept[VEC];
-    load_vec<VEC>(Xk + v[k] * ld + col, x);
-    const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? (float)wsum[k] : 0.0f;
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) kept[i] = adjoint_grad<OBJ>(x[i], acc[k][i], W, alpha, param, xn[i]);
-    store_vec<VEC>(GK + v[k] * ld + col, kept);
-    if (Xn) store_vec<VEC>(Xn + v[k] * ld + col, xn);
-  }
-}
-
-// mu_k from lam_{k+1} at the top of a segment, where the sparse product that
-// gave lam ran before the segment's gradients were known; the rows and their
-// partials lie as in the sparse products
-template <int VEC, int ROWS>
-__global__ __launch_bounds__(256) void k_adj_mask(GraphView g, const float *__restrict__ lam,
-                                                  const float *__restrict__ GK, float *__restrict__ mu_out,
-                                                  double *__restrict__ part, int32_t ncols, int32_t ld,
-                                                  int32_t lanes_log2) {
-  const int64_t nhb = hub_blocks(g, ncols);
-  const int64_t nrb = gridDim.x - nhb;
-  const Blk blk = xcd_blk(g.xcd_local);
-  if (blk.x < nhb) {
-    if (blk.y != 0) return;
-    const HubItem it = hub_item(g, ncols, blk.x);
-    if ((int32_t)threadIdx.x < it.cw) {
-      const int32_t c = it.c0 + threadIdx.x;
-      const int64_t e = it.v * ld + c;
-      float mu;
-      double dv;
-      adjoint_mu(lam[e], GK[e], mu, dv);
-      mu_out[e] = mu;
-      part[(nrb + it.h) * ncols + c] = dv;
-    }
-    return;
-  }
-  int64_t v[ROWS];
-  bool own[ROWS];
-  int32_t col;
-  group_rows<VEC, ROWS>(g, blk.x - nhb, blk.y, lanes_log2, v, own, col);
   double dv[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) dv[i] = 0.0;
@@ -2456,18 +2419,26 @@ __global__ __launch_bounds__(256) void k_adj_mask(GraphView g, const float *__re
   for (int k = 0; k < ROWS; ++k) {
     if (!own[k] || col >= ncols) continue;
     any = true;
-    float ln[VEC], kept[VEC], mu[VEC];
-    load_vec<VEC>(lam + v[k] * ld + col, ln);
-    load_vec<VEC>(GK + v[k] * ld + col, kept);
+    float x[VEC], xn[VEC], o[VEC];
+    load_vec<VEC>(Xk + v[k] * ld + col, x);
+    const float W = OBJ == OBJ_FL || OBJ == OBJ_FP ? (float)wsum[k] : 0.0f;
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) {
-      double d;
-      adjoint_mu(ln[i], kept[i], mu[i], d);
-      dv[i] += d;
+    for (int i = 0; i < VEC; ++i) o[i] = adjoint_grad<OBJ>(x[i], acc[k][i], W, alpha, param, xn[i]);
+    if constexpr (TOP) {
+      float ln[VEC];
+      load_vec<VEC>(lam + v[k] * ld + col, ln);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        double d;
+        adjoint_mu(ln[i], o[i], o[i], d);
+        dv[i] += d;
+      }
+    } else {
+      store_vec<VEC>(Xn + v[k] * ld + col, xn);
     }
-    store_vec<VEC>(mu_out + v[k] * ld + col, mu);
+    store_vec<VEC>(out + v[k] * ld + col, o);
   }
-  block_column_partials<VEC>(dv, any, col, ncols, lanes_log2, part, blk.x - nhb);
+  if constexpr (TOP) block_column_partials<VEC>(dv, any, col, ncols, lanes_log2, part, blk.x - nhb);
 }
 
 // lam_k = mu_k + alpha (H mu_k), H the objective's Hessian:
@@ -3216,20 +3187,22 @@ void launch_reduce_partials(double *part, int64_t nblk, int32_t ncols, double *o
   MQO_LAUNCH(k_reduce_partials, dim3(cx, 1), dim3(256), 0, s, src, rows, ncols, wlog2, rows, out, (int32_t)accumulate);
 }
 
-template <int VEC>
+template <int VEC, bool TOP>
 struct AdjGradLaunch {
   template <int OBJ, bool W>
-  static void run(const GraphView &g, const float *Xk, float *Xn, float *GK, int32_t ncols, int32_t ld, int ll,
-                  float alpha, float param, hipStream_t s) {
+  static void run(const GraphView &g, const float *Xk, float *Xn, const float *lam, float *out, double *part,
+                  int32_t ncols, int32_t ld, int ll, float alpha, float param, hipStream_t s) {
     const dim3 grid = spmm_grid(g, ncols, ll, VEC);
-    const size_t lds = g.nhub ? hub_lds(W) : 0;
+    const size_t lds = std::max(g.nhub ? hub_lds(W) : 0, TOP ? PARTIAL_LDS(VEC) : 0);
     if (spmm_rows(g, ll) == 2)
-      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 2>), grid, dim3(256), lds, s, g, Xk, Xn, GK, ncols, ld, ll, alpha, param);
+      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 2, 4, TOP>), grid, dim3(256), lds, s, g, Xk, Xn, lam, out, part, ncols, ld,
+                 ll, alpha, param);
     else if (g.nhub > 0)  // uneven degrees: eight gathers in flight per lane group
-      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 1, 8>), grid, dim3(256), lds, s, g, Xk, Xn, GK, ncols, ld, ll, alpha,
-                 param);
+      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 1, 8, TOP>), grid, dim3(256), lds, s, g, Xk, Xn, lam, out, part, ncols, ld,
+                 ll, alpha, param);
     else
-      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 1>), grid, dim3(256), lds, s, g, Xk, Xn, GK, ncols, ld, ll, alpha, param);
+      MQO_LAUNCH((k_adj_grad<VEC, OBJ, W, 1, 4, TOP>), grid, dim3(256), lds, s, g, Xk, Xn, lam, out, part, ncols, ld,
+                 ll, alpha, param);
   }
 };
 
@@ -3252,16 +3225,28 @@ struct AdjLambdaLaunch {
   }
 };
 
-void launch_adjoint_grad(int form, const GraphView &g, const float *Xk, float *Xn, float *GK, int32_t ncols,
-                         int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s) {
+template <bool TOP>
+static void adjoint_grad_any(int form, const GraphView &g, const float *Xk, float *Xn, const float *lam, float *out,
+                             double *part, int32_t ncols, int32_t ld, StepCfg cfg, float alpha, float param,
+                             hipStream_t s) {
   const bool w = g.weight != nullptr;
   const int ll = cfg.lanes_log2;
   if (cfg.vec == 4)
-    dispatch_form<AdjGradLaunch<4>>(form, w, g, Xk, Xn, GK, ncols, ld, ll, alpha, param, s);
+    dispatch_form<AdjGradLaunch<4, TOP>>(form, w, g, Xk, Xn, lam, out, part, ncols, ld, ll, alpha, param, s);
   else if (cfg.vec == 2)
-    dispatch_form<AdjGradLaunch<2>>(form, w, g, Xk, Xn, GK, ncols, ld, ll, alpha, param, s);
+    dispatch_form<AdjGradLaunch<2, TOP>>(form, w, g, Xk, Xn, lam, out, part, ncols, ld, ll, alpha, param, s);
   else
-    dispatch_form<AdjGradLaunch<1>>(form, w, g, Xk, Xn, GK, ncols, ld, ll, alpha, param, s);
+    dispatch_form<AdjGradLaunch<1, TOP>>(form, w, g, Xk, Xn, lam, out, part, ncols, ld, ll, alpha, param, s);
+}
+
+void launch_adjoint_grad(int form, const GraphView &g, const float *Xk, float *Xn, float *GK, int32_t ncols,
+                         int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s) {
+  adjoint_grad_any<false>(form, g, Xk, Xn, nullptr, GK, nullptr, ncols, ld, cfg, alpha, param, s);
+}
+
+void launch_adjoint_top(int form, const GraphView &g, const float *Xk, const float *lam, float *mu, double *part,
+                        int32_t ncols, int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s) {
+  adjoint_grad_any<true>(form, g, Xk, nullptr, lam, mu, part, ncols, ld, cfg, alpha, param, s);
 }
 
 void launch_adjoint_lambda(int form, const GraphView &g, const float *mu, const float *GK, float *out, double *part,
@@ -3274,26 +3259,6 @@ void launch_adjoint_lambda(int form, const GraphView &g, const float *mu, const 
     dispatch_form<AdjLambdaLaunch<2>>(form, w, g, mu, GK, out, part, ncols, ld, ll, alpha, param, s);
   else
     dispatch_form<AdjLambdaLaunch<1>>(form, w, g, mu, GK, out, part, ncols, ld, ll, alpha, param, s);
-}
-
-void launch_adjoint_mask(const GraphView &g, const float *lam, const float *GK, float *mu, double *part,
-                         int32_t ncols, int32_t ld, StepCfg cfg, hipStream_t s) {
-  const int ll = cfg.lanes_log2;
-  const dim3 grid = spmm_grid(g, ncols, ll, cfg.vec);
-  const bool pairs = spmm_rows(g, ll) == 2;
-#define MQO_MASK(VV)                                                                                            \
-  if (pairs)                                                                                                    \
-    MQO_LAUNCH((k_adj_mask<VV, 2>), grid, dim3(256), PARTIAL_LDS(VV), s, g, lam, GK, mu, part, ncols, ld, ll);  \
-  else                                                                                                          \
-    MQO_LAUNCH((k_adj_mask<VV, 1>), grid, dim3(256), PARTIAL_LDS(VV), s, g, lam, GK, mu, part, ncols, ld, ll);
-  if (cfg.vec == 4) {
-    MQO_MASK(4)
-  } else if (cfg.vec == 2) {
-    MQO_MASK(2)
-  } else {
-    MQO_MASK(1)
-  }
-#undef MQO_MASK
 }
 
 }  // namespace mqo

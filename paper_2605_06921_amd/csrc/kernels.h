@@ -154,14 +154,14 @@ void launch_scale_rows(const GraphTable &t, const double *scale, const float *gr
 // rows (the reduction's intermediate levels)
 inline int64_t reduce_rows(int64_t nblk) { return nblk / 7 + 64; }
 void launch_reduce_partials(double *part, int64_t nblk, int32_t ncols, double *out, bool accumulate, hipStream_t s);
-// One step of a segment gone through again: x_{k+1} into Xn (unless nullptr)
-// and its gradient, with the clip mask in it, into GK
+// One step of a segment gone through again: x_{k+1} into Xn and its gradient,
+// with the clip mask in it, into GK
 void launch_adjoint_grad(int form, const GraphView &g, const float *Xk, float *Xn, float *GK, int32_t ncols,
                          int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s);
-// mu_k from lam_{k+1} and the kept gradient of step k, with the partials of
-// <mu_k, g_k> (rows as in launch_objective_grad)
-void launch_adjoint_mask(const GraphView &g, const float *lam, const float *GK, float *mu, double *part,
-                         int32_t ncols, int32_t ld, StepCfg cfg, hipStream_t s);
+// The segment's last step: mu_k from lam_{k+1}, with the partials of <mu_k,
+// g_k> (rows as in launch_objective_grad)
+void launch_adjoint_top(int form, const GraphView &g, const float *Xk, const float *lam, float *mu, double *part,
+                        int32_t ncols, int32_t ld, StepCfg cfg, float alpha, float param, hipStream_t s);
 // lam_k = mu_k + alpha H mu_k, as mu_{k-1} with its partials where the kept
 // gradient GK of step k - 1 is given
 void launch_adjoint_lambda(int form, const GraphView &g, const float *mu, const float *GK, float *out, double *part,
