@@ -1444,6 +1444,36 @@ std::vector<TileCfg> tile_candidates(const Solve &S) {
   return out;
 }
 
+// a tuned shape as the cache holds it, and its time per step
+struct TunedTile {
+  TileCfg c{};
+  double ms = 1e30;
+};
+
+std::string tuned_text(const TunedTile &t) {
+  char val[128];
+  snprintf(val, sizeof(val), "%d %d %d %d %d %d %d %.6f", t.c.T, t.c.threads, t.c.vec, t.c.csr, t.c.dreg, t.c.ipt,
+           t.c.sb, t.ms);
+  return val;
+}
+
+bool parse_tuned(const Solve &S, const char *text, TunedTile *t) {
+  TileCfg &c = t->c;
+  return std::sscanf(text, "%d %d %d %d %d %d %d %lf", &c.T, &c.threads, &c.vec, &c.csr, &c.dreg, &c.ipt, &c.sb,
+                     &t->ms) == 8 &&
+         tile_feasible(S, c) && (c.dreg == 0 || c.dreg >= S.max_deg);
+}
+
+// The shape this solve takes: the fastest per step, unless that is a sliced
+// one whose build every solve pays for and the steps do not earn it back
+// against the best shape without one (early exit makes fewer steps of them).
+// The builds take 11 + 65 us for one graph of 3000 rows, 730 us for a star of
+// 2000, 490 us for 128 graphs of 800 rows at 32 trajectories.
+const TunedTile &for_this_solve(const Solve &S, const TunedTile &fastest, double build_ms, const TunedTile &plain) {
+  const double steps = (double)S.p->rounds * S.p->steps_per_round;
+  return fastest.ms * steps + build_ms <= plain.ms * steps ? fastest : plain;
+}
+
 // Time one round of up to 64 steps per candidate; keep the fastest.  Every
 // candidate computes bit-identical results, so this only affects speed.
 // ms_per_step (or nullptr): the chosen shape's time per PGA step.
@@ -1458,19 +1488,30 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
   char fixed[64];
   snprintf(fixed, sizeof(fixed), "|%d|%d|%d|%d|%d|%d|%d", S.p->tile_cols, S.p->tile_threads, S.p->tile_vec,
            S.p->tile_csr, S.p->tile_reg, S.p->tile_sb, deg_class);
-  const std::string key = "tile|" + R.gpu + "|" + tile_key(S) + fixed;
-  std::string cached;
-  if (tune_get(key, &cached)) {
-    TileCfg c{};
-    double ms = 0.0;
-    if (std::sscanf(cached.c_str(), "%d %d %d %d %d %d %d %lf", &c.T, &c.threads, &c.vec, &c.csr, &c.dreg, &c.ipt,
-                    &c.sb, &ms) == 8 &&
-        tile_feasible(S, c) && (c.dreg == 0 || c.dreg >= md)) {
-      *out = c;
-      if (ms_per_step) *ms_per_step = ms;
-      return MQO_OK;
+  // "tile": the fastest shape per step; "build", where that is a sliced one:
+  // its build's time and the fastest shape that needs none
+  const std::string shape_key = R.gpu + "|" + tile_key(S) + fixed;
+  const std::string key = "tile|" + shape_key, build_key = "build|" + shape_key;
+  TunedTile fastest, plain;
+  double build_ms = 0.0;
+  auto take = [&]() {
+    const TunedTile &t = for_this_solve(S, fastest, build_ms, plain);
+    *out = t.c;
+    if (ms_per_step) *ms_per_step = t.ms;
+    return MQO_OK;
+  };
+  std::string cached, with_build;
+  if (tune_get(key, &cached) && parse_tuned(S, cached.c_str(), &fastest)) {
+    int at = 0;
+    if (fastest.c.sb < TILE_ELL || !tune_get(build_key, &with_build) ||
+        std::sscanf(with_build.c_str(), "%lf %n", &build_ms, &at) != 1 ||
+        !parse_tuned(S, with_build.c_str() + at, &plain)) {
+      build_ms = 0.0;
+      plain = fastest;
     }
+    return take();
   }
+  fastest = plain = TunedTile{};
   // widest tiles first: they are the ones that fill the card on large
   // batches, and a fast one early lets the slow ones go after their probe
   std::vector<TileCfg> cands = tile_candidates(S);
@@ -1482,8 +1523,6 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
   // one, 555 ms a solve instead of 528).
   cands.push_back(cands.front());
   S.trials = true;
-  TileCfg best_c = cands[0];
-  double best_t = 1e30;
   const int tsteps = std::max(1, std::min(S.p->steps_per_round, 64));
   {
     hipEvent_t e0, e1;
@@ -1501,8 +1540,8 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       float ms = 0.f;
       if (c.sb >= TILE_ELL && launch_ell_build(a, S.s) != hipSuccess) continue;
       // warm-up, and a probe of a few steps: a shape that takes over three
-      // times the best one's time (and a millisecond for its first launch)
-      // is not timed further.  On 128 graphs x 512 trajectories, where the
+      // times the best one's time of its kind (and a millisecond for its
+      // first launch) is not timed further.  On 128 graphs x 512 trajectories, where the
       // narrow tiles are up to 50 times slower, tuning took 19 s without it.
       a.steps = std::min(tsteps, 8);
       HIP_TRY(hipEventRecord(e0, S.s));
@@ -1510,7 +1549,15 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       HIP_TRY(hipEventRecord(e1, S.s));
       HIP_TRY(hipEventSynchronize(e1));
       HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-      if (ms > 3.0f * (float)best_t * (float)a.steps + 1.0f) continue;
+      if (ms > 3.0f * (float)(c.sb >= TILE_ELL ? fastest.ms : plain.ms) * (float)a.steps + 1.0f) continue;
+      float build = 0.f;
+      if (c.sb >= TILE_ELL) {  // once more: its first launches are over
+        HIP_TRY(hipEventRecord(e0, S.s));
+        (void)launch_ell_build(a, S.s);
+        HIP_TRY(hipEventRecord(e1, S.s));
+        HIP_TRY(hipEventSynchronize(e1));
+        HIP_TRY(hipEventElapsedTime(&build, e0, e1));
+      }
       a.steps = tsteps;
       HIP_TRY(hipEventRecord(e0, S.s));
       for (int rep = 0; rep < 2; ++rep) (void)launch_tile_round(mc, w, a, c.threads, S.s);
@@ -1518,21 +1565,25 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       HIP_TRY(hipEventSynchronize(e1));
       HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
       ms /= 2.0f * (float)tsteps;  // per step
-      if (ms < best_t) {
-        best_t = ms;
-        best_c = c;
+      if (ms < fastest.ms) {
+        fastest = {c, ms};
+        build_ms = build;
       }
+      if (c.sb < TILE_ELL && ms < plain.ms) plain = {c, ms};
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
   }
-  char val[128];
-  snprintf(val, sizeof(val), "%d %d %d %d %d %d %d %.6f", best_c.T, best_c.threads, best_c.vec, best_c.csr,
-           best_c.dreg, best_c.ipt, best_c.sb, best_t);
-  tune_put(key, val);
-  *out = best_c;
-  if (ms_per_step) *ms_per_step = best_t;
-  return MQO_OK;
+  if (fastest.ms >= 1e30) fastest = {cands[0], 1e30};  // no launch succeeded: the solve's own reports it
+  tune_put(key, tuned_text(fastest));
+  if (fastest.c.sb >= TILE_ELL && plain.ms < 1e30) {
+    char ms[32];
+    snprintf(ms, sizeof(ms), "%.6f ", build_ms);
+    tune_put(build_key, ms + tuned_text(plain));
+  } else {
+    plain = fastest;
+  }
+  return take();
 }
 
 // the launch covers every round of the solve
