@@ -1907,14 +1907,24 @@ int trial_plan_ms(Solve &S, int plan, double *ms) {
 // best persistent tile shape's round of steps against the best streaming
 // step launch) when one is more than twice as fast as the other, else per
 // solve, both plans timed on up to eight rounds of it (the rounds' other work --
-// rounding, search, reset, launches -- then decides).  Timed once per shape
-// key and cached.
+// rounding, search, reset, launches -- then decides).  Rounds of fewer than 64
+// steps that take less than a millisecond are timed per solve too, and such
+// choices cached by the rounds and the power of two of the steps: the slices'
+// build and the search weigh more than the steps there (n = 3000, degree 100,
+// 64 trajectories, one round of 10 steps: 4 us a step against 19, but 1.36 ms
+// a solve against 1.05).  Timed once per shape key and cached.
 int choose_plan(Solve &S, int *plan) {
   if (!tile_possible(S)) {
     *plan = MQO_PLAN_BATCHED;
     return MQO_OK;
   }
-  const std::string key = "plan|" + res().gpu + "|" + tile_key(S);
+  std::string key = "plan|" + res().gpu + "|" + tile_key(S);
+  bool brief = S.p->steps_per_round < 64;
+  if (brief) {
+    int bits = 0;
+    while (S.p->steps_per_round >> bits) ++bits;
+    key += "|s" + std::to_string(bits) + "r" + std::to_string(std::min(8, S.p->rounds));
+  }
   std::string cached;
   if (tune_get(key, &cached)) {
     if (cached.rfind("persistent", 0) == 0) {
@@ -1962,9 +1972,14 @@ int choose_plan(Solve &S, int *plan) {
   }
   *plan = step_ms < tile_ms ? MQO_PLAN_BATCHED : MQO_PLAN_PERSISTENT;
   double trial_p = -1.0, trial_b = -1.0;
-  if (step_ms < 2.0 * tile_ms && tile_ms < 2.0 * step_ms) {
-    TRY(trial_plan_ms(S, MQO_PLAN_PERSISTENT, &trial_p));
-    TRY(trial_plan_ms(S, MQO_PLAN_BATCHED, &trial_b));
+  brief = brief && S.p->steps_per_round * std::min(step_ms, tile_ms) < 1.0;
+  if (brief || (step_ms < 2.0 * tile_ms && tile_ms < 2.0 * step_ms)) {
+    // (the first launches of kernels count for more than a brief solve: its
+    // second trial is the one that counts)
+    for (int i = 0; i < (brief ? 2 : 1); ++i) {
+      TRY(trial_plan_ms(S, MQO_PLAN_PERSISTENT, &trial_p));
+      TRY(trial_plan_ms(S, MQO_PLAN_BATCHED, &trial_b));
+    }
     *plan = trial_b < trial_p ? MQO_PLAN_BATCHED : MQO_PLAN_PERSISTENT;
   }
   char val[128];
