@@ -376,6 +376,13 @@ T *at(void *ws, size_t off) {
 
 // max_deg: the largest degree if known (a solve measures it), else -1 for
 // the caller's hint g->max_degree (0 = unknown)
+// no row of many times the mean degree (the rule that lists hubs by default);
+// max_deg 0: not known
+int32_t degrees_even(const mqo_graph *g, int64_t max_deg) {
+  const int64_t mean = (g->nnz_total + g->n_total - 1) / g->n_total;
+  return max_deg > 0 && max_deg <= std::max<int64_t>(128, 8 * mean) ? 1 : 0;
+}
+
 GraphView view_of(const mqo_graph *g, int32_t i, int32_t max_deg = -1) {
   GraphView v;
   v.row_ptr = g->row_ptr;
@@ -396,6 +403,7 @@ GraphView view_of(const mqo_graph *g, int32_t i, int32_t max_deg = -1) {
   const int64_t md = max_deg >= 0 ? max_deg : g->max_degree;
   v.pairs = md > 0 && 10 * g->nnz_total >= 9 * g->n_total * md ? 1 : 0;
   v.xcd_local = g->local_rows == 1;
+  v.even = degrees_even(g, md);
   return v;
 }
 
@@ -721,6 +729,7 @@ GraphView whole_view(const mqo_graph *g) {
   v.hub_deg = 0x7fffffff;
   v.pairs = 0;
   v.xcd_local = g->local_rows == 1;
+  v.even = degrees_even(g, g->max_degree);
   return v;
 }
 
@@ -735,7 +744,9 @@ GraphView batch_view(const mqo_graph *g, int32_t max_deg) {
     v.nhub = (int32_t)g->hub_offset[g->num_graphs];
     v.hub_deg = g->hub_min_degree;
   }
-  v.pairs = view_of(g, 0, max_deg).pairs;
+  const GraphView first = view_of(g, 0, max_deg);
+  v.pairs = first.pairs;
+  v.even = first.even;
   return v;
 }
 

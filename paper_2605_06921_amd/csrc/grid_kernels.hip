@@ -2805,8 +2805,8 @@ static inline dim3 row_grid(int64_t nrows, int32_t ncols, const LiveCols &live, 
   return dim3((unsigned)((nrows + 3) / 4), (unsigned)((chunks + *per_wave - 1) / *per_wave), 1);
 }
 
-// whether the per-column searches take four columns per lane: 4-byte access
-// to the states and flags, 16-byte access to the 32-bit arrays
+// whether rows allow a lane four columns: 4-byte access to the states and
+// flags, 16-byte access to the 32-bit arrays
 static inline bool four_columns(int32_t ncols, int32_t ld, std::initializer_list<const void *> bytes,
                                 std::initializer_list<const void *> words) {
   if (ncols % 4 != 0 || ld % 4 != 0) return false;
@@ -2817,6 +2817,31 @@ static inline bool four_columns(int32_t ncols, int32_t ld, std::initializer_list
   return true;
 }
 
+// Where the per-column searches take them.  A lane's four columns share the
+// passes over the states, which is most of a search of many entries; but one
+// column after the other walks its rows, and the chip has a quarter of the
+// wavefronts, which is most of a search of few (times of whole searches from
+// a random start, one column / four columns):
+// * the 1-flip search from 2^20 entries on (n = 8000, 64 columns 385 / 455
+//   us; n = 20000, 64: 589 / 571; n = 100 000, 64: 1812 / 1491, degree 10),
+//   and only where no row holds up the others: its chain of reads gets
+//   longer (preferential attachment, n = 20000, m = 8: 4.57 / 6.69 ms;
+//   n = 100 000: 10.2 / 14.0);
+// * a pair's best edge where neighbours are close in the vertex order, from
+//   2^21 entries on (torus 300 x 300, 32 columns 970 / 953 us, 500 x 500
+//   1605 / 1490; random graphs lose 1 - 4% at every size);
+// * a pair's selection and application, which walk two rows per proposal, on
+//   degrees of at most 8 from 2^22 entries on (random 5-regular, n = 300 000,
+//   32 columns 327 / 316 us; degree 10 with as many 1.00, degree 20 0.99,
+//   n = 1000 of degree 100 0.78 times as fast).
+static inline bool four_in_search(const GraphView &g, int32_t ncols) { return g.even && g.n * ncols >= (1 << 20); }
+static inline bool four_in_pair_best(const GraphView &g, int32_t ncols) {
+  return g.even && g.xcd_local && g.n * ncols >= (1 << 21);
+}
+static inline bool four_in_pair_moves(const GraphView &g, int32_t ncols, double mean_degree) {
+  return g.even && mean_degree <= 8.0 && g.n * ncols >= (1 << 22);
+}
+
 void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, const int32_t *NB,
                             const uint32_t *PRIO, int32_t *T0, int32_t *T1, int32_t *T2, uint32_t *TB, int32_t ncols,
                             int32_t ld, double mean_degree, hipStream_t s, LiveCols live) {
@@ -2824,7 +2849,7 @@ void launch_pair_candidates(bool maxcut, const GraphView &g, const int8_t *Z, co
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   if (maxcut) {
     uint32_t *bh = reinterpret_cast<uint32_t *>(T1);
-    if (four_columns(ncols, ld, {Z}, {NB, PRIO, T0, T1, T2})) {
+    if (four_in_pair_best(g, ncols) && four_columns(ncols, ld, {Z}, {NB, PRIO, T0, T1, T2})) {
       const int ll4 = lanes_log2_for(ncols / 4);
       const dim3 grid4 = grid_rows(g.n, ncols, ll4, 4, 256);
       if (g.weight)
@@ -2857,7 +2882,7 @@ void launch_pair_apply(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB, 
   const dim3 grid = grid_rows(g.n, ncols, ll, 1, 256);
   if (maxcut) {
     const uint32_t *bh = reinterpret_cast<const uint32_t *>(T1);
-    if (four_columns(ncols, ld, {F}, {T2})) {
+    if (four_in_pair_moves(g, ncols, mean_degree) && four_columns(ncols, ld, {F}, {T2})) {
       const int ll4 = lanes_log2_for(ncols / 4);
       const dim3 grid4 = grid_rows(g.n, ncols, ll4, 4, 256);
       MQO_LAUNCH(k_flip2_select<4>, grid4, dim3(256), 0, s, g, T0, bh, T2, F, active, ncols, ld, ll4);
@@ -2925,7 +2950,7 @@ void launch_ls_iteration(bool maxcut, const GraphView &g, int8_t *Z, int32_t *NB
   } else {                                  \
     MQO_LS(false, false, VEC, GRID, LL)     \
   }
-  if (four_columns(ncols, ld, {Z, F}, {NB, PRIO})) {
+  if (four_in_search(g, ncols) && four_columns(ncols, ld, {Z, F}, {NB, PRIO})) {
     const int ll4 = lanes_log2_for(ncols / 4);
     const dim3 grid4 = grid_rows(g.n, ncols, ll4, 4, 256);
     MQO_LS_FORM(4, grid4, ll4)
