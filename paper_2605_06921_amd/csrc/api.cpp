@@ -2155,13 +2155,17 @@ size_t objective_workspace_min(const mqo_graph *g, int32_t B) {
 }
 
 // graph z of a table that starts at graph g0: appends it and returns true if
-// it leaves at most max_rows partial rows (0: no limit)
+// it leaves at most max_rows partial rows (0: no limit) and, after the first
+// graph, a grid of less than 2^32 threads (a launch takes no more; 64 graphs
+// of a million rows at 64 lanes a row have that many)
+constexpr int64_t MAX_ROW_BLOCKS = ((int64_t)1 << 24) - 1;  // of 256 threads
 bool table_add(GraphTable &t, const mqo_graph *g, int32_t gi, StepCfg cfg, int32_t B, int64_t max_rows) {
   if (t.count == GRAPH_TABLE) return false;
   const int32_t z = t.count;
   const int64_t blk = spmm_row_blocks(view_of(g, gi), cfg), sl = reduce_slices(blk, B);
   const int64_t blocks = (z ? t.blk[z] : 0) + blk, slices = (z ? t.sl[z] : 0) + sl;
-  if (blocks > INT32_MAX || (max_rows > 0 && blocks + slices > max_rows)) return false;
+  if (blocks > INT32_MAX || (z > 0 && blocks > MAX_ROW_BLOCKS) || (max_rows > 0 && blocks + slices > max_rows))
+    return false;
   if (z == 0) {
     t.lo[0] = (int32_t)g->vtx_offset[gi];
     t.blk[0] = t.sl[0] = 0;
