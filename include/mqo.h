@@ -220,7 +220,11 @@ typedef struct {
                               (a step reads one, writes the other), 2 = one
                               buffer (a step gathers into registers, then
                               writes in place: twice the trajectories per
-                              workgroup fit), 0 = autotune                  */
+                              workgroup fit), 0 = autotune.  The sliced
+                              adjacency is offered by the autotuner alone:
+                              any of tile_vec, tile_csr, tile_reg and
+                              tile_sb that is not 0 asks for the general
+                              step loop                                     */
 } mqo_params;
 
 /* Outputs of a solve.  Device arrays are written; host fields are set. */
@@ -259,13 +263,23 @@ typedef struct {
                                   the step kernel (0 on the persistent plan) */
   int32_t step_lanes_used;     /* (host) streaming plans: lanes per row       */
   int32_t tile_single_buffer_used; /* (host) persistent plan: 1 = one iterate
-                                  buffer in LDS                              */
+                                  buffer in LDS (wide slices of 16 to 64
+                                  trajectories too; narrow slices, of up to 4,
+                                  report 0 and tile_vec_used =
+                                  tile_cols_used).  Shapes fixed by these
+                                  fields take the general step loop          */
 } mqo_result;
 
 void mqo_params_default(mqo_params *p);
 
-/* Bytes of workspace a solve needs (0 on invalid input).  The same size
- * covers every plan. */
+/* Bytes of workspace a solve with these parameters wants (0 on invalid
+ * input).  The size for any plan covers every plan.  Where the persistent
+ * plan may lay the rows of unweighted graphs of at most 8192 vertices out in
+ * slices (plan AUTO or PERSISTENT, tile_vec, tile_csr, tile_reg and tile_sb
+ * 0), it includes their room: 288 bytes a row and 8 bytes a stored entry.
+ * A solve whose workspace is that much smaller, the size for
+ * MQO_PLAN_BATCHED, runs without them, with the same results; so do the
+ * searches and the other calls that take this size. */
 size_t mqo_workspace_size(const mqo_graph *g, const mqo_params *p, mqo_objective obj);
 
 /* Batched mutation-guided search (Alg. 1 for MIS, Alg. 2 for MaxCut, run as

@@ -292,13 +292,13 @@ int64_t max_graph_rows(const mqo_graph *g) {
 struct Layout {
   size_t X, Xt, V, Z, Zb, NB, PRIO, F, value, best, acc, act, voff, rpat, bestb, dmax, err, reset, tzs, tnb, tprio,
       tfl, tvm, tail, tls, gorder, lsval, pX, pXt, pV, colact, fixedc, steps, pz[2], pv[2], ph[2], chash, ptaken, psrc,
-      pbase, solz, solv, choice, rgraph, live, eord, estart, eblock, total;
+      pbase, solz, solv, choice, rgraph, live, base, eord, estart, eblock, total;
 };
 
 constexpr int TAIL_INTS = 4;  // Layout::tail before the counters: edge updates, tile error, unused
 
-// K: pool slots per graph (0 = no pool); the pool buffers come last, so the
-// other offsets do not depend on K
+// K: pool slots per graph (0 = no pool).  base: the bytes that every solve and
+// search needs; the sliced adjacency of the persistent plan lies after them.
 Layout make_layout(const mqo_graph *g, int32_t B, int32_t K = 0) {
   Layout L{};
   const int64_t n = g->n_total, G = g->num_graphs, nb = n * B;
@@ -360,6 +360,7 @@ Layout make_layout(const mqo_graph *g, int32_t B, int32_t K = 0) {
   L.choice = take(K ? G * 4 : 0);
   L.rgraph = take(n * 4);  // pair searches: the graph of every row, live columns (two buffers)
   L.live = take(2 * G * ((B + 63) / 64) * 8);
+  L.base = o;
   // persistent plan: the sliced adjacency (shapes that any tile can have)
   const bool ell = max_graph_rows(g) <= 8192 && !g->weight;
   L.eord = take(ell ? n * 2 : 0);
@@ -367,6 +368,16 @@ Layout make_layout(const mqo_graph *g, int32_t B, int32_t K = 0) {
   L.eblock = take(ell ? ell_block_bytes(n, g->nnz_total, G) : 0);
   L.total = o;
   return L;
+}
+
+// whether a solve's tuner offers the sliced shapes, if the workspace has room
+// for them (288 bytes a row and 8 a stored entry): unweighted h or f_B on a
+// plan that may be persistent, no step-loop shape asked for
+bool slices_wanted(const mqo_graph *g, const mqo_params *p, mqo_objective obj) {
+  const bool form = obj == MQO_OBJ_MIS_H || p->maxcut_objective == MQO_OBJ_MAXCUT_FB;
+  return form && !g->weight && max_graph_rows(g) <= 8192 &&
+         (p->plan == MQO_PLAN_AUTO || p->plan == MQO_PLAN_PERSISTENT) && !p->tile_vec && !p->tile_csr &&
+         !p->tile_reg && !p->tile_sb;
 }
 
 template <typename T>
@@ -527,6 +538,7 @@ struct Solve {
   int8_t *Zb = nullptr;    // incumbents [n_total][B]: the caller's traj_best_x when given, else workspace
   int64_t *best = nullptr; // incumbent values [G*B]: the caller's traj_best_value when given, else workspace
   int64_t ls_iters = 0;
+  bool slices_wanted = false, slices = false;  // the sliced shapes: asked for by the call; with room in the workspace
   int64_t search_alt = 0;  // pair iterations that applied a move, summed over the pass searches
   StepCfg step_cfg{0, 0};  // streaming plans: the step kernel's launch shape (of the first loop)
   int32_t deferred_tile_wg = 0;  // > 0: the tile counters are read back with the solve's last synchronisation
@@ -1306,7 +1318,7 @@ int64_t nnz_max_of(const Solve &S) {
 
 bool tile_feasible(const Solve &S, const TileCfg &c) {
   return tile_shape_ok(S.n_max, c.T, c.threads, c.vec, c.csr != 0, c.dreg, c.ipt, c.sb) &&
-         !(c.sb >= TILE_ELL && S.g->weight) &&
+         (c.sb < TILE_ELL || S.slices) &&
          (int64_t)tile_lds_bytes(S.n_max, c.T, nnz_max_of(S), c.csr != 0, c.dreg > 0, c.sb) <=
              tile_lds_budget() - (c.sb >= TILE_ELL ? 2048 : 0);  // their static slice tables
 }
@@ -1440,16 +1452,14 @@ std::vector<TileCfg> tile_candidates(const Solve &S) {
             if (tile_feasible(S, c)) out.push_back(c);
           }
         }
-      // sliced adjacency: all T columns of a row in one lane; offered where no
-      // step-loop shape is asked for
-      if (!S.p->tile_vec && !S.p->tile_csr && !S.p->tile_reg && !S.p->tile_sb && T <= 4) {
+      // sliced adjacency (slices_wanted): all T columns of a row in one lane,
+      // or wide slices
+      if (T <= 4) {
         const TileCfg c{T, th, T, 0, 0, 0, TILE_ELL};
         if (tile_feasible(S, c)) out.push_back(c);
       }
-      if (!S.p->tile_vec && !S.p->tile_csr && !S.p->tile_reg && !S.p->tile_sb) {
-        const TileCfg c{T, th, 4, 0, 0, 0, TILE_WIDE};
-        if (tile_feasible(S, c)) out.push_back(c);
-      }
+      const TileCfg c{T, th, 4, 0, 0, 0, TILE_WIDE};
+      if (tile_feasible(S, c)) out.push_back(c);
     }
   }
   return out;
@@ -1501,7 +1511,8 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
            S.p->tile_csr, S.p->tile_reg, S.p->tile_sb, deg_class);
   // "tile": the fastest shape per step; "build", where that is a sliced one:
   // its build's time and the fastest shape that needs none
-  const std::string shape_key = R.gpu + "|" + tile_key(S) + fixed;
+  // (solves whose workspace has no room for slices choose apart)
+  const std::string shape_key = R.gpu + "|" + tile_key(S) + fixed + (S.slices_wanted && !S.slices ? "|plain" : "");
   const std::string key = "tile|" + shape_key, build_key = "build|" + shape_key;
   TunedTile fastest, plain;
   double build_ms = 0.0;
@@ -2012,7 +2023,8 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
       return fail(MQO_ERR_INVALID_ARG, "traj_ids must be strictly ascending trajectory ids below G * batch");
   }
   const Layout L = make_layout(g, p->batch, p->pool_k);
-  if (!ws || ws_bytes < L.total) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.total);
+  const bool slices = slices_wanted(g, p, obj);
+  if (!ws || ws_bytes < L.base) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", slices ? L.total : L.base);
   TRY(ensure_resources());
   std::lock_guard<std::mutex> host_lock(res().host_mu);
   Resources &R = res();
@@ -2030,6 +2042,8 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
   S.obj = obj;
   S.maxcut = obj != MQO_OBJ_MIS_H;
   S.form = S.maxcut ? p->maxcut_objective : (int)MQO_OBJ_MIS_H;
+  S.slices_wanted = slices;
+  S.slices = slices && ws_bytes >= L.total;
   S.param = S.maxcut ? p->lambda : p->gamma;
   S.B = p->batch;
   S.G = g->num_graphs;
@@ -2249,7 +2263,8 @@ void mqo_params_default(mqo_params *p) {
 
 size_t mqo_workspace_size(const mqo_graph *g, const mqo_params *p, mqo_objective obj) {
   if (check_graph_args(g, obj == MQO_OBJ_MIS_H) != MQO_OK || !p || p->batch < 1) return 0;
-  return make_layout(g, p->batch, p->pool_k >= 0 && p->pool_k <= 64 ? p->pool_k : 0).total;
+  const Layout L = make_layout(g, p->batch, p->pool_k >= 0 && p->pool_k <= 64 ? p->pool_k : 0);
+  return slices_wanted(g, p, obj) ? L.total : L.base;
 }
 
 int mqo_solve_mis(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_result *r, void *ws,
@@ -2486,7 +2501,7 @@ int mqo_round_evaluate(const mqo_graph *g, mqo_objective obj, const float *X, in
   TRY(check_async(g, obj, B));
   if (!X || !Z || !value) return fail(MQO_ERR_INVALID_ARG, "X, Z and value are required");
   const Layout L = make_layout(g, B);
-  if (!ws || ws_bytes < L.total) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.total);
+  if (!ws || ws_bytes < L.base) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.base);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   drop_stale_error();
   const bool mc = obj != MQO_OBJ_MIS_H;
@@ -2507,7 +2522,7 @@ int mqo_local_search(const mqo_graph *g, mqo_objective obj, int32_t B, uint64_t 
   TRY(check_async(g, obj, B));
   if (!Z) return fail(MQO_ERR_INVALID_ARG, "Z is NULL");
   const Layout L = make_layout(g, B);
-  if (!ws || ws_bytes < L.total) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.total);
+  if (!ws || ws_bytes < L.base) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.base);
   TRY(ensure_resources());
   std::lock_guard<std::mutex> host_lock(res().host_mu);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -2537,7 +2552,7 @@ int mqo_pair_search(const mqo_graph *g, mqo_objective obj, int32_t B, uint64_t s
   const bool mc = obj != MQO_OBJ_MIS_H;
   if (!mc && g->weight) return fail(MQO_ERR_INVALID_ARG, "MIS graphs carry no weights");
   const Layout L = make_layout(g, B);
-  if (!ws || ws_bytes < L.total) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.total);
+  if (!ws || ws_bytes < L.base) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.base);
   TRY(ensure_resources());
   std::lock_guard<std::mutex> host_lock(res().host_mu);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -2557,7 +2572,7 @@ int mqo_reset(const mqo_graph *g, mqo_objective obj, int32_t B, uint64_t seed, i
   if (mode != MQO_RESET_ZERO && mode != MQO_RESET_FLIP) return fail(MQO_ERR_INVALID_ARG, "bad reset mode");
   if (!Zbest || !X) return fail(MQO_ERR_INVALID_ARG, "Zbest and X are required");
   const Layout L = make_layout(g, B);
-  if (!ws || ws_bytes < L.total) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.total);
+  if (!ws || ws_bytes < L.base) return fail(MQO_ERR_WORKSPACE, "workspace needs %zu bytes", L.base);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   drop_stale_error();
   const bool mc = obj != MQO_OBJ_MIS_H;

@@ -381,7 +381,7 @@ def solve_maxcut(dg, **kw):
 # --------------------------------------------------------------------------
 
 def _solve_ws(dg, kind, B, workspace=None):
-    p = make_params(batch=B)
+    p = make_params(batch=B, plan="batched")  # a search needs no room for the persistent plan's slices
     nbytes = _lib.mqo_workspace_size(dg.struct, ctypes.byref(p), _KIND[kind])
     return _ws_for(dg.device, workspace).get(nbytes), nbytes
 
