@@ -7,6 +7,7 @@ same library to load instead (for comparing kernel variants).
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -514,17 +515,27 @@ def objective_grad_static(kind, dg: DeviceGraph, X: torch.Tensor, param: float, 
     return f, grad
 
 
+@functools.lru_cache(maxsize=None)
+def _kept_gradient_bytes(device) -> int:
+    """The largest gradient that an Objective keeps from its forward to its
+    backward: a sixteenth of the GPU's memory."""
+    return torch.cuda.get_device_properties(device).total_memory // 16
+
+
 class Objective(torch.autograd.Function):
     """f(X) per trajectory (h of Eq. (3) or f_B of Eq. (7)); the gradient is
     dL/dX = dL/df_b * (c + H x).  Where a gradient will be asked for, the
-    forward's sparse product writes c + H x too (the backward then only
-    scales it); otherwise the backward runs the product."""
+    forward's sparse product writes c + H x too and keeps it, one more array
+    like X until the backward has run, which then only scales it.  Otherwise,
+    and where that array is larger than a sixteenth of the GPU's memory, the
+    backward runs the product and nothing but X is kept."""
 
     @staticmethod
     def forward(ctx, X, dg, kind, param, want_grad=None):
         if want_grad is None:
             want_grad = ctx.needs_input_grad[0]
-        f, grad = objective_grad(kind, dg, X, param, want_grad=want_grad and X.is_contiguous())
+        want_grad = want_grad and X.is_contiguous() and 4 * X.numel() <= _kept_gradient_bytes(dg.device)
+        f, grad = objective_grad(kind, dg, X, param, want_grad=want_grad)
         # X is kept in both cases: a change to it before the backward is refused
         ctx.save_for_backward(X, grad)
         ctx.dg, ctx.kind, ctx.param = dg, kind, param
