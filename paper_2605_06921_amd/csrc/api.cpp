@@ -1305,10 +1305,9 @@ int solve_plain(Solve &S, int32_t *rounds_done) {
 // ---------------------------------------------------------------------------
 // persistent tile plan + autotuner
 // ---------------------------------------------------------------------------
-int tile_lds_budget() {
-  const int static_lds = 4 * 64 * 4 + 2 * 64 * 8 + 64 * 4 + 2 * 4 + 256;
-  return std::min(res().lds_limit, 160 * 1024) - static_lds;
-}
+// dynamic LDS a workgroup of the tile kernel can ask for: what its static
+// arrays leave of 160 KB (the sliced shapes have a table of slices there)
+int tile_lds_budget(bool sliced) { return std::min(res().lds_limit, 160 * 1024) - tile_static_lds(sliced); }
 
 int64_t nnz_max_of(const Solve &S) {
   int64_t m = 0;
@@ -1320,7 +1319,7 @@ bool tile_feasible(const Solve &S, const TileCfg &c) {
   return tile_shape_ok(S.n_max, c.T, c.threads, c.vec, c.csr != 0, c.dreg, c.ipt, c.sb) &&
          (c.sb < TILE_ELL || S.slices) &&
          (int64_t)tile_lds_bytes(S.n_max, c.T, nnz_max_of(S), c.csr != 0, c.dreg > 0, c.sb) <=
-             tile_lds_budget() - (c.sb >= TILE_ELL ? 2048 : 0);  // their static slice tables
+             tile_lds_budget(c.sb >= TILE_ELL);
 }
 
 // any shape at all fits (plan selection)
@@ -2160,10 +2159,7 @@ size_t partial_count(const mqo_graph *g, int32_t B, int32_t copies = 1) {
   return (size_t)(nblk + reduce_rows(nblk)) * B;
 }
 
-// objective and gradient of every graph after validation; part: the float64
-// partial rows (partial_count doubles), needed when f_out is requested
-// objective_workspace: that for the largest graph, and up to 4 MiB so that
-// graphs share launches; ws_bytes: what the caller gave.
+// the smallest workspace that is accepted: the partial rows of the largest graph
 size_t objective_workspace_min(const mqo_graph *g, int32_t B) {
   return align_up(partial_count(g, B) * sizeof(double));
 }
@@ -2191,6 +2187,10 @@ bool table_add(GraphTable &t, const mqo_graph *g, int32_t gi, StepCfg cfg, int32
   return true;
 }
 
+// objective and gradient of every graph, after the checks of the entry
+// points; part_ws, ws_bytes: room for the float64 partial rows, needed when
+// f_out is requested (at least objective_workspace_min; more lets more graphs
+// share a launch)
 int objective_grad_run(const mqo_graph *g, mqo_objective obj, float param, const float *X, int32_t B,
                        const float *scale, double *f_out, float *grad_out, void *part_ws, size_t ws_bytes,
                        void *stream) {
@@ -2293,6 +2293,7 @@ size_t mqo_objective_workspace_size(const mqo_graph *g, int32_t B) {
       const int64_t blk = spmm_row_blocks(view_of(g, gi), default_step_cfg(B, B));
       rows += (size_t)(blk + reduce_slices(blk, B));
     }
+  // what the largest graph needs, and up to 4 MiB so that graphs share launches
   return std::max(objective_workspace_min(g, B),
                   std::min(align_up(rows * B * sizeof(double)), (size_t)4 << 20));
 }

@@ -724,10 +724,10 @@ __device__ __forceinline__ void raise_flag(bool any, int32_t *active) {
 // when P is non-empty.  When prev_active is given and *prev_active == 0
 // the search has already stopped and the kernel does nothing.
 // Once the search has settled an iteration is one pass over the states and
-// counts, so a lane takes VEC = 4 columns where rows allow 4- and 16-byte
-// access (1000 x 1000 torus, 32 trajectories: select 33 us and apply 25 us an
-// iteration, with one column per lane 63 and 41); the neighbours of its
-// candidates are read for the four columns together.
+// counts, so in large searches a lane takes VEC = 4 columns (1000 x 1000 torus,
+// 32 trajectories: select 33 us and apply 25 us an iteration, with one column
+// per lane 63 and 41; where the line lies: four_in_search); the neighbours of
+// its candidates are read for the four columns together.
 template <bool MAXCUT, int VEC>
 __global__ __launch_bounds__(256) void k_ls_select(GraphView g, const int8_t *__restrict__ Z,
                                                    const int32_t *__restrict__ NB, const uint32_t *__restrict__ PRIO,
@@ -1356,8 +1356,8 @@ __device__ __forceinline__ bool pair_beats(int32_t ga, uint32_t ha, int32_t mina
 
 // Best improving cut edge at v: gain g_v + g_u + 2 w > 0 (g = s t the 1-flip
 // gains), largest pair key.  BG = gain, BH = hash, BP = CSR position or -1.
-// VEC = 4 columns per lane where rows allow 16-byte access (184 us on the
-// 1000 x 1000 torus with 32 trajectories, 317 with one column per lane).
+// VEC = 4 columns per lane: 184 us on the 1000 x 1000 torus with 32
+// trajectories, 317 with one (where the line lies: four_in_pair_best).
 template <bool WEIGHTED, int VEC>
 __global__ __launch_bounds__(256) void k_flip2_best(GraphView g, const int8_t *__restrict__ Z,
                                                     const int32_t *__restrict__ NB, const uint32_t *__restrict__ PRIO,
@@ -1423,8 +1423,9 @@ __global__ __launch_bounds__(256) void k_flip2_best(GraphView g, const int8_t *_
 }
 
 // The lower end v of a mutual pair (v, u) applies it (F[v] = 1) when no
-// other vertex adjacent to v or u holds a larger best-pair key.  (VEC = 4 as
-// above: 109 us against 145, the application 76 against 94.)
+// other vertex adjacent to v or u holds a larger best-pair key.  (VEC = 4 on
+// that torus: 109 us against 145, the application 76 against 94; where the
+// line lies: four_in_pair_moves.)
 template <int VEC>
 __global__ __launch_bounds__(256) void k_flip2_select(GraphView g, const int32_t *__restrict__ BG,
                                                       const uint32_t *__restrict__ BH,

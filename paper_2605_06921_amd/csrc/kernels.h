@@ -229,6 +229,8 @@ constexpr int TILE_ELL = 2;   // TileArgs::sb of the sliced step loop
 constexpr int TILE_WIDE = 3;  // one iterate buffer, slices of the rows of a wavefront
 bool tile_shape_ok(int64_t n_max, int T, int threads, int vec, bool csr_lds, int dreg, int ipt, int sb);
 size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool state_lds, int sb);
+// bytes of the kernel's static LDS arrays, as built (callers hold the host lock)
+int tile_static_lds(bool sliced);
 size_t ell_slice_bytes(int64_t n_total, int64_t G);
 size_t ell_block_bytes(int64_t n_total, int64_t nnz_total, int64_t G);
 // writes what the shapes TILE_ELL and TILE_WIDE read (row order, slices, entries)

@@ -1251,6 +1251,22 @@ size_t tile_lds_bytes(int64_t n_max, int T, int64_t nnz_max, bool csr_lds, bool 
   return (b + 15) & ~(size_t)15;
 }
 
+int tile_static_lds(bool sliced) {
+  static int bytes[2] = {0, 0};
+  int &b = bytes[sliced ? 1 : 0];
+  if (b == 0) {
+    hipFuncAttributes fa{};
+    const void *k = sliced ? reinterpret_cast<const void *>(k_tile_round<true, false, 4, false, 0, 1, true, false, true>)
+                           : reinterpret_cast<const void *>(k_tile_round<true, false, 4, false, 0, 1, true, false, false>);
+    if (hipFuncGetAttributes(&fa, k) != hipSuccess) {
+      (void)hipGetLastError();
+      return 8192;
+    }
+    b = (int)fa.sharedSizeBytes;
+  }
+  return b;
+}
+
 template <bool MC, bool W, int VEC, bool CL, int DREG, int IPT, bool SB = false, bool ELL = false, bool WIDE = false>
 static hipError_t tile_launch_t(const TileArgs &a, int threads, hipStream_t s) {
   const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, ELL ? TILE_ELL : WIDE ? TILE_WIDE : SB ? 1 : 0);
@@ -1264,7 +1280,10 @@ static hipError_t tile_launch_t(const TileArgs &a, int threads, hipStream_t s) {
   if (dev < 0 || dev >= 64 || (int)lds > limit_set[dev]) {
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+      (void)hipGetLastError();  // not left for the next launch's check
+      return e;
+    }
     if (dev >= 0 && dev < 64) limit_set[dev] = (int)lds;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)(a.G * a.tiles)), dim3(threads), lds, s, a);
