@@ -2035,6 +2035,15 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
 
   const double wall0 = now_s();
   Solve S;
+  // a solve that fails leaves nothing running: the caller may free or reuse
+  // the workspace on its own stream at once
+  struct Drain {
+    hipStream_t s;
+    bool armed;
+    ~Drain() {
+      if (armed) (void)hipStreamSynchronize(s);
+    }
+  } drain{s, true};
   S.tracing = trace_target() != nullptr;
   S.g = g;
   S.p = p;
@@ -2123,6 +2132,7 @@ int solve_common(const mqo_graph *g, const mqo_params *p, const float *x0, mqo_r
   r->step_vec_used = plan == MQO_PLAN_PERSISTENT ? 0 : S.step_cfg.vec;
   r->step_lanes_used = plan == MQO_PLAN_PERSISTENT ? 0 : 1 << S.step_cfg.lanes_log2;
   if (S.tracing) write_trace(S, plan, rounds_done, 1e3 * (now_s() - wall0));
+  drain.armed = false;  // read_tail waited for everything
   return MQO_OK;
 }
 
