@@ -2251,9 +2251,11 @@ __global__ __launch_bounds__(256) void k_reduce_partials_batch(double *__restric
 
 // The backward of an objective from its unscaled gradient, one pass instead
 // of another sparse product (preferential-attachment graph, n = 1e5, 64
-// trajectories: 39 us of gathers against 10 us; the call with its forward
-// 124 -> 92 us where the host keeps up).  Four columns at a time where ncols
-// is a multiple of 4 and both arrays are 16-byte aligned.
+// trajectories: 10 us of kernel against 39; the call with its forward, bound by
+// the host, 126 -> 117 us, and the first call on new inputs as long as before.
+// A forward that is asked for a gradient and not followed by a backward writes
+// it for nothing: 55 -> 60 us on the random 5-regular graph).  Four columns at
+// a time where ncols is a multiple of 4 and both arrays are 16-byte aligned.
 template <int VEC>
 __global__ __launch_bounds__(256) void k_scale_rows(GraphTable t, const double *__restrict__ scale,
                                                     const float *__restrict__ grad, float *__restrict__ out,
@@ -2368,8 +2370,9 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double *__restric
 // a step; with the gradient recomputed for the mask as well it was 2.8 (K =
 // 20, checkpoints every 5: 56 products for the backward, now 40).  What
 // bounds each is the neighbour gathers; the kept gradients add one write and
-// one read of an array per step.  Random 5-regular n = 1e5, 64 trajectories,
-// forward and backward: 2.25 -> 1.94 ms.
+// one read of an array per step but a segment's last.  Random 5-regular n =
+// 1e5, 64 trajectories: forward and backward 2.26 -> 1.90 ms; the backward alone
+// 1620 -> 1266 us, with checkpoints at every step 1310 -> 1301.
 //
 // A kept gradient of a clipped entry (mask 0, mu = 0) is one of two NaNs: its
 // product <mu, g> is 0, or NaN where g is not finite.  An entry inside the box

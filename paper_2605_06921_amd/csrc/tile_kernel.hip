@@ -117,7 +117,8 @@ __host__ __device__ inline size_t tile_rord_offset(int64_t n_max, int T, bool si
 }
 __host__ __device__ inline size_t tile_cls_offset(int64_t n_max, int T, bool single_buf, bool row_order,
                                                   bool ell) {
-  const size_t b = tile_rord_offset(n_max, T, single_buf, ell) + (row_order ? (size_t)(n_max + 1) * sizeof(uint16_t) : 0);
+  const size_t b =
+      tile_rord_offset(n_max, T, single_buf, ell) + (row_order ? (size_t)(n_max + 1) * sizeof(uint16_t) : 0);
   return (b + 15) & ~(size_t)15;
 }
 __host__ __device__ inline size_t tile_state_offset(int64_t n_max, int T, int64_t nnz_max, bool csr_lds,
@@ -1256,9 +1257,9 @@ int tile_static_lds(bool sliced) {
   int &b = bytes[sliced ? 1 : 0];
   if (b == 0) {
     hipFuncAttributes fa{};
-    const void *k = sliced ? reinterpret_cast<const void *>(k_tile_round<true, false, 4, false, 0, 1, true, false, true>)
-                           : reinterpret_cast<const void *>(k_tile_round<true, false, 4, false, 0, 1, true, false, false>);
-    if (hipFuncGetAttributes(&fa, k) != hipSuccess) {
+    const auto k = sliced ? k_tile_round<true, false, 4, false, 0, 1, true, false, true>
+                          : k_tile_round<true, false, 4, false, 0, 1, true, false, false>;
+    if (hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(k)) != hipSuccess) {
       (void)hipGetLastError();
       return 8192;
     }
@@ -1269,7 +1270,8 @@ int tile_static_lds(bool sliced) {
 
 template <bool MC, bool W, int VEC, bool CL, int DREG, int IPT, bool SB = false, bool ELL = false, bool WIDE = false>
 static hipError_t tile_launch_t(const TileArgs &a, int threads, hipStream_t s) {
-  const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, ELL ? TILE_ELL : WIDE ? TILE_WIDE : SB ? 1 : 0);
+  const int sb = ELL ? TILE_ELL : WIDE ? TILE_WIDE : SB ? 1 : 0;
+  const size_t lds = tile_lds_bytes(a.n_max, a.T, a.nnz_max, CL, DREG > 0, sb);
   auto kern = k_tile_round<MC, W, VEC, CL, DREG, IPT, SB, ELL, WIDE>;
   // the dynamic-LDS limit only ever grows; raise it when a launch needs more
   // (per device; callers hold the library's host lock)
