@@ -385,8 +385,6 @@ T *at(void *ws, size_t off) {
   return reinterpret_cast<T *>(reinterpret_cast<char *>(ws) + off);
 }
 
-// max_deg: the largest degree if known (a solve measures it), else -1 for
-// the caller's hint g->max_degree (0 = unknown)
 // no row of many times the mean degree (the rule that lists hubs by default);
 // max_deg 0: not known
 int32_t degrees_even(const mqo_graph *g, int64_t max_deg) {
@@ -394,6 +392,8 @@ int32_t degrees_even(const mqo_graph *g, int64_t max_deg) {
   return max_deg > 0 && max_deg <= std::max<int64_t>(128, 8 * mean) ? 1 : 0;
 }
 
+// max_deg: the largest degree if known (a solve measures it), else -1 for
+// the caller's hint g->max_degree (0 = unknown)
 GraphView view_of(const mqo_graph *g, int32_t i, int32_t max_deg = -1) {
   GraphView v;
   v.row_ptr = g->row_ptr;
@@ -474,9 +474,9 @@ int read_back_many(const std::vector<std::pair<const int32_t *, int>> &parts, st
 // Device-side canonical-form check with one synchronisation: the column
 // and hub checks guard their own reads, so they run in the same pass as the
 // row_ptr check.  voff_dev must already hold vtx_offset; err_dev has room
-// for 4 ints (17 with dmax_dev = err_dev + 16).  When rpat_dev / dmax_dev are given, it also returns the
-// row_ptr entries at the graph boundaries (rp, G+1 values) and the largest
-// degree (max_deg).
+// for 4 ints (17 with dmax_dev = err_dev + 16).  When rpat_dev / dmax_dev are
+// given, it also returns the row_ptr entries at the graph boundaries (rp, G+1
+// values) and the largest degree (max_deg).
 int validate_on_device(const mqo_graph *g, int64_t *voff_dev, int32_t *err_dev, hipStream_t s,
                        int32_t *rpat_dev = nullptr, int32_t *dmax_dev = nullptr, std::vector<int32_t> *rp = nullptr,
                        int32_t *max_deg = nullptr) {
@@ -1562,8 +1562,9 @@ int tune_tile(Solve &S, const float *x0, TileCfg *out, double *ms_per_step = nul
       if (c.sb >= TILE_ELL && launch_ell_build(a, S.s) != hipSuccess) continue;
       // warm-up, and a probe of a few steps: a shape that takes over three
       // times the best one's time of its kind (and a millisecond for its
-      // first launch) is not timed further.  On 128 graphs x 512 trajectories, where the
-      // narrow tiles are up to 50 times slower, tuning took 19 s without it.
+      // first launch) is not timed further.  On 128 graphs x 512 trajectories,
+      // where the narrow tiles are up to 50 times slower, tuning took 19 s
+      // without it.
       a.steps = std::min(tsteps, 8);
       HIP_TRY(hipEventRecord(e0, S.s));
       if (launch_tile_round(mc, w, a, c.threads, S.s) != hipSuccess) continue;

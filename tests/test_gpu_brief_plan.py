@@ -37,7 +37,7 @@ def test_short_and_long_rounds_choose_apart(tmp_path):
     lib.mqo_clear_caches()
     long = mqo.solve("mis", dg, steps_per_round=200, rounds=2, **kw)
     short = dict(steps_per_round=10, rounds=1, **kw)
-    auto = solve_ms(mqo, dg, **short)
+    chosen = mqo.solve("mis", dg, **short)["plan"]
     each = {plan: solve_ms(mqo, dg, plan=plan, **short) for plan in ("persistent", "batched")}
     mqo.tune_cache_save(path)
     lib.mqo_clear_caches()
@@ -45,5 +45,5 @@ def test_short_and_long_rounds_choose_apart(tmp_path):
         plans = [ln.split("\t") for ln in f if ln.startswith("plan|")]
     assert len(plans) == 2 and plans[0][0] != plans[1][0]
     assert long["plan"] == "persistent"
-    # the chosen plan is within a tenth of the better one (they are a quarter apart)
-    assert auto <= 1.1 * min(each.values()), (auto, each)
+    # the chosen plan is the better one (they are a quarter apart), or as good
+    assert each[chosen] <= 1.1 * min(each.values()), (chosen, each)
